@@ -37,7 +37,8 @@ namespace {
 thread_local std::string g_init_error;
 
 constexpr int RED_BLOCKS = 512;          // blocks of every reduction launch (fixed: deterministic sums)
-constexpr int BW_BLOCKS = 256;           // blocks per vertex of the BW stage reduction
+constexpr int BW_BLOCKS = 1024;          // most blocks per vertex of the BW stage reduction
+constexpr int BW2_BLOCKS = 256;          // blocks per vertex of the partial-integration route's reductions
 constexpr size_t LINE_STATIC_LDS = 1024;  // bound on the line kernel's static LDS
 constexpr int NKIND = 6;                 // kernel-stats kinds (swf_kernel_stats)
 constexpr int PROF_POOL = 2048;          // event pairs kept in flight when profiling
@@ -690,7 +691,7 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         P.off_M2 = off = align256(off);
         off += sizeof(double2) * 3 * n_verts;
         P.off_part2 = off = align256(off);
-        off += sizeof(double2) * 4 * 9 * (size_t)BW_BLOCKS * n_verts;
+        off += sizeof(double2) * 4 * 9 * (size_t)BW2_BLOCKS * n_verts;
     }
     P.total = align256(off);
     return SWF_OK;
@@ -956,6 +957,7 @@ static int bw_stage(swf_ctx* ctx, int stage) {
     b.nst = ctx->P.nst;
     b.nvert = (int)ctx->P.hv.size();
     b.part = ctx->d_part();
+    b.nblk = BW_BLOCKS;
     b.M = ctx->d_M();
     b.groups = ctx->d_vgroups();
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -975,11 +977,16 @@ static int bw_stage(swf_ctx* ctx, int stage) {
         while (g1 < hg.size() && hg[g1].nu == hg[g0].nu && hg[g1].nv == hg[g0].nv) ++g1;
         swf::BwArgs bg = b;
         bg.groups = ctx->d_vgroups() + g0;
-        HIPCHK(swf::launch_bw_stage(ctx->P.fp64, bg, BW_BLOCKS, hg[g0].nu, hg[g0].nv, (int)(g1 - g0), ctx->st));
+        int nb = 1;
+        for (size_t g = g0; g < g1; ++g) nb = std::max(nb, swf::bw_blocks(ctx->P.hs[hg[g].su[0]].nsites, BW_BLOCKS));
+        HIPCHK(swf::launch_bw_stage(ctx->P.fp64, bg, nb, hg[g0].nu, hg[g0].nv, (int)(g1 - g0), ctx->st));
         g0 = g1;
     }
-    if (!ctx->P.packets.empty())
-        HIPCHK(swf::launch_bw_packet_stage(ctx->P.fp64, b, BW_BLOCKS, (int)ctx->P.packets.size(), ctx->st));
+    if (!ctx->P.packets.empty()) {
+        int nb = 1;
+        for (int v : ctx->P.packets) nb = std::max(nb, swf::bw_blocks(ctx->P.hs[ctx->P.hv[v].su].nsites, BW_BLOCKS));
+        HIPCHK(swf::launch_bw_packet_stage(ctx->P.fp64, b, nb, (int)ctx->P.packets.size(), ctx->st));
+    }
     if (prof) {
         // every state of a group's solves is read once; a packet reads its two
         double bytes = 0;
@@ -1002,8 +1009,9 @@ static int bw_accum(swf_ctx* ctx) {
     for (int st = 0; st < ctx->P.nst; ++st) b.wst[st] = ctx->P.wst[st];
     b.nvert = (int)ctx->P.hv.size();
     b.part = ctx->d_part();
+    b.nblk = BW_BLOCKS;
     b.M = ctx->d_M();
-    HIPCHK(swf::launch_bw_accum(b, BW_BLOCKS, ctx->st));
+    HIPCHK(swf::launch_bw_accum(b, ctx->st));
     return SWF_OK;
 }
 
@@ -1032,7 +1040,7 @@ static int bw2_stage(swf_ctx* ctx, int stage) {
     b.nvert = (int)P.hv.size();
     b.part2 = ctx->d_part2();
     b.M2 = ctx->d_M2();
-    HIPCHK(swf::launch_bw2_src(P.fp64, b, BW_BLOCKS, ctx->st));
+    HIPCHK(swf::launch_bw2_src(P.fp64, b, BW2_BLOCKS, ctx->st));
     // phase held by each solve's A0/A1: NONE = A1 still holds S in x space
     const long long NONE = -2;
     std::vector<long long> held(P.solves.size(), NONE);
@@ -1057,7 +1065,7 @@ static int bw2_stage(swf_ctx* ctx, int stage) {
         if (!r) r = transform(P.hv[v].sv, P.hv[v].phk);
         if (r) return r;
         b.vtx = v;
-        HIPCHK(swf::launch_bw2_kss(P.fp64, b, BW_BLOCKS, ctx->st));
+        HIPCHK(swf::launch_bw2_kss(P.fp64, b, BW2_BLOCKS, ctx->st));
     }
     return SWF_OK;
 }
@@ -1073,7 +1081,7 @@ static int bw2_accum(swf_ctx* ctx) {
     b.nvert = (int)ctx->P.hv.size();
     b.part2 = ctx->d_part2();
     b.M2 = ctx->d_M2();
-    HIPCHK(swf::launch_bw2_accum(b, BW_BLOCKS, ctx->st));
+    HIPCHK(swf::launch_bw2_accum(b, BW2_BLOCKS, ctx->st));
     return SWF_OK;
 }
 

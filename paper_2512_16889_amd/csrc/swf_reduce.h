@@ -61,6 +61,15 @@ struct VertexGroupDev {
     long long t2[BWG_SOLVES];             // V background phase exp(i k.x), per V solve
 };
 
+// Workgroups of a vertex' stage reduction on a lattice of ns sites: one site
+// per thread until they fill the chip (nblk), so a short line takes a few
+// workgroups and leaves as few partials to add.
+constexpr int RED_THREADS = 256;
+__host__ __device__ inline int bw_blocks(long long ns, int nblk) {
+    const long long b = (ns + RED_THREADS - 1) / RED_THREADS;
+    return b < nblk ? (int)b : nblk;
+}
+
 struct BwArgs {
     const SolveDev* solves;
     const VertexDev* verts;
@@ -75,6 +84,7 @@ struct BwArgs {
     int nst;             // stages per step (4 RK4, 6 Dormand-Prince)
     double wst[6];       // the stages' quadrature weights (sum 1)
     int nvert;
+    int nblk;            // blocks a vertex and stage have room for in `part`
     double2* part;       // [vertex][stage][block][3]
     double2* M;          // [vertex][3] accumulated integrals (device, double)
     // partial-integration route
@@ -132,7 +142,7 @@ hipError_t launch_pair_gemm(int fp64, const PairArgs& a, hipStream_t st);
 // a.groups: ngroups consecutive groups, all of nu U and nv V solves (1 or 2 each)
 hipError_t launch_bw_stage(int fp64, const BwArgs& a, int blocks, int nu, int nv, int ngroups, hipStream_t st);
 hipError_t launch_bw_packet_stage(int fp64, const BwArgs& a, int blocks, int npackets, hipStream_t st);
-hipError_t launch_bw_accum(const BwArgs& a, int nblk, hipStream_t st);
+hipError_t launch_bw_accum(const BwArgs& a, hipStream_t st);
 hipError_t launch_bw2_src(int fp64, const BwArgs& a, int blocks, hipStream_t st);
 hipError_t launch_bw2_kss(int fp64, const BwArgs& a, int blocks, hipStream_t st);
 hipError_t launch_bw2_accum(const BwArgs& a, int nblk, hipStream_t st);
