@@ -165,13 +165,15 @@ struct Group {
     int grid;
     std::vector<int> solves;
     const swf::SizeKernels* k[3] = {nullptr, nullptr, nullptr};
-    // offsets (int2) into the item array and counts: the stepping passes per
-    // tile variant, then the whole-state row and column kernels
-    size_t it_row[swf::NVAR] = {}, it_coly[swf::NVAR] = {}, it_colz[swf::NVAR] = {};
-    int n_row[swf::NVAR] = {}, n_coly[swf::NVAR] = {}, n_colz[swf::NVAR] = {};
+    // offsets (int2) into the item array and counts: the stepping passes (the
+    // column ones per tile variant), then the whole-state row and column kernels
+    size_t it_row = 0, it_coly[swf::NVAR] = {}, it_colz[swf::NVAR] = {};
+    int n_row = 0, n_coly[swf::NVAR] = {}, n_colz[swf::NVAR] = {};
+    size_t it_line = 0;   // one item per solve (1D whole-loop kernel)
+    int n_line = 0;
     size_t it_orow = 0, it_ocy = 0, it_ocz = 0;
     int n_orow = 0, n_ocy = 0, n_ocz = 0;
-    int vr = 0, vy = 0, vz = 0;   // tile variants of the stepping passes in use
+    int vy = 0, vz = 0;   // tile variants of the stepping column passes in use
 };
 
 struct Plan {
@@ -209,7 +211,7 @@ struct Plan {
     // arena layout (byte offsets)
     size_t off_state = 0, off_solves = 0, off_terms = 0, off_verts = 0, off_vgroups = 0, off_modes = 0, off_packets = 0,
            off_rtab = 0, off_ctab = 0,
-           off_items = 0, off_step = 0, off_M = 0, off_part = 0, off_red = 0, off_M2 = 0, off_part2 = 0, total = 0;
+           off_items = 0, off_consts = 0, off_step = 0, off_M = 0, off_part = 0, off_red = 0, off_M2 = 0, off_part2 = 0, total = 0;
     std::vector<size_t> solve_off;      // state offset of each solve (bytes from off_state)
     bool bw2 = false;                   // partial-integration BW route on
     std::vector<int> bw2_solves;        // solves of its vertices (they get the A0, A1 buffers)
@@ -266,8 +268,9 @@ static void add_items(Plan& P, Group& g, int fp64) {
     g.k[0] = swf::size_kernels(fp64, G.n[0]);
     if (G.dim >= 2) g.k[1] = swf::size_kernels(fp64, G.n[1]);
     if (G.dim >= 3) g.k[2] = swf::size_kernels(fp64, G.n[2]);
+    g.it_row = row_items(P, g, g.k[0]->row.rows, g.n_row);
+    if (G.dim == 1) g.it_line = row_items(P, g, 1, g.n_line);
     for (int v = 0; v < swf::NVAR; ++v) {
-        g.it_row[v] = row_items(P, g, g.k[0]->row[v].rows, g.n_row[v]);
         if (G.dim >= 2) g.it_coly[v] = col_items(P, g, 1, g.k[1]->cd[v].w, g.n_coly[v]);
         if (G.dim >= 3) g.it_colz[v] = col_items(P, g, 2, g.k[2]->cd[v].w, g.n_colz[v]);
     }
@@ -435,6 +438,15 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         twoff.push_back({n, o});
         return o;
     };
+    // derivative factors k / n of an axis, transform order (the Nyquist mode negative)
+    std::map<std::pair<int, double>, size_t> ktoff;
+    auto kt_for = [&](int n, double dk) -> size_t {
+        auto it = ktoff.find({n, dk});
+        if (it != ktoff.end()) return it->second;
+        std::vector<double> k(n);
+        for (int m = 0; m < n; ++m) k[m] = dk / (double)n * (2 * m < n ? m : m - n);
+        return ktoff[{n, dk}] = add_r(k);
+    };
     // field tables per (grid, field)
     std::vector<std::pair<std::pair<int, int>, int>> combos;   // (grid, field) -> first TermDev
     for (int i = 0; i < n_solves; ++i) {
@@ -486,6 +498,7 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         d.inv_n = 1.0 / (double)d.nsites;
         d.term0 = first;
         d.nterm = (int)P.fields[s.field].size();
+        for (const auto& t : P.fields[s.field]) d.mus |= 1 << t.mu;
         std::vector<cd> ph;
         for (int j = 0; j < 3; ++j)
             for (int k = 0; k < G.n[j]; ++k) ph.push_back(j < G.dim ? std::polar(1.0, sgn * s.p[j] * xcoord(G, j, k)) : cd(1.0));
@@ -507,7 +520,10 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
                 }
             d.mask = (long long)add_r(m);
         }
-        for (int j = 0; j < 3; ++j) d.tw[j] = (long long)tw_for(G.n[j] > 1 ? G.n[j] : G.n[0]);
+        for (int j = 0; j < 3; ++j) {
+            d.tw[j] = (long long)tw_for(G.n[j] > 1 ? G.n[j] : G.n[0]);
+            d.kt[j] = j < G.dim ? (long long)kt_for(G.n[j], d.dk[j]) : 0;
+        }
         P.hs.push_back(d);
     }
     for (int v = 0; v < n_verts; ++v) {
@@ -679,6 +695,8 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
     off += P.csize * std::max<size_t>(1, P.ctab.size());
     P.off_items = off = align256(off);
     off += sizeof(int2) * std::max<size_t>(1, P.items.size());
+    P.off_consts = off = align256(off);
+    off += (P.fp64 ? sizeof(swf::StageConst<double>) : sizeof(swf::StageConst<float>)) * (size_t)P.nst * n_solves;
     P.off_step = off = align256(off);
     off += 256;
     P.off_M = off = align256(off);
@@ -710,6 +728,7 @@ struct swf_ctx {
     char* arena = nullptr;
     bool own_arena = false;
     int step = 0;
+    int step_add = 0;             // steps enqueued since the device step counter was last advanced
     size_t lds_max = 65536;       // dynamic LDS one workgroup may use on this device
     int ncu = 256;                // compute units of this device
     void* pm_buf = nullptr;       // pair-matrix scratch (grown on demand, freed by swf_free)
@@ -739,6 +758,7 @@ struct swf_ctx {
     int* d_packets() { return (int*)(arena + P.off_packets); }
     void* d_rtab() { return arena + P.off_rtab; }
     void* d_ctab() { return arena + P.off_ctab; }
+    void* d_consts() { return arena + P.off_consts; }
     int2* d_items() { return (int2*)(arena + P.off_items); }
     int* d_step() { return (int*)(arena + P.off_step); }
     // first (step, solve) of a non-finite value seen by the in-loop check, as ~key (0: none)
@@ -816,6 +836,9 @@ static swf::PassArgs pass_args(swf_ctx* ctx) {
     a.step = ctx->d_step();
     a.t_out = ctx->P.t0;
     a.dt = ctx->P.sdt;
+    a.step_add = ctx->step_add;
+    a.consts = ctx->d_consts();
+    a.nst = ctx->P.nst;
     return a;
 }
 
@@ -876,8 +899,8 @@ static int row_pass(swf_ctx* ctx, const Group& g, int mode, int stage, int src, 
     }
     const double bytes = trav * 4.0 * ctx->P.csize * group_sites(ctx, g);
     if (mode == swf::ROW_STAGE) {
-        const auto& v = k->row[g.vr];
-        return launch(ctx, ctx->P.dp5 ? v.dp5[stage] : v.stage[stage], g.n_row[g.vr], g.it_row[g.vr], v.threads,
+        const auto& v = k->row;
+        return launch(ctx, ctx->P.dp5 ? v.dp5[stage] : v.stage[stage], g.n_row, g.it_row, v.threads,
                       v.lds, a, kind, bytes);
     }
     return launch(ctx, k->row_other[mode], g.n_orow, g.it_orow, k->row0_threads, k->row0_lds, a, kind, bytes);
@@ -950,6 +973,7 @@ static int bw_stage(swf_ctx* ctx, int stage) {
     b.verts = ctx->d_verts();
     b.ctab = ctx->d_ctab();
     b.step = ctx->d_step();
+    b.step_add = ctx->step_add;
     b.t_out = ctx->P.win.t_out;
     b.dt = ctx->P.win.dt;
     b.stage = stage;
@@ -1034,6 +1058,7 @@ static int bw2_stage(swf_ctx* ctx, int stage) {
     b.solves = ctx->d_solves();
     b.verts = ctx->d_verts();
     b.step = ctx->d_step();
+    b.step_add = ctx->step_add;
     b.t_out = P.win.t_out;
     b.dt = P.win.dt;
     b.stage = stage;
@@ -1076,6 +1101,7 @@ static int bw2_accum(swf_ctx* ctx) {
     b.solves = ctx->d_solves();
     b.verts = ctx->d_verts();
     b.step = ctx->d_step();
+    b.step_add = ctx->step_add;
     b.t_out = ctx->P.win.t_out;
     b.dt = ctx->P.win.dt;
     b.nvert = (int)ctx->P.hv.size();
@@ -1175,13 +1201,34 @@ static int ip_step(swf_ctx* ctx) {
     });
     if (!r) r = bw_accum(ctx);
     if (r) return r;
-    HIPCHK(swf::launch_tick(ctx->d_step(), ctx->st));
+    ++ctx->step_add;
+    return SWF_OK;
+}
+
+static int stage_consts(swf_ctx* ctx) {
+    swf::StageNodes n;
+    for (int st = 0; st < 6; ++st) n.c[st] = ctx->P.cst[st];
+    HIPCHK(swf::launch_stage_consts(ctx->P.fp64, pass_args(ctx), n, (int)ctx->P.solves.size(), ctx->st));
+    return SWF_OK;
+}
+
+// Bring the device step counter up to the steps enqueued.  It is moved once per
+// swf_step call (or per captured graph), not per step: the launches in between
+// carry their distance from it.
+static int advance(swf_ctx* ctx) {
+    const int n = ctx->step_add;
+    ctx->step_add = 0;
+    if (n > 0) HIPCHK(swf::launch_advance(ctx->d_step(), n, ctx->st));
     return SWF_OK;
 }
 
 // Enqueue one full RK4 step of every solve.
 static int enqueue_step(swf_ctx* ctx) {
     if (ctx->P.ip) return ip_step(ctx);
+    {
+        int r = stage_consts(ctx);
+        if (r) return r;
+    }
     if (ctx->opt.batched && ctx->opt.chunk > 0 && ctx->P.hv.empty()) {
         // chunk-major: all stages of one chunk before the next chunk
         for (const auto& g : groups(ctx))
@@ -1189,7 +1236,7 @@ static int enqueue_step(swf_ctx* ctx) {
                 int r = stage_passes(ctx, g, s);
                 if (r) return r;
             }
-        HIPCHK(swf::launch_tick(ctx->d_step(), ctx->st));
+        ++ctx->step_add;
         return SWF_OK;
     }
     for (int s = 0; s < ctx->P.nst; ++s) {
@@ -1204,7 +1251,7 @@ static int enqueue_step(swf_ctx* ctx) {
     int r = bw_accum(ctx);
     if (!r && ctx->P.bw2) r = bw2_accum(ctx);
     if (r) return r;
-    HIPCHK(swf::launch_tick(ctx->d_step(), ctx->st));
+    ++ctx->step_add;
     return SWF_OK;
 }
 
@@ -1251,7 +1298,7 @@ static int line_steps(swf_ctx* ctx, int n) {
             a.nsteps = c;
             const double bytes = 2.0 * 4.0 * ctx->P.csize * group_sites(ctx, g);
             const int w = line_build(ctx, g);
-            int r = launch(ctx, g.k[0]->line[w], g.n_row[0], g.it_row[0], g.k[0]->line_threads,
+            int r = launch(ctx, g.k[0]->line[w], g.n_line, g.it_line, g.k[0]->line_threads,
                            line_lds(ctx, g, max_terms(ctx, g), w), a, 5, bytes);
             if (r) return r;
         }
@@ -1267,6 +1314,8 @@ static int capture_steps(swf_ctx* ctx, int steps, hipGraph_t* graph, hipGraphExe
     HIPCHK(hipStreamBeginCapture(ctx->st, hipStreamCaptureModeThreadLocal));
     int r = SWF_OK;
     for (int i = 0; i < steps && !r; ++i) r = enqueue_step(ctx);
+    if (!r) r = advance(ctx);
+    ctx->step_add = 0;
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(ctx->st, &g);
     if (r) {
@@ -1292,13 +1341,13 @@ static int build_graph(swf_ctx* ctx) {
 }
 
 // ------------------------------------------------------------ autotuner
-// Times every tile variant of the three stepping passes of each group on the
+// Times every tile variant of the stepping column passes of each group on the
 // problem itself (zero state, stage 1), keeps the fastest, and caches the
 // choice by (precision, grid, batch size) in a text file.
 static std::string tune_key(swf_ctx* ctx, const Group& g) {
     const swf_grid& G = ctx->P.grids[g.grid];
     char b[160];
-    snprintf(b, sizeof(b), "deriv%s %s d%d n%dx%dx%d b%zu", ctx->P.dp5 ? "-dp5" : "", ctx->P.fp64 ? "f64" : "f32", G.dim,
+    snprintf(b, sizeof(b), "deriv2%s %s d%d n%dx%dx%d b%zu", ctx->P.dp5 ? "-dp5" : "", ctx->P.fp64 ? "f64" : "f32", G.dim,
              G.n[0], G.n[1], G.n[2], g.solves.size());
     return b;
 }
@@ -1339,33 +1388,30 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
     const int prof = ctx->opt.profile;
     ctx->opt.profile = 0;
     std::ostringstream rep;
+    int rc = stage_consts(ctx);
+    if (rc) return rc;
     for (auto& g : gl) {
         const std::string key = tune_key(ctx, g);
         auto it = cache.find(key);
         const int dim = ctx->P.grids[g.grid].dim;
         if (it != cache.end()) {
-            g.vr = std::min(it->second[0], g.k[0]->nvar - 1);
             g.vy = dim >= 2 ? std::min(it->second[1], g.k[1]->nvar - 1) : 0;
             g.vz = dim >= 3 ? std::min(it->second[2], g.k[2]->nvar - 1) : 0;
-            rep << key << ": cached " << g.vr << " " << g.vy << " " << g.vz << "\n";
+            rep << key << ": cached 0 " << g.vy << " " << g.vz << "\n";
             continue;
         }
         const int reps = 4;
-        float best = 1e30f;
-        int bv = 0;
-        for (int v = 0; v < g.k[0]->nvar; ++v) {
-            g.vr = v;
+        {
+            // the row pass has one variant: its time is reported only
             float ms = 0;
             const int st = ctx->P.dp5 ? 3 : 1;   // a middle stage of the stepper
-            int r = time_it(ctx, [&] { return row_pass(ctx, g, swf::ROW_STAGE, st, 0, 0, 0, 0, 4); }, reps, &ms);
+            int r = time_it(ctx, [&] { return row_pass(ctx, g, swf::ROW_STAGE, st, 0, 0, 0, 0, 4); }, 1, &ms);
             if (r) { ctx->opt.profile = prof; return r; }
-            rep << key << ": row v" << v << " " << ms << " ms\n";
-            if (ms < best) { best = ms; bv = v; }
+            rep << key << ": row v0 " << ms << " ms\n";
         }
-        g.vr = bv;
         for (int axis = 1; axis < dim; ++axis) {
-            best = 1e30f;
-            bv = 0;
+            float best = 1e30f;
+            int bv = 0;
             for (int v = 0; v < g.k[axis]->nvar; ++v) {
                 (axis == 1 ? g.vy : g.vz) = v;
                 float ms = 0;
@@ -1376,10 +1422,10 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
             }
             (axis == 1 ? g.vy : g.vz) = bv;
         }
-        cache[key] = {g.vr, g.vy, g.vz};
+        cache[key] = {0, g.vy, g.vz};
         if (!ctx->tune_path.empty()) {
             std::ofstream out(ctx->tune_path, std::ios::app);
-            out << key << "|" << g.vr << " " << g.vy << " " << g.vz << "\n";
+            out << key << "|0 " << g.vy << " " << g.vz << "\n";
         }
     }
     ctx->opt.profile = prof;
@@ -1891,11 +1937,11 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
                         INITCHK(hipFuncSetAttribute(k->line[w], hipFuncAttributeMaxDynamicSharedMemorySize,
                                                     (int)std::min(ctx->lds_max - LINE_STATIC_LDS,
                                                                   line_lds(ctx, g, swf::MAX_TERMS, w))));
+                for (int st = 0; st < 4; ++st)
+                    INITCHK(hipFuncSetAttribute(k->row.stage[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row.lds));
+                for (int st = 0; st < 6; ++st)
+                    INITCHK(hipFuncSetAttribute(k->row.dp5[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row.lds));
                 for (int v = 0; v < swf::NVAR; ++v) {
-                    for (int st = 0; st < 4; ++st)
-                        INITCHK(hipFuncSetAttribute(k->row[v].stage[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row[v].lds));
-                    for (int st = 0; st < 6; ++st)
-                        INITCHK(hipFuncSetAttribute(k->row[v].dp5[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row[v].lds));
                     for (int a = 0; a < 2; ++a)
                         for (int m = 0; m < 2; ++m)
                             INITCHK(hipFuncSetAttribute(k->cd[v].fn[a][m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->cd[v].lds));
@@ -1908,7 +1954,6 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
         const int v = opt->force_variant - 1;
         for (auto* gl : {&P.batched, &P.single})
             for (auto& g : *gl) {
-                g.vr = std::min(v, g.k[0]->nvar - 1);
                 g.vy = g.k[1] ? std::min(v, g.k[1]->nvar - 1) : 0;
                 g.vz = g.k[2] ? std::min(v, g.k[2]->nvar - 1) : 0;
             }
@@ -1967,11 +2012,16 @@ swf_status swf_step(swf_ctx* ctx, int n_steps, int* steps_left) {
                 HIPCHK(hipGraphLaunch(ctx->gexec, ctx->st));
             } else {
                 r = enqueue_step(ctx);
-                if (r) return (swf_status)r;
+                if (r) {
+                    ctx->step_add = 0;
+                    return (swf_status)r;
+                }
             }
             if (K > 0 && (ctx->step + i) % K == 0 && (r = check(ctx->step + i))) return (swf_status)r;
         }
     }
+    r = advance(ctx);
+    if (r) return (swf_status)r;
     if (n_steps > 0) {
         ctx->step += n_steps;
         std::fill(ctx->kvalid.begin(), ctx->kvalid.end(), 0);

@@ -65,9 +65,19 @@ struct SolveDev {
     double dV;
     double inv_n;         // 1 / nsites (normalisation of the inverse transform)
     int term0, nterm;     // field terms
+    int mus;              // bit mu set: a term of the field has that component
     long long ph;         // offset (complex) of the background phase tables exp(i K_j x_j): n0 + n1 + n2 entries
     long long mask;       // offset (reals) of absorber mask tables, -1 if off
     long long tw[3];      // offset (complex) of the twiddle table of each axis' length
+    long long kt[3];      // offset (reals) of k_j / n_j in transform order (n_j entries): the derivatives' factors
+};
+
+// Per solve and stage, formed once per step in double and rounded once (R: the
+// state's precision): the background spinor w e^{-i E t}, (re, im) x 4, and
+// amp * ft(t) of every field term.
+template <class R> struct StageConst {
+    R w[8];
+    R coef[MAX_TERMS];
 };
 
 enum { BUF_Y = 0, BUF_ACC = 1, BUF_YS = 2, BUF_T = 3, BUF_A0 = 4, BUF_A1 = 5, BUF_K3 = 6, BUF_K4 = 7 };
@@ -330,6 +340,14 @@ __device__ __forceinline__ void fft_step(C (&v)[NC][N / T], int t, const C* __re
     }
 }
 
+// Orders a wave's LDS accesses before and after it: the LDS serves one wave's
+// instructions in order, so only the compiler has to be held back.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Exchange the outputs of step J-1 into the inputs of step J through LDS,
 // CG components at a time.  Lay::addr(q, line, idx) is the LDS slot of point
 // idx of component q (within the group) of this thread's line.
@@ -384,6 +402,79 @@ struct FftRun {
 template <class C, int N, int T, int DIR, int NC, int CG, class Lay, class P = FftPlan<N>>
 __device__ __forceinline__ void fft_line(C (&v)[NC][N / T], C* lds, int t, int line, const C* tw) {
     FftRun<C, N, T, 0, DIR, NC, CG, Lay, P>::run(v, lds, t, line, tw);
+}
+
+// The same transform of one line held by T lanes of one wave (T divides 64):
+// its exchanges need no barrier.  Output k of butterfly b of a step (radix Rp,
+// stride NSp) is kept in LDS at k (N/Rp + PAD) + b, so a thread writes one row
+// per output, lanes side by side, and what the next step's butterfly takes,
+//   point i = b + k N/R:  row (i / NSp) mod Rp, entry (i / NS) NSp + i mod NSp,
+// lies at constant distances for its inputs k: one address per butterfly
+// instead of one per point (a third of the transform's integer work), and
+// fewer bank conflicts (counted over all exchanges of a line, 320 points of 8
+// bytes: 608 cycles a wave instead of 912).  SPLIT: the real and the imaginary
+// parts one after the other through a buffer of half the size.
+// PAD and the extra distance between a wave's lines are those with the fewest
+// bank conflicts, counted for every length and element size (4, 8 or 16 bytes).
+constexpr int xch_pad(int n, int bytes) {
+    return n % 5 == 0 ? (n == 320 ? (bytes <= 8 ? 13 : 5) : n == 160 ? 5 : 1)
+         : n % 3 == 0 ? (bytes <= 8 && n >= 192 ? 11 : 3)
+         : n < 128 || bytes == 16 ? 1 : bytes == 8 || n == 128 ? 2 : 4;
+}
+constexpr int xch_skew(int n, int bytes) {
+    return n == 16 ? 2 : n == 32 ? 4 : n == 40 ? 1 : n == 80 ? 7 : bytes == 16 ? 0 : n == 96 ? 12 : n == 160 ? 15
+         : bytes == 4 && n == 320 ? 15 : bytes == 4 && n == 192 ? 4 : 0;
+}
+// elements of one line's exchange buffer
+template <int N, class P, int BYTES> constexpr int xch_stride() {
+    int r = 0;
+    for (int j = 0; j + 1 < P::NR; ++j) r = P::R[j] > r ? P::R[j] : r;
+    return N + r * xch_pad(N, BYTES) + xch_skew(N, BYTES);
+}
+template <class C, int N, int T, int J, bool SPLIT, class P>
+__device__ __forceinline__ void fft_exchange_wave(C (&v)[N / T], void* line, int t) {
+    using R_ = decltype(C::x);
+    constexpr int Rp = P::R[J - 1];
+    constexpr int NSp = plan_stride<P>(J - 1);
+    constexpr int NS = NSp * Rp;
+    constexpr int R = P::R[J];
+    constexpr int E = N / T;
+    constexpr int Bp = E / Rp;
+    constexpr int B = E / R;
+    constexpr int ROW = N / Rp + xch_pad(N, SPLIT ? sizeof(R_) : sizeof(C));
+#pragma unroll
+    for (int h = 0; h < (SPLIT ? 2 : 1); ++h) {
+        wave_lds_order();
+#pragma unroll
+        for (int c = 0; c < Bp; ++c)
+#pragma unroll
+            for (int k = 0; k < Rp; ++k) {
+                const C x = v[c + Bp * k];
+                if constexpr (SPLIT) ((R_*)line)[k * ROW + T * c + t] = h ? x.y : x.x;
+                else ((C*)line)[k * ROW + T * c + t] = x;
+            }
+        wave_lds_order();
+#pragma unroll
+        for (int c = 0; c < B; ++c) {
+            const int b = t + T * c;
+            const int at = (b / NSp) % Rp * ROW + b / NS * NSp + b % NSp;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                C& x = v[c + B * k];
+                if constexpr (SPLIT) (h ? x.y : x.x) = ((const R_*)line)[at + k * (N / (R * Rp))];
+                else x = ((const C*)line)[at + k * (N / (R * Rp))];
+            }
+        }
+    }
+}
+template <class C, int N, int T, int J, int DIR, bool SPLIT, class P>
+__device__ __forceinline__ void fft_line_wave(C (&v)[N / T], void* line, int t, const C* tw) {
+    static_assert(64 % T == 0, "a line within one wave");
+    if constexpr (J < P::NR) {
+        if constexpr (J > 0) fft_exchange_wave<C, N, T, J, SPLIT, P>(v, line, t);
+        fft_step<C, N, T, J, DIR, 1, P>(reinterpret_cast<C(&)[1][N / T]>(v), t, tw);
+        fft_line_wave<C, N, T, J + 1, DIR, SPLIT, P>(v, line, t, tw);
+    }
 }
 
 // LDS layouts.  Row passes: lanes run along the line (t fastest), one padded

@@ -51,15 +51,16 @@ struct PassArgs {
     double t_explicit;     // time of ROW_RHS
     long long ph2;         // ROW_FWDPH: complex offset of exp(i k_j x_j) tables
     int nitems;            // work items of this launch
+    int step_add;          // steps enqueued since the device counter was last advanced
+    const void* consts;    // StageConst per solve and stage of the current step (nst each)
+    int nst;               // stages of the stepper
     int nsteps;            // line_kernel: RK4 steps per launch
 };
 
 // ------------------------------------------------------------------ tile variants
-// A pass kernel is instantiated for several tile shapes; the host times them on
-// the actual problem (autotuner) and keeps the fastest.
-//   row pass: T threads per x-line, ROWS lines per block, CG components per
-//             LDS exchange round;
-//   column pass: T threads per line, W adjacent x-columns per block, CG.
+// A column pass kernel is instantiated for several tile shapes; the host times
+// them on the actual problem (autotuner) and keeps the fastest: T threads per
+// line, W adjacent x-columns per block.
 template <int N, int T, class P = FftPlan<N>> constexpr bool plan_ok() {
     if (T < 1 || N % T) return false;
     for (int j = 0; j < P::NR; ++j)
@@ -73,7 +74,7 @@ template <int N> constexpr int half_t() {
     constexpr int T = FftPlan<N>::T;
     return (T % 2 == 0 && 2 * N / T <= 16 && plan_ok<N, T / 2>()) ? T / 2 : T;
 }
-constexpr int NVAR = 4;       // tile variants of the stepping passes (row and column)
+constexpr int NVAR = 4;       // tile variants of the stepping column passes
 template <int N> constexpr int nvar() { return N >= 256 ? NVAR : 1; }
 constexpr size_t LDS_CAP = 72 * 1024;
 constexpr int imax(int a, int b) { return a > b ? a : b; }
@@ -278,7 +279,7 @@ __global__ void __launch_bounds__((RowVar<R, N, V>::THREADS)) row_kernel(PassArg
                 ts = a.t_explicit;
             } else {
                 const double cst = a.stage == 0 ? 0.0 : (a.stage == 3 ? 1.0 : 0.5);
-                ts = a.t_out - (double)(*a.step) * a.dt - cst * a.dt;
+                ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - cst * a.dt;
             }
             const int nterm = S->nterm;
             for (int j = t; j < nterm; j += T) {
@@ -612,301 +613,278 @@ __global__ void __launch_bounds__((CdVar<R, N, V>::THREADS)) col_d_kernel(PassAr
     }
 }
 
-// Row (x) stage pass: the RK4 stage STAGE for one spinor component per
-// thread.  T threads share a component line (E = N/T points each), 4T a
-// grid line.  A thread reads its own component of the stage input y_i and
-// exchanges it through LDS for the two it also needs (3 - q and q ^ 2, the
-// partners alpha^j couples q to), transforms component 3 - q along x,
-// multiplies by k_x / n_0 and transforms back, which gives (alpha^1 D_x y)_q,
-// and then finishes its own component at its points:
+// Row (x) stage pass: the RK4 stage STAGE.  T threads hold one spinor component
+// of a grid line (E = N/T points each), 4T a line.  A thread transforms
+// component 3 - q along x, multiplies by k_x / n_0 and transforms back, which
+// gives (alpha^1 D_x y)_q, leaves it in LDS, and finishes whole sites (all
+// four components of the sites t + T m, m = q, q + 4, ...), reading the stage
+// input there again from the cache, so that the field and phase work is done
+// once per site:
 //     k_q = -i [alpha^1 D_x y + G + (beta y) + sum over trivial axes kappa_j (alpha^j y)
 //               + (A_0 + alpha^j A_j)(y + psi_b)]_q,
-// the RK4 update of component q with the accumulator written once, and the
-// absorber at the last stage.  STAGE 4..9 are the six stages of the
-// fixed-step Dormand-Prince 5(4) stepper instead: the stage writes its slope
-// k_s and the next stage input y + h sum_{j<=s} a_{s+1,j} k_j (reading the
-// earlier slopes), the last one the step y + h sum_j b_j k_j.
-//   v0 / v1: few-points plan, 256 / 128 threads per block;
-//   v2 / v3 (SITE): few-points / default plan, 256 / 128 threads: the thread
-//   reads component 3 - q of the stage input for the transform straight from
-//   memory, leaves (alpha^1 D_x y)_q in LDS, and finishes whole sites (all
-//   four components of the sites t + T m, m = q, q+4, ...), reading the
-//   stage input there again, so the field and phase work is done once per site.
-template <class R, int N, int V> struct RdVar {
-    static constexpr bool SITE = V >= 2;
-    static constexpr bool SMALL = (V <= 2) && has_small_plan<N>();
-    using PL = typename PlanSel<N, SMALL>::type;
+// the RK4 update with the accumulator written once, and the absorber at the
+// last stage.  STAGE 4..9 are the six stages of the fixed-step Dormand-Prince
+// 5(4) stepper instead: the stage writes its slope k_s and the next stage input
+// y + h sum_{j<=s} a_{s+1,j} k_j (reading the earlier slopes), the last one the
+// step y + h sum_j b_j k_j.
+//
+// Every component line lies within one wave (T divides 64 in the default
+// plans), so the transforms run without a barrier: the waves of a compute unit
+// drift apart and one's loads cover another's arithmetic.
+// The exchanges move real and imaginary parts one after the other (SPLIT): half
+// the LDS, so that three or four waves per SIMD fit for every length (1024
+// points in double: 0.59 ms against 0.63 ms unsplit, 9 x 1024^2, stage 1; the
+// shorter lengths differ by 2% at most either way).  Blocks of 256 threads: 128
+// were up to 9% slower (256 points in single precision) and at most 2% faster.
+//
+// What bounds it: HBM.  A kernel that only reads and writes the same lines of
+// the same arrays takes 1.04 / 0.59 ms for stages 1 / 0 on 64 x 512^2 in double
+// (5.2 / 5.5 TB/s), this pass 1.00 / 0.56 ms; 8 x 320^3 in single precision 7.7
+// against 8.0 ms.  With barriers between the exchanges, the field selected by
+// component per term and site, and the time factors formed per workgroup, the
+// same stages took 0.99 / 0.67 ms and 9.1 ms, 9 x 1024^2 in double 0.82 ms
+// (now 0.59) and 192 x 192 x 256 x 4 in double 3.7 ms (now 2.2).
+template <class R, int N> struct RdVar {
+    using PL = FftPlan<N>;
     static constexpr int T = PL::T;
     static constexpr int E = N / T;
-    static constexpr int ROWS = imax(1, ((V % 2) == 0 ? 256 : 128) / (4 * T));
-    static constexpr int THREADS = 4 * T * ROWS;
-    using Lay = RowLay<N, 4 * ROWS>;
-    static constexpr size_t BYTES = (size_t)4 * ROWS * Lay::STRIDE * sizeof(cpx<R>);
+    static constexpr int LT = 4 * T;          // threads of a grid line
+    static constexpr bool WLINE = LT <= 64;   // a line within one wave
+    static constexpr int ROWS = imax(1, 256 / LT);
+    static constexpr int THREADS = LT * ROWS;
+    static constexpr int SITES = E / 4;       // sites a thread finishes
+    static constexpr int STRIDE = xch_stride<N, PL, sizeof(R)>();   // reals of a component line
+    static constexpr size_t XCH = ((size_t)4 * ROWS * STRIDE * sizeof(R) + 15) / 16 * 16;
+    // exchange buffer, twiddles and (single precision) the derivative's factors
+    static constexpr size_t BYTES = XCH + N * sizeof(cpx<R>) + (sizeof(R) == 4 ? N * sizeof(R) : 0);
     // waves per SIMD the compiler is asked to fit: what the LDS of a compute
-    // unit (160 KiB) allows, at most 2 in double (four components' worth of
-    // points stay live) and 4 in single precision
-    static constexpr int BLOCKS_PER_CU = (int)(163840 / (BYTES + N * sizeof(cpx<R>) + 512));
-    static constexpr int WAVES = imax(1, imin(SITE ? 4 : (sizeof(R) == 8 ? 2 : 4), BLOCKS_PER_CU * (THREADS / 64) / 4));
-    static_assert(plan_ok<N, T, PL>(), "row derivative variant violates the FFT plan constraints");
-    static_assert(THREADS <= 1024, "row derivative block too large");
+    // unit allows, and what the points and a prefetched site leave registers for
+    static constexpr int BLOCKS_PER_CU = (int)(163840 / BYTES);
+    static constexpr int WAVES = imax(1, imin(sizeof(R) == 4 ? (E >= 20 ? 3 : 4) : (E >= 20 ? 2 : 3), BLOCKS_PER_CU * imax(1, THREADS / 64) / 4));
+    static_assert(plan_ok<N, T, PL>(), "row derivative pass violates the FFT plan constraints");
+    static_assert(64 % T == 0 && E % 4 == 0, "a component line within one wave, whole sites per thread");
 };
 
+// Values that are the same for a whole workgroup are read through the constant
+// address space, as scalar loads.
+template <class T> using sptr = const T __attribute__((address_space(4)))*;
+template <class T> __device__ __forceinline__ sptr<T> uni(const T* p) { return (sptr<T>)p; }
+
+// A complex number at a uniform base plus a byte offset of 32 bits.
+template <class C> __device__ __forceinline__ C gload_at(gptr<const char> base, unsigned off) {
+    using V2 = nv2<decltype(C::x)>;
+    const V2 v = __builtin_nontemporal_load((gptr<const V2>)(base + off));
+    return cmake<C>(v.x, v.y);
+}
+template <class C> __device__ __forceinline__ void gstore_at(gptr<char> base, unsigned off, C c) {
+    using V2 = nv2<decltype(C::x)>;
+    V2 v;
+    v.x = c.x;
+    v.y = c.y;
+    __builtin_nontemporal_store(v, (gptr<V2>)(base + off));
+}
+
+// (V: the tile variant, of which this pass has one; profiles name the kernel by it)
 template <class R, int N, int V, int STAGE>
-__global__ void __launch_bounds__((RdVar<R, N, V>::THREADS))
-__attribute__((amdgpu_waves_per_eu(RdVar<R, N, V>::WAVES, 8))) row_d_kernel(PassArgs a) {
+__global__ void __launch_bounds__((RdVar<R, N>::THREADS))
+__attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArgs a) {
     using C = cpx<R>;
-    using VC = RdVar<R, N, V>;
+    using VC = RdVar<R, N>;
     constexpr int T = VC::T;
     constexpr int E = VC::E;
     constexpr int ROWS = VC::ROWS;
-    using Lay = typename VC::Lay;
+    constexpr int LT = VC::LT;
+    constexpr int SITES = VC::SITES;
     using PL = typename VC::PL;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    C* lds = reinterpret_cast<C*>(smem_raw);
-    __shared__ R sh_fyz[ROWS][MAX_TERMS];
-    __shared__ int sh_mu[MAX_TERMS];
-    __shared__ long long sh_tab[MAX_TERMS];
-    __shared__ C sh_wc[4];
-    __shared__ C sh_phyz[ROWS];
-    __shared__ C tw[N];
+    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH);
+    R* kt = reinterpret_cast<R*>(tw + N);
 
     const int tid = threadIdx.x;
     const int t = tid % T;
-    const int q = (tid / T) % 4;
-    const int line = tid / (4 * T);
-    const int qx = 3 - q, qz = q ^ 2;
-    const int2 it = a.items[blockIdx.x];
-    const SolveDev* __restrict__ S = a.solves + it.x;
-    const int row = it.y * ROWS + line;
-    const bool act = row < S->nrows;
-    const int rowc = act ? row : 0;
-    const long long base = (long long)rowc * N;
+    // (uniform over the wave where a line, or a component line, takes whole waves)
+    const int q = T == 64 ? __builtin_amdgcn_readfirstlane(tid / T % 4) : tid / T % 4;
+    const int line = LT >= 64 ? __builtin_amdgcn_readfirstlane(tid / LT) : tid / LT;
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const int solve = (int)(unsigned)item, ty = (int)(item >> 32);
+    const sptr<SolveDev> S = uni(a.solves + solve);
+    const int row0 = ty * ROWS;
+    const bool act = row0 + line < S->nrows;
+    const int linec = act ? line : 0;       // a line beyond the last one repeats the tile's first
     const long long ns = S->nsites;
+    const long long tile0 = (long long)row0 * N;
     gptr<const nv2<R>> ctab = cview<R>(a.ctab);
     gptr<const R> rtab = glob(reinterpret_cast<const R*>(a.rtab));
-    for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S->tw[0] + i);
-    const int n0 = S->n[0], n1 = S->n[1];
-    const int yy = rowc % n1, zz = rowc / n1;
 
     // STAGE 0..3: classical RK4 stages; 4..9: Dormand-Prince stages 0..5
     constexpr bool DP = STAGE >= 4;
     constexpr int DS = DP ? STAGE - 4 : 0;
     constexpr bool FIRST = STAGE == 0 || STAGE == 4, LAST = STAGE == 3 || STAGE == 9;
-    gptr<const nv2<R>> pin = cview<R>(S->buf[FIRST ? BUF_Y : BUF_YS]) + base;
-    C v[1][E];
-    C yq[E], yx[E], yz[E];
-    if constexpr (VC::SITE) {
-        // the component alpha^1 takes, straight from memory (read again by the epilogue)
+    gptr<const nv2<R>> pin = cview<R>(S->buf[FIRST ? BUF_Y : BUF_YS]) + tile0;
+    for (int i = tid; i < N; i += VC::THREADS) {
+        tw[i] = gload<C>(ctab, S->tw[0] + i);
+        if constexpr (sizeof(R) == 4) kt[i] = rtab[S->kt[0] + i];
+    }
+    // the component alpha^1 takes (read again, as whole sites, by the epilogue)
+    C v[E];
+    {
+        gptr<const nv2<R>> p = pin + (3 - q) * ns + (linec * N + t);
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[0][m] = gload<C>(pin, qx * ns + t + T * m);
+        for (int m = 0; m < E; ++m) v[m] = gload<C>(p, T * m);
+    }
+    __syncthreads();
+    R* xl = reinterpret_cast<R*>(smem_raw) + 4 * line * VC::STRIDE;   // this line's exchange buffer
+    R* xch = xl + q * VC::STRIDE;                                     // this component's part of it
+    fft_line_wave<C, N, T, 0, -1, true, PL>(v, xch, t, tw);
+    // k_x / n_0 (numpy order; E is even, so the sign of k follows from m)
+    if constexpr (sizeof(R) == 4) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = cscale(v[m], kt[t + T * m]);
     } else {
-        // own component of the stage input
+        const double kscale = S->dk[0] / (double)N, td = (double)t;
 #pragma unroll
-        for (int m = 0; m < E; ++m) yq[m] = gload_nt<C>(pin, q * ns + t + T * m);
+        for (int m = 0; m < E; ++m) v[m] = cscale(v[m], (R)(kscale * (td + (double)(T * m - (m < E / 2 ? 0 : N)))));
     }
-    // per-line constants of the stage time (read after the barriers below)
-    constexpr double cst = DP ? dp5_c(DS) : (STAGE == 0 ? 0.0 : (STAGE == 3 ? 1.0 : 0.5));
-    const double ts = a.t_out - (double)(*a.step) * a.dt - cst * a.dt;
-    const int nterm = S->nterm;
-    if (q == 0) {
-        for (int j = t; j < nterm; j += T) {
-            const TermDev tm = a.terms[S->term0 + j];
-            const double coef = tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts);
-            sh_fyz[line][j] = (R)coef * rtab[tm.tab + n0 + yy] * rtab[tm.tab + n0 + n1 + zz];
-            if (line == 0) {
-                sh_mu[j] = tm.mu;
-                sh_tab[j] = tm.tab;
-            }
-        }
-        if (t == 0) sh_phyz[line] = cmul(gload<C>(ctab, S->ph + n0 + yy), gload<C>(ctab, S->ph + n0 + n1 + zz));
-    }
-    if (tid < 4) {
-        double sn, cs;
-        sincos(-S->E * ts, &sn, &cs);
-        const double wr = S->w[2 * tid], wi = S->w[2 * tid + 1];
-        sh_wc[tid] = cmake<C>((R)(wr * cs - wi * sn), (R)(wr * sn + wi * cs));
-    }
-    if constexpr (!VC::SITE) {
-        // the partner components through LDS
-#pragma unroll
-        for (int m = 0; m < E; ++m) lds[Lay::addr(0, 4 * line + q, t + T * m)] = yq[m];
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            yx[m] = lds[Lay::addr(0, 4 * line + qx, t + T * m)];
-            yz[m] = lds[Lay::addr(0, 4 * line + qz, t + T * m)];
-            v[0][m] = yx[m];
-        }
-    }
-    // (alpha^1 D_x y)_q: the first exchange's barrier orders the reads above
-    // before the transform reuses the LDS
-    fft_line<C, N, T, -1, 1, 1, Lay, PL>(v, lds, t, 4 * line + q, tw);
-    const double kscale = S->dk[0] / (double)N;
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[0][m] = cscale(v[0][m], (R)(kscale * kindex(t + T * m, N)));
-    fft_line<C, N, T, +1, 1, 1, Lay, PL>(v, lds, t, 4 * line + q, tw);
 
-    // ---- stage epilogue
+    // ---- stage epilogue: the thread's sites t + T (q + 4 j), one at a time, the
+    // next one's operands in flight
+    gptr<const char> by[4], bg[4], bo[4];
+    gptr<char> w0[4], w1[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const long long o = c * ns + tile0;
+        by[c] = (gptr<const char>)(pin + c * ns);
+        bg[c] = (gptr<const char>)(cview<R>(S->buf[BUF_T]) + o);
+        bo[c] = (gptr<const char>)(cview<R>(S->buf[STAGE == 3 ? BUF_ACC : BUF_Y]) + o);
+        w0[c] = (gptr<char>)(wview<R>(S->buf[LAST ? BUF_Y : BUF_YS]) + o);
+        w1[c] = (gptr<char>)(wview<R>(S->buf[DP ? dp5_kbuf(DS < 5 ? DS : 0) : BUF_ACC]) + o);
+    }
+    const int dim = S->dim, nterm = S->nterm, mus = S->mus;
+    const int site0 = t + T * q;
+    const unsigned off0 = (unsigned)(linec * N + site0) * (unsigned)sizeof(C);
+    struct Ops { C y[4], g[4], o[4]; };
+    auto load = [&](Ops& p, int j) {
+        const unsigned off = off0 + (unsigned)(4 * T * j * (int)sizeof(C));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p.y[c] = gload_at<C>(by[c], off);
+        if (dim >= 2) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) p.g[c] = gload_at<C>(bg[c], off);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) p.g[c] = cmake<C>((R)0, (R)0);
+        }
+        if constexpr (!FIRST) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) p.o[c] = gload_at<C>(bo[c], off);
+        }
+    };
+
+    fft_line_wave<C, N, T, 0, +1, true, PL>(v, xch, t, tw);
+
+    Ops ops[2];
+    load(ops[0], 0);
+    // ---- from one component per thread to whole sites
+    C d[SITES][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h && !VC::WLINE) __syncthreads();
+        else wave_lds_order();
+#pragma unroll
+        for (int m = 0; m < E; ++m) xch[t + T * m] = h ? v[m].y : v[m].x;
+        if constexpr (VC::WLINE) wave_lds_order();
+        else __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SITES; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) (h ? d[j][c].y : d[j][c].x) = xl[c * VC::STRIDE + site0 + 4 * T * j];
+    }
+
     const R h = (R)(-a.dt);
     const R h2 = (R)(-0.5 * a.dt), h6 = (R)(-a.dt / 6.0), third = (R)(1.0 / 3.0);
-    const C phyz = sh_phyz[line];
-    const R ky = (R)S->kap[1], kz = (R)S->kap[2];   // zero on non-trivial axes
-    const bool has_g = S->dim >= 2;
+    const R hk = (R)(-a.dt * dp5_a(DS + 1, DS));   // h a_{s+1,s} for the stage's own slope
+    const sptr<StageConst<R>> K = uni(reinterpret_cast<const StageConst<R>*>(a.consts) + (long long)solve * a.nst + (DP ? DS : STAGE));
+    const int n0 = N, n1 = S->n[1];
+    const int row = row0 + linec;
+    const int yy = row % n1, zz = row / n1;
+    const C phyz = cmul(gload<C>(ctab, S->ph + n0 + yy), gload<C>(ctab, S->ph + n0 + n1 + zz));
     const long long mask = S->mask;
     const R myz = (LAST && mask >= 0) ? rtab[mask + n0 + yy] * rtab[mask + n0 + n1 + zz] : (R)1;
-    // Dormand-Prince: slope k_j of the stage input's sum, at offset off of the line
-    auto dp5_prev = [&](C acc, long long off) {
 #pragma unroll
-        for (int j = 0; j < DS; ++j)
-            if (dp5_a(DS + 1, j) != 0.0)
-                acc = cadd(acc, cscale(gload_nt<C>(cview<R>(S->buf[dp5_kbuf(j)]) + base, off), (R)(-a.dt * dp5_a(DS + 1, j))));
-        return acc;
-    };
-    const R hk = (R)(-a.dt * dp5_a(DS + 1, DS));   // h a_{s+1,s} for the stage's own slope
-    // field A_mu at point idx of this line
-    auto field = [&](int idx, R (&A)[4]) {
-        A[0] = A[1] = A[2] = A[3] = (R)0;
+    for (int j = 0; j < SITES; ++j) {
+        const int idx = site0 + 4 * T * j;
+        const unsigned off = off0 + (unsigned)(4 * T * j * (int)sizeof(C));
+        // field A_mu and background phase at the site
+        R A[4] = {(R)0, (R)0, (R)0, (R)0};
+        for (int jt = 0; jt < nterm; ++jt) {
+            const sptr<TermDev> tm = uni(a.terms + S->term0 + jt);
+            gptr<const R> tab = rtab + tm->tab;
+            const R f = K->coef[jt] * tab[n0 + yy] * tab[n0 + n1 + zz] * tab[idx];
+            const int mu = tm->mu;
 #pragma unroll
-        for (int jt = 0; jt < MAX_TERMS; ++jt) {
-            if (jt < nterm) {
-                const R f = sh_fyz[line][jt] * rtab[sh_tab[jt] + idx];
-                const int mu = sh_mu[jt];
-                A[0] += mu == 0 ? f : (R)0;
-                A[1] += mu == 1 ? f : (R)0;
-                A[2] += mu == 2 ? f : (R)0;
-                A[3] += mu == 3 ? f : (R)0;
-            }
+            for (int u = 0; u < 4; ++u)
+                if (mu == u) A[u] += f;
         }
-    };
-    if constexpr (VC::SITE) {
-        // whole sites: (alpha^1 D_x y) of all four components through LDS
-        __syncthreads();
+        const C ph = cmul(gload<C>(ctab, S->ph + idx), phyz);
+        if (j + 1 < SITES) load(ops[(j + 1) & 1], j + 1);
+        const Ops& p = ops[j & 1];
+        // u = alpha^1 D_x y + G + beta y + kappa terms + (A_0 + alpha^j A_j)(y + psi_b)
+        C u[4], s[4];
 #pragma unroll
-        for (int m = 0; m < E; ++m) lds[Lay::addr(0, 4 * line + q, t + T * m)] = v[0][m];
-        __syncthreads();
-        const C wc[4] = {sh_wc[0], sh_wc[1], sh_wc[2], sh_wc[3]};
-        gptr<const nv2<R>> pg = cview<R>(S->buf[BUF_T]) + base;
-        gptr<const nv2<R>> pop = cview<R>(S->buf[STAGE == 3 ? BUF_ACC : BUF_Y]) + base;
-        gptr<nv2<R>> wys = wview<R>(S->buf[BUF_YS]) + base;
-        gptr<nv2<R>> wk = wview<R>(S->buf[dp5_kbuf(DS < 5 ? DS : 0)]) + base;
-        gptr<nv2<R>> wacc = wview<R>(S->buf[BUF_ACC]) + base;
-        gptr<nv2<R>> wy = wview<R>(S->buf[BUF_Y]) + base;
+        for (int c = 0; c < 4; ++c) {
+            const C w = cadd(d[j][c], p.g[c]);
+            u[c] = c < 2 ? cadd(w, p.y[c]) : csub(w, p.y[c]);
+            s[c] = cadd(p.y[c], cmul(cmake<C>(K->w[2 * c], K->w[2 * c + 1]), ph));
+        }
+        if (dim < 3) {
+            const R ky = (R)S->kap[1], kz = (R)S->kap[2];   // zero on non-trivial axes
 #pragma unroll
-        for (int j = 0; j < (E + 3) / 4; ++j) {
-            const int m = q + 4 * j;
-            if (m < E) {
-                const int idx = t + T * m;
-                C y[4], g[4], y0[4], u[4];
+            for (int c = 0; c < 4; ++c)
+                u[c] = cadd(u[c], cadd(cscale(alpha2_phase(c, p.y[3 - c]), ky), cscale(alpha3_phase(c, p.y[c ^ 2]), kz)));
+        }
+        // only the components some term has (the bits are the same for the whole workgroup)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    y[c] = gload_nt<C>(pin, c * ns + idx);
-                    g[c] = has_g ? gload_nt<C>(pg, c * ns + idx) : cmake<C>((R)0, (R)0);
-                    y0[c] = FIRST ? cmake<C>((R)0, (R)0) : gload_nt<C>(pop, c * ns + idx);
-                }
-                R A[4];
-                field(idx, A);
-                const C ph = cmul(gload<C>(ctab, S->ph + idx), phyz);
-                C sv[4], vs[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sv[c] = cadd(y[c], cmul(wc[c], ph));
-                apply_pot(sv, vs, A[0], A[1], A[2], A[3]);
-                const R mk = (LAST && mask >= 0) ? rtab[mask + idx] * myz : (R)1;
+        for (int mu = 0; mu < 4; ++mu)
+            if (mus & (1 << mu)) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const R bc = c < 2 ? (R)1 : (R)-1;
-                    C w = cadd(cadd(lds[Lay::addr(0, 4 * line + c, idx)], g[c]), cscale(y[c], bc));
-                    w = cadd(w, cadd(cscale(alpha2_phase(c, y[3 - c]), ky), cscale(alpha3_phase(c, y[c ^ 2]), kz)));
-                    u[c] = cmul_mi(cadd(w, vs[c]));   // k_c
-                }
-                // classical RK4 with the accumulator written once: with the stage
-                // inputs y_2 = y + h/2 k1, y_3 = y + h/2 k2, y_4 = y + h k3,
-                //   y_{n+1} = (y_2 + 2 y_3 - y)/3 + y_4/3 + h/6 k4,
-                // so stage 1 stores acc = (y_2 + 2 y_3 - y)/3 and stage 3 finishes
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const C k = u[c];
-                    if constexpr (DP) {
-                        // Dormand-Prince: y_{s+1} = y + h sum_{j<=s} a_{s+1,j} k_j (row 6: the step)
-                        const C yn = cadd(dp5_prev(DS == 0 ? y[c] : y0[c], c * ns + idx), cscale(k, hk));
-                        if (act) {
-                            if constexpr (DS < 5) {
-                                gstore_nt<C>(wk, c * ns + idx, k);
-                                gstore_nt<C>(wys, c * ns + idx, yn);
-                            } else {
-                                gstore_nt<C>(wy, c * ns + idx, cscale(yn, mk));
-                            }
-                        }
-                    } else if constexpr (STAGE == 0) {
-                        if (act) gstore_nt<C>(wys, c * ns + idx, cadd(y[c], cscale(k, h2)));             // y_2
-                    } else if constexpr (STAGE == 1) {
-                        const C y3 = cadd(y0[c], cscale(k, h2));                                          // y_3
-                        if (act) {
-                            gstore_nt<C>(wacc, c * ns + idx, cscale(csub(cadd(y[c], cscale(y3, (R)2)), y0[c]), third));
-                            gstore_nt<C>(wys, c * ns + idx, y3);
-                        }
-                    } else if constexpr (STAGE == 2) {
-                        if (act) gstore_nt<C>(wys, c * ns + idx, cadd(y0[c], cscale(k, h)));             // y_4
-                    } else {
-                        if (act) gstore_nt<C>(wy, c * ns + idx, cscale(cadd(cadd(y0[c], cscale(y[c], third)), cscale(k, h6)), mk));
-                    }
+                    const C b = mu == 0 ? s[c] : mu == 1 ? s[3 - c] : mu == 2 ? alpha2_phase(c, s[3 - c]) : alpha3_phase(c, s[c ^ 2]);
+                    u[c] = cadd(u[c], cscale(b, A[mu]));
                 }
             }
-        }
-    } else {
-        // component q at the thread's own points
-        const C wq = sh_wc[q], wx = sh_wc[qx], wz = sh_wc[qz];
-        const R bq = q < 2 ? (R)1 : (R)-1;
-        gptr<const nv2<R>> pg = cview<R>(S->buf[BUF_T]) + base + q * ns + t;
-        gptr<const nv2<R>> py = cview<R>(S->buf[BUF_Y]) + base + q * ns + t;
-        gptr<const nv2<R>> pacc = cview<R>(S->buf[BUF_ACC]) + base + q * ns + t;
-        gptr<nv2<R>> wys = wview<R>(S->buf[BUF_YS]) + base + q * ns + t;
-        gptr<nv2<R>> wacc = wview<R>(S->buf[BUF_ACC]) + base + q * ns + t;
-        gptr<nv2<R>> wy = wview<R>(S->buf[BUF_Y]) + base + q * ns + t;
-        gptr<nv2<R>> wk = wview<R>(S->buf[dp5_kbuf(DS < 5 ? DS : 0)]) + base + q * ns + t;
+        // classical RK4 with the accumulator written once: with the stage
+        // inputs y_2 = y + h/2 k1, y_3 = y + h/2 k2, y_4 = y + h k3,
+        //   y_{n+1} = (y_2 + 2 y_3 - y)/3 + y_4/3 + h/6 k4,
+        // so stage 1 stores acc = (y_2 + 2 y_3 - y)/3 and stage 3 finishes
+        const R mk = (LAST && mask >= 0) ? rtab[mask + idx] * myz : (R)1;
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int idx = t + T * m;
-            const C g = has_g ? gload_nt<C>(pg, T * m) : cmake<C>((R)0, (R)0);
-            C y0 = cmake<C>((R)0, (R)0);
-            if constexpr (STAGE == 1 || STAGE == 2 || (DP && DS > 0)) y0 = gload_nt<C>(py, T * m);
-            if constexpr (STAGE == 3) y0 = gload_nt<C>(pacc, T * m);
-            R A[4];
-            field(idx, A);
-            const C ph = cmul(gload<C>(ctab, S->ph + idx), phyz);
-            // y + psi_b on the three components
-            const C sq = cadd(yq[m], cmul(wq, ph)), sx = cadd(yx[m], cmul(wx, ph)), sz = cadd(yz[m], cmul(wz, ph));
-            // [alpha^1 D_x y + G + beta y + kappa terms + A0 s + (A1 alpha^1 + A2 alpha^2) s + A3 alpha^3 s]_q
-            C u = cadd(cadd(v[0][m], g), cscale(yq[m], bq));
-            u = cadd(u, cadd(cscale(alpha2_phase(q, yx[m]), ky), cscale(alpha3_phase(q, yz[m]), kz)));
-            u = cadd(u, cscale(sq, A[0]));
-            u = cadd(u, cadd(cscale(sx, A[1]), cscale(alpha2_phase(q, sx), A[2])));
-            u = cadd(u, cscale(alpha3_phase(q, sz), A[3]));
-            const C k = cmul_mi(u);
-            // classical RK4 with the accumulator written once (as above)
+        for (int c = 0; c < 4; ++c) {
+            const C k = cmul_mi(u[c]);
+            C o0, o1;
             if constexpr (DP) {
-                const C yn = cadd(dp5_prev(DS == 0 ? yq[m] : y0, q * ns + idx), cscale(k, hk));
-                if (act) {
-                    if constexpr (DS < 5) {
-                        gstore_nt<C>(wk, T * m, k);
-                        gstore_nt<C>(wys, T * m, yn);
-                    } else {
-                        const R mk = mask >= 0 ? rtab[mask + idx] * myz : (R)1;
-                        gstore_nt<C>(wy, T * m, cscale(yn, mk));
-                    }
-                }
+                // Dormand-Prince: y_{s+1} = y + h sum_{j<=s} a_{s+1,j} k_j (row 6: the step)
+                C acc = DS == 0 ? p.y[c] : p.o[c];
+#pragma unroll
+                for (int i = 0; i < DS; ++i)
+                    if (dp5_a(DS + 1, i) != 0.0)
+                        acc = cadd(acc, cscale(gload_at<C>((gptr<const char>)(cview<R>(S->buf[dp5_kbuf(i)]) + (c * ns + tile0)), off),
+                                               (R)(-a.dt * dp5_a(DS + 1, i))));
+                o0 = cadd(acc, cscale(k, hk));
+                if constexpr (LAST) o0 = cscale(o0, mk);
+                o1 = k;
             } else if constexpr (STAGE == 0) {
-                if (act) gstore_nt<C>(wys, T * m, cadd(yq[m], cscale(k, h2)));                    // y_2
+                o0 = cadd(p.y[c], cscale(k, h2));                                                 // y_2
             } else if constexpr (STAGE == 1) {
-                const C y3 = cadd(y0, cscale(k, h2));                                              // y_3
-                if (act) {
-                    gstore_nt<C>(wacc, T * m, cscale(csub(cadd(yq[m], cscale(y3, (R)2)), y0), third));
-                    gstore_nt<C>(wys, T * m, y3);
-                }
+                o0 = cadd(p.o[c], cscale(k, h2));                                                 // y_3
+                o1 = cscale(csub(cadd(p.y[c], cscale(o0, (R)2)), p.o[c]), third);
             } else if constexpr (STAGE == 2) {
-                if (act) gstore_nt<C>(wys, T * m, cadd(y0, cscale(k, h)));                          // y_4
+                o0 = cadd(p.o[c], cscale(k, h));                                                  // y_4
             } else {
-                const R mk = mask >= 0 ? rtab[mask + idx] * myz : (R)1;
-                if (act) gstore_nt<C>(wy, T * m, cscale(cadd(cadd(y0, cscale(yq[m], third)), cscale(k, h6)), mk));
+                o0 = cscale(cadd(cadd(p.o[c], cscale(p.y[c], third)), cscale(k, h6)), mk);
+            }
+            if (act) {
+                if constexpr (STAGE == 1 || (DP && DS < 5)) gstore_at(w1[c], off, o1);
+                gstore_at(w0[c], off, o0);
             }
         }
     }
@@ -1114,8 +1092,8 @@ struct RowVariant { const void* stage[4]; const void* dp5[6]; int threads, rows;
 struct CdVariant { const void* fn[2][2]; int threads, w; size_t lds; int pipe; };   // [axis - 1][accumulate]; pipe: persistent y pass
 struct ColVariant { const void* fn[2][3]; int threads, w; size_t lds; };
 struct SizeKernels {
-    int nvar;                      // tile variants of the stepping passes
-    RowVariant row[NVAR];          // the RK4 stage row pass, by variant
+    int nvar;                      // tile variants of the stepping column passes
+    RowVariant row;                // the stage row pass
     CdVariant cd[NVAR];            // the stepping column passes, by variant
     const void* row_other[ROW_NMODES];  // whole-state row modes
     int row0_threads, row0_rows;
@@ -1127,14 +1105,14 @@ struct SizeKernels {
     size_t line_lds[2];            // their dynamic LDS without the field-term profiles
 };
 
-template <class R, int N, int V>
+template <class R, int N>
 RowVariant make_row_variant() {
-    using VC = RdVar<R, N, V>;
-    return RowVariant{{(const void*)row_d_kernel<R, N, V, 0>, (const void*)row_d_kernel<R, N, V, 1>,
-                       (const void*)row_d_kernel<R, N, V, 2>, (const void*)row_d_kernel<R, N, V, 3>},
-                      {(const void*)row_d_kernel<R, N, V, 4>, (const void*)row_d_kernel<R, N, V, 5>,
-                       (const void*)row_d_kernel<R, N, V, 6>, (const void*)row_d_kernel<R, N, V, 7>,
-                       (const void*)row_d_kernel<R, N, V, 8>, (const void*)row_d_kernel<R, N, V, 9>},
+    using VC = RdVar<R, N>;
+    return RowVariant{{(const void*)row_d_kernel<R, N, 0, 0>, (const void*)row_d_kernel<R, N, 0, 1>,
+                       (const void*)row_d_kernel<R, N, 0, 2>, (const void*)row_d_kernel<R, N, 0, 3>},
+                      {(const void*)row_d_kernel<R, N, 0, 4>, (const void*)row_d_kernel<R, N, 0, 5>,
+                       (const void*)row_d_kernel<R, N, 0, 6>, (const void*)row_d_kernel<R, N, 0, 7>,
+                       (const void*)row_d_kernel<R, N, 0, 8>, (const void*)row_d_kernel<R, N, 0, 9>},
                       VC::THREADS, VC::ROWS, VC::BYTES};
 }
 template <class R, int N, int V>
@@ -1171,20 +1149,14 @@ template <class R, int N>
 SizeKernels make_size_kernels() {
     SizeKernels k;
     k.nvar = nvar<N>();
-    k.row[0] = make_row_variant<R, N, 0>();
+    k.row = make_row_variant<R, N>();
     k.cd[0] = make_cd_variant<R, N, 0>();
     if constexpr (nvar<N>() > 1) {
-        k.row[1] = make_row_variant<R, N, 1>();
-        k.row[2] = make_row_variant<R, N, 2>();
-        k.row[3] = make_row_variant<R, N, 3>();
         k.cd[1] = make_cd_variant<R, N, 1>();
         k.cd[2] = make_cd_variant<R, N, 2>();
         k.cd[3] = make_cd_variant<R, N, 3>();
     } else {
-        for (int v = 1; v < NVAR; ++v) {
-            k.row[v] = k.row[0];
-            k.cd[v] = k.cd[0];
-        }
+        for (int v = 1; v < NVAR; ++v) k.cd[v] = k.cd[0];
     }
     // whole-state column transforms: the few-points plan where there is one
     k.col = make_col_variant<R, N, (nvar<N>() > 1 && has_small_plan<N>()) ? 2 : 0>();

@@ -70,6 +70,7 @@ __host__ __device__ inline int bw_blocks(long long ns, int nblk) {
     return b < nblk ? (int)b : nblk;
 }
 
+struct PassArgs;
 struct BwArgs {
     const SolveDev* solves;
     const VertexDev* verts;
@@ -78,6 +79,7 @@ struct BwArgs {
     const int* packets;             // the wave-packet vertices, one per blockIdx.y of their reduction
     const void* ctab;
     const int* step;
+    int step_add;        // steps enqueued since the device counter was last advanced
     double t_out, dt;
     int stage;
     double cst;          // the stage's time node: t = t_out - (step + cst) dt
@@ -146,7 +148,10 @@ hipError_t launch_bw_accum(const BwArgs& a, hipStream_t st);
 hipError_t launch_bw2_src(int fp64, const BwArgs& a, int blocks, hipStream_t st);
 hipError_t launch_bw2_kss(int fp64, const BwArgs& a, int blocks, hipStream_t st);
 hipError_t launch_bw2_accum(const BwArgs& a, int nblk, hipStream_t st);
-hipError_t launch_tick(int* step, hipStream_t st);
+// The stage constants (StageConst) of every solve at the step *a.step + a.step_add, for
+// the stage nodes cst[0..a.nst).
+struct StageNodes { double c[6]; };
+hipError_t launch_stage_consts(int fp64, const PassArgs& a, const StageNodes& cst, int nsolves, hipStream_t st);
 hipError_t launch_advance(int* step, int n, hipStream_t st);
 hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, int step, unsigned long long* flag,
                                hipStream_t st);

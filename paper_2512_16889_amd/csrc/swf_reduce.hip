@@ -339,7 +339,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_stage_kernel(BwArgs a) {
         double2 s = shw[0][3 * p + c];
 #pragma unroll
         for (int w = 1; w < NW; ++w) s = dadd(s, shw[w][3 * p + c]);
-        const double ts = a.t_out - (double)(*a.step) * a.dt - a.cst * a.dt;
+        const double ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - a.cst * a.dt;
         // phase of the term: -(k0 + [E_V]) t for (s,s) / (s,b), (E_U - k0) t for (b,s)
         double w = -a.verts[G->vtx[0]].k0;
         if (c == 1) w += a.solves[G->su[G->ui[j]]].E;
@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_packet_stage_kernel(BwArgs a) 
     const SolveDev* SU = a.solves + V->su;
     const SolveDev* SV = a.solves + V->sv;
     const int role = a.stage == 0 ? BUF_Y : BUF_YS;
-    const double ts = a.t_out - (double)(*a.step) * a.dt - a.cst * a.dt;
+    const double ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - a.cst * a.dt;
     const C* ctab = reinterpret_cast<const C*>(a.ctab);
     const int nm = V->nmodes;
     const int nblk = bw_blocks(SU->nsites, a.nblk);
@@ -603,7 +603,7 @@ __global__ void bw2_accum_kernel(BwArgs a, int nblk) {
     const SolveDev* SU = a.solves + V->su;
     const SolveDev* SV = a.solves + V->sv;
     const double wst[4] = {1.0, 2.0, 2.0, 1.0};
-    const int n = *a.step;
+    const int n = *a.step + a.step_add;
     double2 s = d2(0, 0);
     for (int st = 0; st < 4; ++st) {
         const double cst = st == 0 ? 0.0 : (st == 3 ? 1.0 : 0.5);
@@ -694,6 +694,39 @@ __global__ void __launch_bounds__(RED_THREADS) finite_kernel(const SolveDev* sol
 
 __global__ void tick_kernel(int* step, int n) {
     if (threadIdx.x == 0) __hip_atomic_fetch_add(step, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One thread per solve, stage and value: the background spinor at the stage's
+// time and the terms' time factors, in double.  (Formed here once per step, not
+// by every workgroup of every row pass: a pass' arithmetic then holds no
+// transcendental, and its loads wait for none.)
+template <class R>
+__global__ void __launch_bounds__(RED_THREADS) stage_const_kernel(PassArgs a, StageNodes nodes, int count) {
+    constexpr int SLOTS = 4 + MAX_TERMS;
+    const int gid = blockIdx.x * RED_THREADS + threadIdx.x;
+    if (gid >= count) return;
+    const int slot = gid % SLOTS, st = (gid / SLOTS) % a.nst, solve = gid / SLOTS / a.nst;
+    const SolveDev* S = a.solves + solve;
+    StageConst<R>* K = (StageConst<R>*)a.consts + (long long)solve * a.nst + st;
+    const double ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - nodes.c[st] * a.dt;
+    if (slot < 4) {
+        double sn, cs;
+        sincos(-S->E * ts, &sn, &cs);
+        const double wr = S->w[2 * slot], wi = S->w[2 * slot + 1];
+        K->w[2 * slot] = (R)(wr * cs - wi * sn);
+        K->w[2 * slot + 1] = (R)(wr * sn + wi * cs);
+    } else if (slot - 4 < S->nterm) {
+        const TermDev tm = a.terms[S->term0 + slot - 4];
+        K->coef[slot - 4] = (R)(tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts));
+    }
+}
+
+hipError_t launch_stage_consts(int fp64, const PassArgs& a, const StageNodes& nodes, int nsolves, hipStream_t st) {
+    const int count = nsolves * a.nst * (4 + MAX_TERMS);
+    const dim3 g((count + RED_THREADS - 1) / RED_THREADS), b(RED_THREADS);
+    if (fp64) hipLaunchKernelGGL(stage_const_kernel<double>, g, b, 0, st, a, nodes, count);
+    else hipLaunchKernelGGL(stage_const_kernel<float>, g, b, 0, st, a, nodes, count);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ launchers
@@ -805,8 +838,6 @@ hipError_t launch_combo(int fp64, const ComboArgs& a, int nitems, hipStream_t st
     else hipLaunchKernelGGL(combo_kernel<float>, dim3(nitems), dim3(RED_THREADS), 0, st, a);
     return hipGetLastError();
 }
-
-hipError_t launch_tick(int* step, hipStream_t st) { return launch_advance(step, 1, st); }
 
 hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, int step, unsigned long long* flag,
                                hipStream_t st) {
