@@ -849,14 +849,11 @@ static double group_sites(swf_ctx* ctx, const Group& g) {
 }
 
 // Launch one pass kernel over n items starting at item offset `it`.
-// maxblocks > 0: a persistent kernel that loops over the items with the grid's
-// stride, given at most that many workgroups per blockIdx.y.
 static int launch(swf_ctx* ctx, const void* fn, int nitems, size_t it, int threads, size_t lds, swf::PassArgs a,
-                  int kind, double bytes, int gy = 1, int maxblocks = 0) {
+                  int kind, double bytes, int gy = 1) {
     if (nitems <= 0) return SWF_OK;
     a.items = ctx->d_items() + it;
     a.nitems = nitems;
-    const int blocks = maxblocks > 0 ? std::min(nitems, maxblocks) : nitems;
     void* args[] = {&a};
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool prof = ctx->opt.profile && !ctx->gexec;
@@ -866,7 +863,7 @@ static int launch(swf_ctx* ctx, const void* fn, int nitems, size_t it, int threa
         if (r) return r;
         HIPCHK(hipEventRecord(e0, ctx->st));
     }
-    HIPCHK(hipLaunchKernel(fn, dim3(blocks, gy), dim3(threads), args, lds, ctx->st));
+    HIPCHK(hipLaunchKernel(fn, dim3(nitems, gy), dim3(threads), args, lds, ctx->st));
     if (prof) {
         HIPCHK(hipEventRecord(e1, ctx->st));
         ctx->pending.push_back({e0, e1, kind, bytes});
@@ -932,9 +929,20 @@ static int cd_pass(swf_ctx* ctx, const Group& g, int axis, int src, int kind) {
     a.dst = swf::BUF_T;
     const int n = axis == 1 ? g.n_coly[v] : g.n_colz[v];
     const size_t it = axis == 1 ? g.it_coly[v] : g.it_colz[v];
-    // persistent y passes: one workgroup per compute unit (all the LDS they leave room for)
-    return launch(ctx, cv.fn[axis - 1][accum], n, it, cv.threads, cv.lds, a, kind,
-                  (2.0 + accum) * 4.0 * ctx->P.csize * group_sites(ctx, g), 4, cv.pipe && !accum ? ctx->ncu : 0);
+    return launch(ctx, cv.fn[axis - 1], n, it, cv.threads, cv.lds, a, kind,
+                  (2.0 + accum) * 4.0 * ctx->P.csize * group_sites(ctx, g), 4);
+}
+
+// Tile variant of a stepping column pass when none was timed or forced: the
+// widest tile of which a compute unit holds several (4 lines of 128 bytes up to
+// 128 points, 2 up to 512, 1 beyond; the measured rates stand at the kernel),
+// narrower while the launch would leave compute units without a workgroup.
+static int default_tile(const swf_ctx* ctx, const Group& g, int axis) {
+    if (!g.k[axis]) return 0;
+    const int n = ctx->P.grids[g.grid].n[axis];
+    int v = n <= 128 ? 2 : n <= 512 ? 1 : 0;
+    while (v > 0 && 4 * (axis == 1 ? g.n_coly[v] : g.n_colz[v]) < 2 * ctx->ncu) --v;
+    return v;
 }
 
 // The passes of one RK4 stage of a group: the column derivatives of the stage
@@ -1395,8 +1403,8 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
         auto it = cache.find(key);
         const int dim = ctx->P.grids[g.grid].dim;
         if (it != cache.end()) {
-            g.vy = dim >= 2 ? std::min(it->second[1], g.k[1]->nvar - 1) : 0;
-            g.vz = dim >= 3 ? std::min(it->second[2], g.k[2]->nvar - 1) : 0;
+            g.vy = dim >= 2 ? std::min(it->second[1], swf::NVAR - 1) : 0;
+            g.vz = dim >= 3 ? std::min(it->second[2], swf::NVAR - 1) : 0;
             rep << key << ": cached 0 " << g.vy << " " << g.vz << "\n";
             continue;
         }
@@ -1412,7 +1420,7 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
         for (int axis = 1; axis < dim; ++axis) {
             float best = 1e30f;
             int bv = 0;
-            for (int v = 0; v < g.k[axis]->nvar; ++v) {
+            for (int v = 0; v < swf::NVAR; ++v) {
                 (axis == 1 ? g.vy : g.vz) = v;
                 float ms = 0;
                 int r = time_it(ctx, [&] { return cd_pass(ctx, g, axis, swf::BUF_YS, 4); }, reps, &ms);
@@ -1943,10 +1951,14 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
                     INITCHK(hipFuncSetAttribute(k->row.dp5[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row.lds));
                 for (int v = 0; v < swf::NVAR; ++v) {
                     for (int a = 0; a < 2; ++a)
-                        for (int m = 0; m < 2; ++m)
-                            INITCHK(hipFuncSetAttribute(k->cd[v].fn[a][m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->cd[v].lds));
+                        INITCHK(hipFuncSetAttribute(k->cd[v].fn[a], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->cd[v].lds));
                 }
             }
+    for (auto* gl : {&P.batched, &P.single})
+        for (auto& g : *gl) {
+            g.vy = default_tile(ctx, g, 1);
+            g.vz = default_tile(ctx, g, 2);
+        }
     ctx->kvalid.assign(P.solves.size(), 0);
     ctx->bw_done.assign(P.hv.size(), 0);
     ctx->bw_cache.assign(6 * P.hv.size(), cd(0));
@@ -1954,8 +1966,7 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
         const int v = opt->force_variant - 1;
         for (auto* gl : {&P.batched, &P.single})
             for (auto& g : *gl) {
-                g.vy = g.k[1] ? std::min(v, g.k[1]->nvar - 1) : 0;
-                g.vz = g.k[2] ? std::min(v, g.k[2]->nvar - 1) : 0;
+                g.vy = g.vz = std::min(v, swf::NVAR - 1);
             }
     } else if (opt->tune && !line_path(ctx) && !ctx->P.ip) {   // (the interaction picture runs no stage pass)
         int rr = autotune(ctx, ctx->opt.batched ? ctx->P.batched : ctx->P.single);

@@ -133,6 +133,51 @@ SWF_PLAN(160, 8, 5, 4, 4, 2)
 SWF_PLAN(320, 16, 5, 4, 4, 4)
 #undef SWF_PLAN
 
+// Plans of the stepping passes, whose threads hold one component of a line: at
+// most 64 threads a line, and composite radices (12, 16, 20) so that the points
+// go through LDS once less than with the default plans: one exchange for 16 to
+// 80 points, three for 384 and 768, two for the others.  (One exchange for 128
+// and 256 points, by radix 16 with half the threads, was no faster on large
+// batches and 1.5x slower on 8 x 128^2, which then has too few wavefronts.)
+template <int N> struct StepPlan;
+#define SWF_PLAN(N_, T_, ...)                                            \
+    template <> struct StepPlan<N_> {                                    \
+        static constexpr int T = T_;                                     \
+        static constexpr int R[] = {__VA_ARGS__};                        \
+        static constexpr int NR = sizeof(R) / sizeof(int);               \
+    };
+SWF_PLAN(16, 2, 8, 2)
+SWF_PLAN(32, 4, 8, 4)
+SWF_PLAN(64, 8, 8, 8)
+SWF_PLAN(128, 16, 8, 8, 2)
+SWF_PLAN(256, 32, 8, 8, 4)
+SWF_PLAN(512, 64, 8, 8, 8)
+SWF_PLAN(1024, 64, 16, 16, 4)
+SWF_PLAN(48, 4, 12, 4)
+SWF_PLAN(96, 8, 12, 4, 2)
+SWF_PLAN(192, 16, 12, 4, 4)
+SWF_PLAN(384, 32, 12, 4, 4, 2)
+SWF_PLAN(768, 64, 12, 4, 4, 4)
+SWF_PLAN(40, 2, 20, 2)
+SWF_PLAN(80, 4, 20, 4)
+SWF_PLAN(160, 8, 20, 4, 2)
+SWF_PLAN(320, 16, 20, 4, 4)
+#undef SWF_PLAN
+
+// Plans of the stepping column passes, where they differ.
+template <int N> struct ColPlan : StepPlan<N> {};
+#define SWF_PLAN(N_, T_, ...)                                            \
+    template <> struct ColPlan<N_> {                                     \
+        static constexpr int T = T_;                                     \
+        static constexpr int R[] = {__VA_ARGS__};                        \
+        static constexpr int NR = sizeof(R) / sizeof(int);               \
+    };
+SWF_PLAN(384, 16, 8, 8, 6)
+SWF_PLAN(768, 32, 8, 8, 12)
+SWF_PLAN(1024, 32, 32, 32)
+#undef SWF_PLAN
+
+
 // Plans with 4 points per thread (radix 4, a final radix 2 when log2 N is
 // odd): twice the threads per line and half the registers of the default.
 template <int N> struct Plan4;
@@ -301,6 +346,82 @@ template <int DIR, class C> struct Dft<10, DIR, C> {
     }
 };
 
+// cos(2 pi m / 32)
+constexpr double cos32(int m) {
+    constexpr double c[9] = {1.0, 0.98078528040323044913, 0.92387953251128675613, 0.83146961230254523708,
+                             0.70710678118654752440, 0.55557023301960222474, 0.38268343236508977173,
+                             0.19509032201612826785, 0.0};
+    m &= 31;
+    return m <= 8 ? c[m] : m <= 16 ? -c[16 - m] : m <= 24 ? -c[m - 16] : c[32 - m];
+}
+// R1 R2 points (dividing 32), w = exp(DIR 2 pi i / (R1 R2)):
+//   y[k1 + R1 k2] = sum_n2 w_R2^{n2 k2} w^{n2 k1} sum_n1 w_R1^{n1 k1} a[R2 n1 + n2]
+template <int R1, int R2, int DIR, class C> __device__ __forceinline__ void dft_twiddled(C* a) {
+    using R = decltype(C::x);
+    C b[R2][R1];
+#pragma unroll
+    for (int n = 0; n < R2; ++n) {
+#pragma unroll
+        for (int i = 0; i < R1; ++i) b[n][i] = a[R2 * i + n];
+        Dft<R1, DIR, C>::run(b[n]);
+#pragma unroll
+        for (int k = 0; k < R1; ++k) {
+            const int m = n * k * (32 / (R1 * R2));
+            if (m == 8) b[n][k] = cmul_di<DIR>(b[n][k]);
+            else if (m != 0) b[n][k] = cmul(b[n][k], cmake<C>((R)cos32(m), (R)(DIR * cos32(m - 8))));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < R1; ++k) {
+        C d[R2];
+#pragma unroll
+        for (int n = 0; n < R2; ++n) d[n] = b[n][k];
+        Dft<R2, DIR, C>::run(d);
+#pragma unroll
+        for (int m = 0; m < R2; ++m) a[k + R1 * m] = d[m];
+    }
+}
+template <int DIR, class C> struct Dft<16, DIR, C> {
+    static __device__ __forceinline__ void run(C* a) { dft_twiddled<4, 4, DIR, C>(a); }
+};
+template <int DIR, class C> struct Dft<32, DIR, C> {
+    static __device__ __forceinline__ void run(C* a) { dft_twiddled<4, 8, DIR, C>(a); }
+};
+
+// Coprime R1 R2 (Good and Thomas): with n = (R2 n1 + R1 n2) mod R the transform
+// is the two-dimensional one of R1 x R2 points without twiddles, its output
+// (k1, k2) at the k with k mod R1 = k1 and k mod R2 = k2.
+template <int R1, int R2, int DIR, class C> __device__ __forceinline__ void dft_coprime(C* a) {
+    constexpr int R = R1 * R2;
+    C b[R1][R2];
+#pragma unroll
+    for (int i = 0; i < R1; ++i) {
+#pragma unroll
+        for (int j = 0; j < R2; ++j) b[i][j] = a[(R2 * i + R1 * j) % R];
+        Dft<R2, DIR, C>::run(b[i]);
+    }
+#pragma unroll
+    for (int j = 0; j < R2; ++j) {
+        C d[R1];
+#pragma unroll
+        for (int i = 0; i < R1; ++i) d[i] = b[i][j];
+        Dft<R1, DIR, C>::run(d);
+#pragma unroll
+        for (int i = 0; i < R1; ++i) b[i][j] = d[i];
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) a[k] = b[k % R1][k % R2];
+}
+template <int DIR, class C> struct Dft<12, DIR, C> {
+    static __device__ __forceinline__ void run(C* a) { dft_coprime<3, 4, DIR, C>(a); }
+};
+template <int DIR, class C> struct Dft<24, DIR, C> {
+    static __device__ __forceinline__ void run(C* a) { dft_coprime<3, 8, DIR, C>(a); }
+};
+template <int DIR, class C> struct Dft<20, DIR, C> {
+    static __device__ __forceinline__ void run(C* a) { dft_coprime<5, 4, DIR, C>(a); }
+};
+
 // ---------------------------------------------------------------- Stockham steps
 // Registers: v[q][m] holds component q's point t + T*m (natural order) before
 // the first step and after the last.  Step J (radix R, stride NS = product of the
@@ -404,36 +525,46 @@ __device__ __forceinline__ void fft_line(C (&v)[NC][N / T], C* lds, int t, int l
     FftRun<C, N, T, 0, DIR, NC, CG, Lay, P>::run(v, lds, t, line, tw);
 }
 
-// The same transform of one line held by T lanes of one wave (T divides 64):
-// its exchanges need no barrier.  Output k of butterfly b of a step (radix Rp,
-// stride NSp) is kept in LDS at k (N/Rp + PAD) + b, so a thread writes one row
-// per output, lanes side by side, and what the next step's butterfly takes,
+// The transform of the stepping passes: one component per thread.  Output k of
+// butterfly b of a step (radix Rp, stride NSp) is kept in LDS at entry
+// k (N/Rp + PAD) + b, so a thread writes one row per output, lanes side by side,
+// and what the next step's butterfly takes,
 //   point i = b + k N/R:  row (i / NSp) mod Rp, entry (i / NS) NSp + i mod NSp,
 // lies at constant distances for its inputs k: one address per butterfly
 // instead of one per point (a third of the transform's integer work), and
-// fewer bank conflicts (counted over all exchanges of a line, 320 points of 8
-// bytes: 608 cycles a wave instead of 912).  SPLIT: the real and the imaginary
-// parts one after the other through a buffer of half the size.
-// PAD and the extra distance between a wave's lines are those with the fewest
-// bank conflicts, counted for every length and element size (4, 8 or 16 bytes).
+// fewer bank conflicts.  W: distance of neighbouring entries in the buffer (the
+// columns of a tile).  SPLIT: the real and the imaginary parts one after the
+// other through a buffer of half the size.  WAVE: all threads of the line (of
+// the tile) are in one wave, so the exchange needs no barrier.
+//
+// PAD and the extra distance between the lines of a wave are those with the
+// fewest bank conflicts, counted over all exchanges of every length and element
+// size (4, 8 or 16 bytes; 320 points of 8 bytes: 416 cycles a wave, where the
+// default plan padded by 1 in 16 took 912).
 constexpr int xch_pad(int n, int bytes) {
-    return n % 5 == 0 ? (n == 320 ? (bytes <= 8 ? 13 : 5) : n == 160 ? 5 : 1)
-         : n % 3 == 0 ? (bytes <= 8 && n >= 192 ? 11 : 3)
-         : n < 128 || bytes == 16 ? 1 : bytes == 8 || n == 128 ? 2 : 4;
+    return bytes == 16 ? 1
+         : bytes == 8 ? (n >= 128 && n != 160 && n != 320 && n != 1024 ? 2 : 1)
+         : n == 192 ? 6 : n == 320 ? 5 : n == 384 || n == 768 ? 12 : n == 256 || n == 512 ? 4 : n == 128 || n == 1024 ? 2 : 1;
 }
 constexpr int xch_skew(int n, int bytes) {
-    return n == 16 ? 2 : n == 32 ? 4 : n == 40 ? 1 : n == 80 ? 7 : bytes == 16 ? 0 : n == 96 ? 12 : n == 160 ? 15
-         : bytes == 4 && n == 320 ? 15 : bytes == 4 && n == 192 ? 4 : 0;
+    return n == 16 || n == 40 ? 2 : n == 32 ? 4
+         : bytes == 16 ? 0
+         : n == 96 ? 12 : n == 160 ? 4
+         : bytes == 4 && n == 192 ? 8 : bytes == 4 && n == 320 ? 12 : 0;
 }
-// elements of one line's exchange buffer
+// entries of one line's exchange buffer
 template <int N, class P, int BYTES> constexpr int xch_stride() {
     int r = 0;
     for (int j = 0; j + 1 < P::NR; ++j) r = P::R[j] > r ? P::R[j] : r;
     return N + r * xch_pad(N, BYTES) + xch_skew(N, BYTES);
 }
-template <class C, int N, int T, int J, bool SPLIT, class P>
-__device__ __forceinline__ void fft_exchange_wave(C (&v)[N / T], void* line, int t) {
-    using R_ = decltype(C::x);
+template <bool WAVE> __device__ __forceinline__ void xch_order() {
+    if constexpr (WAVE) wave_lds_order();
+    else __syncthreads();
+}
+template <class C, int N, int T, int J, class P, int W, int PAD, bool SPLIT, bool WAVE>
+__device__ __forceinline__ void step_exchange(C (&v)[N / T], void* buf, int t) {
+    using E_ = decltype(C::x);
     constexpr int Rp = P::R[J - 1];
     constexpr int NSp = plan_stride<P>(J - 1);
     constexpr int NS = NSp * Rp;
@@ -441,40 +572,49 @@ __device__ __forceinline__ void fft_exchange_wave(C (&v)[N / T], void* line, int
     constexpr int E = N / T;
     constexpr int Bp = E / Rp;
     constexpr int B = E / R;
-    constexpr int ROW = N / Rp + xch_pad(N, SPLIT ? sizeof(R_) : sizeof(C));
+    constexpr int ROW = N / Rp + PAD;
 #pragma unroll
     for (int h = 0; h < (SPLIT ? 2 : 1); ++h) {
-        wave_lds_order();
+        xch_order<WAVE>();
 #pragma unroll
         for (int c = 0; c < Bp; ++c)
 #pragma unroll
             for (int k = 0; k < Rp; ++k) {
                 const C x = v[c + Bp * k];
-                if constexpr (SPLIT) ((R_*)line)[k * ROW + T * c + t] = h ? x.y : x.x;
-                else ((C*)line)[k * ROW + T * c + t] = x;
+                if constexpr (SPLIT) ((E_*)buf)[(k * ROW + T * c) * W + t * W] = h ? x.y : x.x;
+                else ((C*)buf)[(k * ROW + T * c) * W + t * W] = x;
             }
-        wave_lds_order();
+        xch_order<WAVE>();
 #pragma unroll
         for (int c = 0; c < B; ++c) {
             const int b = t + T * c;
-            const int at = (b / NSp) % Rp * ROW + b / NS * NSp + b % NSp;
+            const int at = ((b / NSp) % Rp * ROW + b / NS * NSp + b % NSp) * W;
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 C& x = v[c + B * k];
-                if constexpr (SPLIT) (h ? x.y : x.x) = ((const R_*)line)[at + k * (N / (R * Rp))];
-                else x = ((const C*)line)[at + k * (N / (R * Rp))];
+                if constexpr (SPLIT) (h ? x.y : x.x) = ((const E_*)buf)[at + k * (N / (R * Rp)) * W];
+                else x = ((const C*)buf)[at + k * (N / (R * Rp)) * W];
             }
         }
     }
 }
-template <class C, int N, int T, int J, int DIR, bool SPLIT, class P>
-__device__ __forceinline__ void fft_line_wave(C (&v)[N / T], void* line, int t, const C* tw) {
-    static_assert(64 % T == 0, "a line within one wave");
+template <class C, int N, int T, int J, int DIR, class P, int W, int PAD, bool SPLIT, bool WAVE>
+__device__ __forceinline__ void step_line(C (&v)[N / T], void* buf, int t, const C* tw) {
     if constexpr (J < P::NR) {
-        if constexpr (J > 0) fft_exchange_wave<C, N, T, J, SPLIT, P>(v, line, t);
+        if constexpr (J > 0) step_exchange<C, N, T, J, P, W, PAD, SPLIT, WAVE>(v, buf, t);
         fft_step<C, N, T, J, DIR, 1, P>(reinterpret_cast<C(&)[1][N / T]>(v), t, tw);
-        fft_line_wave<C, N, T, J + 1, DIR, SPLIT, P>(v, line, t, tw);
+        step_line<C, N, T, J + 1, DIR, P, W, PAD, SPLIT, WAVE>(v, buf, t, tw);
     }
+}
+// a row line within one wave; a column tile of W lines
+template <class C, int N, int DIR, bool SPLIT, class P>
+__device__ __forceinline__ void fft_row(C (&v)[N / P::T], void* line, int t, const C* tw) {
+    static_assert(64 % P::T == 0, "a line within one wave");
+    step_line<C, N, P::T, 0, DIR, P, 1, xch_pad(N, SPLIT ? sizeof(v[0].x) : sizeof(C)), SPLIT, true>(v, line, t, tw);
+}
+template <class C, int N, int DIR, int W, bool SPLIT, class P>
+__device__ __forceinline__ void fft_col(C (&v)[N / P::T], void* col, int t, const C* tw) {
+    step_line<C, N, P::T, 0, DIR, P, W, 0, SPLIT, P::T * W <= 64>(v, col, t, tw);
 }
 
 // LDS layouts.  Row passes: lanes run along the line (t fastest), one padded

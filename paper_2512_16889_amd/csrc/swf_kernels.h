@@ -74,8 +74,7 @@ template <int N> constexpr int half_t() {
     constexpr int T = FftPlan<N>::T;
     return (T % 2 == 0 && 2 * N / T <= 16 && plan_ok<N, T / 2>()) ? T / 2 : T;
 }
-constexpr int NVAR = 4;       // tile variants of the stepping column passes
-template <int N> constexpr int nvar() { return N >= 256 ? NVAR : 1; }
+constexpr int NVAR = 3;       // tile variants of the stepping column passes
 constexpr size_t LDS_CAP = 72 * 1024;
 constexpr int imax(int a, int b) { return a > b ? a : b; }
 constexpr int imin(int a, int b) { return a < b ? a : b; }
@@ -421,195 +420,152 @@ __global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArg
 template <class C> __device__ __forceinline__ C alpha2_phase(int q, C v) { return (q & 1) ? cmul_i(v) : cmul_mi(v); }
 template <class C> __device__ __forceinline__ C alpha3_phase(int q, C v) { return (q & 1) ? cmake<C>(-v.x, -v.y) : v; }
 
+// Values that are the same for a whole workgroup are read through the constant
+// address space, as scalar loads.
+template <class T> using sptr = const T __attribute__((address_space(4)))*;
+template <class T> __device__ __forceinline__ sptr<T> uni(const T* p) { return (sptr<T>)p; }
+
+// A uniform address the compiler has to keep in scalar registers (it otherwise
+// folds the lane's offset into a chain of 64-bit vector addresses, two registers
+// each).
+__device__ __forceinline__ gptr<const char> scalar_base(gptr<const char> p) {
+    asm("" : "+s"(p));
+    return p;
+}
+// A complex number at a uniform base plus a byte offset of 32 bits.
+template <class C, bool NT = true> __device__ __forceinline__ C gload_at(gptr<const char> base, unsigned off) {
+    using V2 = nv2<decltype(C::x)>;
+    V2 v;
+    if constexpr (NT) v = __builtin_nontemporal_load((gptr<const V2>)(base + off));
+    else v = *(gptr<const V2>)(base + off);
+    return cmake<C>(v.x, v.y);
+}
+template <bool NT = true, class C> __device__ __forceinline__ void gstore_at(gptr<char> base, unsigned off, C c) {
+    using V2 = nv2<decltype(C::x)>;
+    V2 v;
+    v.x = c.x;
+    v.y = c.y;
+    if constexpr (NT) __builtin_nontemporal_store(v, (gptr<V2>)(base + off));
+    else *(gptr<V2>)(base + off) = v;
+}
+
 // Column derivative pass: the blocks of blockIdx.y = q transform the
 // component alpha^j takes for output component q along axis j = AXIS (y or
 // z), multiply by k_j / n_j, transform back, and write (ACCUM = 0) or add
 // (ACCUM = 1) the result, with alpha^j's phase, into component q of the G
 // buffer (a.dst).  a.src: the stage input.  One component per thread: E
-// points of the transform in registers.
-//   v0: default plan, one 128-byte line of x per tile;  v1: few-points plan, one line;
-//   v2: few-points plan, two lines;                      v3: default plan, two lines.
+// points of the transform in registers, exchanged through LDS: as real and
+// imaginary parts in turn where whole numbers would leave a compute unit room
+// for one workgroup (SPLIT), so that one's loads cover another's transform.
+//   v0, v1, v2: 1, 2, 4 lines of 128 bytes along x per tile.
+// What bounds it: the access pattern, rows of a tile's width at the stride of
+// the axis.  More lines per row help while several tiles fit a compute unit:
+// 31 x 128^3 in single precision, y / z: 4.9 / 5.0 TB/s with one line, 6.1 / 5.8
+// with four; 64 x 512^2 in double 5.1 with one, 5.5 with two; 768 points and
+// more only fit one (28 x 768^2 in double 4.8 TB/s, two lines 4.0).  The 768-
+// and 1024-point passes ran at 3.2 / 3.9 TB/s in double and 2.7 / 3.4 in single
+// precision as one persistent workgroup per compute unit with the default plans.
 template <class R, int N, int V> struct CdVar {
-    static constexpr int WANT = sizeof(R) == 4 ? 16 : 8;   // columns per 128-byte line
-    static constexpr bool SMALL = (V == 1 || V == 2) && has_small_plan<N>();
-    using PL = typename PlanSel<N, SMALL>::type;
+    static constexpr int LINE = 128 / sizeof(cpx<R>);   // columns per 128-byte line
+    using PL = ColPlan<N>;
     static constexpr int T = PL::T;
     static constexpr int E = N / T;
-    // widest power-of-two tile whose exchange buffer fits the LDS with the twiddles
-    static constexpr int WFIT = (int)((163840 - N * sizeof(cpx<R>) - 1024) / (N * sizeof(cpx<R>)));
-    static constexpr int WMAX = WFIT >= 32 ? 32 : (WFIT >= 16 ? 16 : (WFIT >= 8 ? 8 : (WFIT >= 4 ? 4 : 2)));
-    static constexpr int W = imax(1, imin(imin(WANT * (V >= 2 ? 2 : 1), 1024 / T), WMAX));
+    static constexpr size_t TAB = N * sizeof(cpx<R>) + (sizeof(R) == 4 ? N * sizeof(R) : 0);
+    // widest power-of-two tile whose exchange buffer fits the LDS with the tables
+    static constexpr int WFIT = (int)((163840 - TAB) / (N * sizeof(R)));
+    static constexpr int WMAX = WFIT >= 64 ? 64 : (WFIT >= 32 ? 32 : (WFIT >= 16 ? 16 : 8));
+    // (short lines: at least a wave per tile)
+    static constexpr int W = imin(imin(imax(LINE << V, 64 / T), 1024 / T), WMAX);
     static constexpr int THREADS = T * W;
-    static constexpr size_t BYTES = (size_t)N * W * sizeof(cpx<R>);
-    // A tile whose exchange buffer and twiddles leave room for only one
-    // workgroup per compute unit (160 KB of LDS) would leave HBM idle while it
-    // transforms; those y passes run as a persistent loop over the tiles that
-    // loads the next tile while this one is transformed.  Only where the
-    // workgroup has at most 512 threads (with more, the prefetch would spill)
-    // and the tile is at most 8 columns wide: every lattice length is a
-    // multiple of 8, so such tiles are never partial.
-    static constexpr bool PIPE = 2 * (BYTES + N * sizeof(cpx<R>)) > 163840 && THREADS <= 512 && 8 % W == 0;
+    static constexpr bool SPLIT = 2 * (N * W * sizeof(cpx<R>) + TAB) > 163840;
+    static constexpr int XB = SPLIT ? sizeof(R) : sizeof(cpx<R>);
+    static constexpr size_t XCH = (size_t)N * W * XB;
+    static constexpr size_t BYTES = XCH + TAB;
+    // the z pass's partial sums: loaded ahead of the transforms, or after them
+    // where they would cost a workgroup's worth of registers (320 points in single
+    // precision, two lines: 4.9 TB/s against 4.1)
+    static constexpr bool LATE = sizeof(R) == 4 && E >= 20;
+    // waves per SIMD the compiler is asked to fit, where it would otherwise end a
+    // few registers above what the LDS has room for: 8 points a thread (512 points
+    // in double, two lines: 66 registers leave one workgroup a compute unit and
+    // 3.9 TB/s, 64 leave two and 5.3), and the longest lines
+    static constexpr int FIT = (int)(163840 / BYTES) * imax(1, THREADS / 64) / 4;
+    template <int ACCUM> static constexpr int waves() {
+        return E <= 8 ? (ACCUM ? 1 : imax(1, imin(8, FIT)))
+             : sizeof(R) == 8 ? (E >= 24 && !ACCUM ? 2 : 1) : E >= 24 ? (ACCUM ? 2 : 4) : 1;
+    }
     static_assert(plan_ok<N, T, PL>(), "column derivative variant violates the FFT plan constraints");
 };
 
 template <class R, int N, int V, int AXIS, int ACCUM>
-__global__ void __launch_bounds__((CdVar<R, N, V>::THREADS)) col_d_kernel(PassArgs a) {
+__global__ void __launch_bounds__((CdVar<R, N, V>::THREADS))
+__attribute__((amdgpu_waves_per_eu(CdVar<R, N, V>::template waves<ACCUM>(), 8))) col_d_kernel(PassArgs a) {
     using C = cpx<R>;
     using VC = CdVar<R, N, V>;
     constexpr int T = VC::T;
     constexpr int W = VC::W;
     constexpr int E = VC::E;
-    using Lay = ColLay<N, W>;
     using PL = typename VC::PL;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    C* lds = reinterpret_cast<C*>(smem_raw);
-    __shared__ C tw[N];
+    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH);
+    R* kt = reinterpret_cast<R*>(tw + N);
 
     const int tid = threadIdx.x;
     const int xl = tid % W;
     const int t = tid / W;
     const int q = blockIdx.y;                       // output component
     const int src = AXIS == 1 ? 3 - q : (q ^ 2);    // the component alpha^j takes
-    // (the persistent loop only for the y pass: the z pass's partial sums would
-    // double the registers a prefetch holds)
-    constexpr bool PIPE = VC::PIPE && !ACCUM;
-    if constexpr (!PIPE) {
-        // one tile = W adjacent columns of one solve at one fixed other-axis index
-        const int2 it = a.items[blockIdx.x];
-        const SolveDev* __restrict__ S = a.solves + it.x;
-        const int n0 = S->n[0], n1 = S->n[1];
-        const int ntx = (n0 + W - 1) / W;
-        const int other = it.y / ntx;
-        const int x = (it.y % ntx) * W + xl;
-        const bool act = x < n0;
-        const long long stride = AXIS == 1 ? (long long)n0 : (long long)n0 * n1;
-        const long long obase = AXIS == 1 ? (long long)other * n0 * n1 : (long long)other * n0;
-        const long long base = obase + (act ? x : 0) + (long long)t * stride;
-        const long long ns = S->nsites;
-        gptr<const nv2<R>> ctab = cview<R>(a.ctab);
-        for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S->tw[AXIS] + i);
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const int solve = (int)(unsigned)item, ty = (int)(item >> 32);
+    const sptr<SolveDev> S = uni(a.solves + solve);
+    const int n0 = S->n[0], n1 = S->n[1];
+    const int ntx = (n0 + W - 1) / W;
+    const long long ns = S->nsites;
+    const unsigned stride = AXIS == 1 ? (unsigned)n0 : (unsigned)n0 * (unsigned)n1;
+    // One tile = W adjacent columns of one solve at one fixed other-axis index;
+    // thread (t, x) holds points t + T m of column x, at a 32-bit offset from
+    // uniform addresses.
+    const int other = __builtin_amdgcn_readfirstlane(ty / ntx), x0 = (ty - other * ntx) * W;
+    const bool act = x0 + xl < n0;
+    const long long base = x0 + (AXIS == 1 ? (long long)other * n0 * n1 : (long long)other * n0);
+    const unsigned off = (unsigned)(t * stride + (act ? xl : 0)) * (unsigned)sizeof(C);
+    gptr<const char> ps = (gptr<const char>)(cview<R>(S->buf[a.src]) + (base + src * ns));
+    gptr<const char> pd = (gptr<const char>)(cview<R>(S->buf[a.dst]) + (base + q * ns));
+    const long long step = (long long)T * stride * (long long)sizeof(C);   // from a thread's point to its next
 
-        C v[1][E];
-        C g[E];
-        {
-            gptr<const nv2<R>> p = cview<R>(S->buf[a.src]) + base + src * ns;
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
+    gptr<const R> rtab = glob(reinterpret_cast<const R*>(a.rtab));
+    for (int i = tid; i < N; i += VC::THREADS) {
+        tw[i] = gload<C>(ctab, S->tw[AXIS] + i);
+        if constexpr (sizeof(R) == 4) kt[i] = rtab[S->kt[AXIS] + i];
+    }
+    C v[E], g[E];
 #pragma unroll
-            for (int m = 0; m < E; ++m) v[0][m] = gload_nt<C>(p, (long long)(T * m) * stride);
-            if constexpr (ACCUM) {
-                // the partial sum of the earlier axis, loaded ahead of the transforms
-                gptr<const nv2<R>> pg = cview<R>(S->buf[a.dst]) + base + q * ns;
+    for (int m = 0; m < E; ++m) v[m] = gload_at<C>(scalar_base(ps + m * step), off);
+    if constexpr (ACCUM && !VC::LATE) {
 #pragma unroll
-                for (int m = 0; m < E; ++m) g[m] = gload_nt<C>(pg, (long long)(T * m) * stride);
-            }
-        }
-        fft_line<C, N, T, -1, 1, 1, Lay, PL>(v, lds, t, xl, tw);
-        const double kscale = S->dk[AXIS] / (double)N;
+        for (int m = 0; m < E; ++m) g[m] = gload_at<C>(scalar_base(pd + m * step), off);
+    }
+    if constexpr (T * W <= 64) __syncthreads();   // the tables (else the first exchange's barriers come before their use)
+    unsigned char* col = smem_raw + xl * VC::XB;
+    fft_col<C, N, -1, W, VC::SPLIT, PL>(v, col, t, tw);
+    const double kscale = S->dk[AXIS] / (double)N, td = (double)t;
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const C w = cscale(v[0][m], (R)(kscale * kindex(t + T * m, N)));
-            v[0][m] = AXIS == 1 ? alpha2_phase(q, w) : alpha3_phase(q, w);
-        }
-        fft_line<C, N, T, +1, 1, 1, Lay, PL>(v, lds, t, xl, tw);
-        if (act) {
-            gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + base + q * ns;
+    for (int m = 0; m < E; ++m) {
+        // k / n (numpy order; E is even, so the sign of k follows from m)
+        C w;
+        if constexpr (sizeof(R) == 4) w = cscale(v[m], kt[t + T * m]);
+        else w = cscale(v[m], (R)(kscale * (td + (double)(T * m - (m < E / 2 ? 0 : N)))));
+        v[m] = AXIS == 1 ? alpha2_phase(q, w) : alpha3_phase(q, w);
+    }
+    fft_col<C, N, +1, W, VC::SPLIT, PL>(v, col, t, tw);
+    if constexpr (ACCUM && VC::LATE) {
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const C o = ACCUM ? cadd(g[m], v[0][m]) : v[0][m];
-                gstore_nt<C>(p, (long long)(T * m) * stride, o);
-            }
-        }
-    } else {
-        // Every solve of a launch has the same lengths (so the same twiddles); a
-        // tile's own descriptor words (its item and its solve's arrays) are read
-        // through the constant address space, as scalar loads, which do not wait
-        // for the previous tile's stores still in flight.
-        const SolveDev* S0 = a.solves + a.items[blockIdx.x].x;
-        const int n0 = S0->n[0], n1 = S0->n[1];
-        const int ntx = (n0 + W - 1) / W;
-        const long long ns = S0->nsites;
-        const long long stride = AXIS == 1 ? (long long)n0 : (long long)n0 * n1;
-        const double kscale = S0->dk[AXIS] / (double)N;
-        gptr<const nv2<R>> ctab = cview<R>(a.ctab);
-        for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S0->tw[AXIS] + i);
-        using cword = const unsigned long long __attribute__((address_space(4)))*;
-        struct Tile {
-            unsigned long long src, dst;   // the solve's stage input and G arrays
-            long long base;
-            bool act;
-        };
-        auto tile = [&](int item) {
-            const unsigned long long w = *(cword)(a.items + item);
-            const int solve = (int)(unsigned)w, ty = (int)(w >> 32);
-            const int other = ty / ntx;
-            const int x = (ty % ntx) * W + xl;
-            Tile u;
-            // (no partial persistent tiles: their stores need no branch)
-            u.act = PIPE || x < n0;
-            const long long obase = AXIS == 1 ? (long long)other * n0 * n1 : (long long)other * n0;
-            u.base = obase + (u.act ? x : 0) + (long long)t * stride;
-            const SolveDev* S = a.solves + solve;
-            u.src = *(cword)(&S->buf[a.src]);
-            u.dst = *(cword)(&S->buf[a.dst]);
-            return u;
-        };
-        auto load = [&](const Tile& u, C (&v)[E], C (&g)[E]) {
-            gptr<const nv2<R>> p = cview<R>((const void*)u.src) + u.base + src * ns;
-    #pragma unroll
-            for (int m = 0; m < E; ++m) v[m] = gload_nt<C>(p, (long long)(T * m) * stride);
-            if constexpr (ACCUM) {
-                // the partial sum of the earlier axis, loaded ahead of the transforms
-                gptr<const nv2<R>> pg = cview<R>((const void*)u.dst) + u.base + q * ns;
-    #pragma unroll
-                for (int m = 0; m < E; ++m) g[m] = gload_nt<C>(pg, (long long)(T * m) * stride);
-            }
-        };
-
-        // Order of a persistent iteration: issue the next tile's loads, transform
-        // this tile, store it, then take the next tile's values (waiting for its
-        // loads but not for the stores just issued).  The first tile's loads are
-        // waited for before the loop, so that at the loop's top only stores are
-        // in flight and nothing there waits for them.
-        int item = blockIdx.x;
-        Tile u = tile(item);
-        C v[1][E], g[E];
-        load(u, v[0], g);
-        if constexpr (PIPE) {
-    #pragma unroll
-            for (int m = 0; m < E; ++m) asm volatile("" ::"v"(v[0][m].x), "v"(v[0][m].y));
-        }
-        for (;;) {
-            const int next = item + (int)gridDim.x;
-            const bool more = PIPE && next < a.nitems;
-            Tile un;
-            C vn[E], gn[E];
-            if (more) {
-                un = tile(next);
-                load(un, vn, gn);
-            }
-            fft_line<C, N, T, -1, 1, 1, Lay, PL>(v, lds, t, xl, tw);
-    #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const C w = cscale(v[0][m], (R)(kscale * kindex(t + T * m, N)));
-                v[0][m] = AXIS == 1 ? alpha2_phase(q, w) : alpha3_phase(q, w);
-            }
-            fft_line<C, N, T, +1, 1, 1, Lay, PL>(v, lds, t, xl, tw);
-            if (u.act) {
-                gptr<nv2<R>> p = wview<R>((void*)u.dst) + u.base + q * ns;
-    #pragma unroll
-                for (int m = 0; m < E; ++m) {
-                    const C o = ACCUM ? cadd(g[m], v[0][m]) : v[0][m];
-                    gstore_nt<C>(p, (long long)(T * m) * stride, o);
-                }
-            }
-            if (!more) break;
-            item = next;
-            u = un;
-    #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                v[0][m] = vn[m];
-                g[m] = gn[m];
-            }
-        }
+        for (int m = 0; m < E; ++m) g[m] = gload_at<C>(scalar_base(pd + m * step), off);
+    }
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) gstore_at((gptr<char>)scalar_base(pd + m * step), off, ACCUM ? cadd(g[m], v[m]) : v[m]);
     }
 }
 
@@ -645,7 +601,7 @@ __global__ void __launch_bounds__((CdVar<R, N, V>::THREADS)) col_d_kernel(PassAr
 // same stages took 0.99 / 0.67 ms and 9.1 ms, 9 x 1024^2 in double 0.82 ms
 // (now 0.59) and 192 x 192 x 256 x 4 in double 3.7 ms (now 2.2).
 template <class R, int N> struct RdVar {
-    using PL = FftPlan<N>;
+    using PL = StepPlan<N>;
     static constexpr int T = PL::T;
     static constexpr int E = N / T;
     static constexpr int LT = 4 * T;          // threads of a grid line
@@ -660,29 +616,10 @@ template <class R, int N> struct RdVar {
     // waves per SIMD the compiler is asked to fit: what the LDS of a compute
     // unit allows, and what the points and a prefetched site leave registers for
     static constexpr int BLOCKS_PER_CU = (int)(163840 / BYTES);
-    static constexpr int WAVES = imax(1, imin(sizeof(R) == 4 ? (E >= 20 ? 3 : 4) : (E >= 20 ? 2 : 3), BLOCKS_PER_CU * imax(1, THREADS / 64) / 4));
+    static constexpr int WAVES = imax(1, imin(sizeof(R) == 4 ? (E >= 20 ? 3 : 4) : (E >= 16 ? 2 : 3), BLOCKS_PER_CU * imax(1, THREADS / 64) / 4));
     static_assert(plan_ok<N, T, PL>(), "row derivative pass violates the FFT plan constraints");
     static_assert(64 % T == 0 && E % 4 == 0, "a component line within one wave, whole sites per thread");
 };
-
-// Values that are the same for a whole workgroup are read through the constant
-// address space, as scalar loads.
-template <class T> using sptr = const T __attribute__((address_space(4)))*;
-template <class T> __device__ __forceinline__ sptr<T> uni(const T* p) { return (sptr<T>)p; }
-
-// A complex number at a uniform base plus a byte offset of 32 bits.
-template <class C> __device__ __forceinline__ C gload_at(gptr<const char> base, unsigned off) {
-    using V2 = nv2<decltype(C::x)>;
-    const V2 v = __builtin_nontemporal_load((gptr<const V2>)(base + off));
-    return cmake<C>(v.x, v.y);
-}
-template <class C> __device__ __forceinline__ void gstore_at(gptr<char> base, unsigned off, C c) {
-    using V2 = nv2<decltype(C::x)>;
-    V2 v;
-    v.x = c.x;
-    v.y = c.y;
-    __builtin_nontemporal_store(v, (gptr<V2>)(base + off));
-}
 
 // (V: the tile variant, of which this pass has one; profiles name the kernel by it)
 template <class R, int N, int V, int STAGE>
@@ -735,7 +672,7 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
     __syncthreads();
     R* xl = reinterpret_cast<R*>(smem_raw) + 4 * line * VC::STRIDE;   // this line's exchange buffer
     R* xch = xl + q * VC::STRIDE;                                     // this component's part of it
-    fft_line_wave<C, N, T, 0, -1, true, PL>(v, xch, t, tw);
+    fft_row<C, N, -1, true, PL>(v, xch, t, tw);
     // k_x / n_0 (numpy order; E is even, so the sign of k follows from m)
     if constexpr (sizeof(R) == 4) {
 #pragma unroll
@@ -780,7 +717,7 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
         }
     };
 
-    fft_line_wave<C, N, T, 0, +1, true, PL>(v, xch, t, tw);
+    fft_row<C, N, +1, true, PL>(v, xch, t, tw);
 
     Ops ops[2];
     load(ops[0], 0);
@@ -1089,10 +1026,9 @@ __global__ void __launch_bounds__((LineVar<R, N, WIDE>::T)) line_kernel(PassArgs
 
 // Kernel table of one (precision, N) instantiation.
 struct RowVariant { const void* stage[4]; const void* dp5[6]; int threads, rows; size_t lds; };   // RK4 / Dormand-Prince stages
-struct CdVariant { const void* fn[2][2]; int threads, w; size_t lds; int pipe; };   // [axis - 1][accumulate]; pipe: persistent y pass
+struct CdVariant { const void* fn[2]; int threads, w; size_t lds; };   // [axis - 1]: y writes G, z adds to it
 struct ColVariant { const void* fn[2][3]; int threads, w; size_t lds; };
 struct SizeKernels {
-    int nvar;                      // tile variants of the stepping column passes
     RowVariant row;                // the stage row pass
     CdVariant cd[NVAR];            // the stepping column passes, by variant
     const void* row_other[ROW_NMODES];  // whole-state row modes
@@ -1119,14 +1055,11 @@ template <class R, int N, int V>
 CdVariant make_cd_variant() {
     using VC = CdVar<R, N, V>;
     CdVariant c;
-    c.fn[0][0] = (const void*)col_d_kernel<R, N, V, 1, 0>;
-    c.fn[0][1] = (const void*)col_d_kernel<R, N, V, 1, 1>;
-    c.fn[1][0] = (const void*)col_d_kernel<R, N, V, 2, 0>;
-    c.fn[1][1] = (const void*)col_d_kernel<R, N, V, 2, 1>;
+    c.fn[0] = (const void*)col_d_kernel<R, N, V, 1, 0>;
+    c.fn[1] = (const void*)col_d_kernel<R, N, V, 2, 1>;
     c.threads = VC::THREADS;
     c.w = VC::W;
     c.lds = VC::BYTES;
-    c.pipe = VC::PIPE ? 1 : 0;
     return c;
 }
 template <class R, int N, int V>
@@ -1148,18 +1081,12 @@ ColVariant make_col_variant() {
 template <class R, int N>
 SizeKernels make_size_kernels() {
     SizeKernels k;
-    k.nvar = nvar<N>();
     k.row = make_row_variant<R, N>();
     k.cd[0] = make_cd_variant<R, N, 0>();
-    if constexpr (nvar<N>() > 1) {
-        k.cd[1] = make_cd_variant<R, N, 1>();
-        k.cd[2] = make_cd_variant<R, N, 2>();
-        k.cd[3] = make_cd_variant<R, N, 3>();
-    } else {
-        for (int v = 1; v < NVAR; ++v) k.cd[v] = k.cd[0];
-    }
+    k.cd[1] = make_cd_variant<R, N, 1>();
+    k.cd[2] = make_cd_variant<R, N, 2>();
     // whole-state column transforms: the few-points plan where there is one
-    k.col = make_col_variant<R, N, (nvar<N>() > 1 && has_small_plan<N>()) ? 2 : 0>();
+    k.col = make_col_variant<R, N, (N >= 256 && has_small_plan<N>()) ? 2 : 0>();
     k.row_other[ROW_FWD] = (const void*)row_kernel<R, N, 0, ROW_FWD, 0>;
     k.row_other[ROW_STAGE] = nullptr;
     k.row_other[ROW_INV] = (const void*)row_kernel<R, N, 0, ROW_INV, 0>;
