@@ -127,16 +127,17 @@ typedef struct {
                                (0 = all solves of a grid size).  Without BW vertices a
                                time step then runs all passes of one chunk before the
                                next, so a chunk's arrays can stay in the on-die cache  */
-    int force_variant;      /* > 0: use tile variant force_variant - 1 (0..3) for every pass
-                               (testing); 0: the autotuned or the default variant       */
-    int persistent;         /* 1: when every grid is one-dimensional with a power-of-two
-                               length 64..1024, the field's profile tables fit in LDS
-                               next to the state (FP64, 1024 points: up to 4 terms) and
-                               there are no BW vertices, each swf_step call runs all its
-                               time steps in one kernel per launch group (at most 1024
-                               steps per launch), one workgroup per solve, with the state
-                               held on chip; otherwise, and with 0, one launch per pass
-                               and RK4 stage                                            */
+    int force_variant;      /* > 0: use tile variant force_variant - 1 for every column pass
+                               (the widest for more; testing); 0: the autotuned or the
+                               default variant       */
+    int persistent;         /* 1: when every grid is one-dimensional, the profiles of the
+                               field's terms beyond the fourth fit in LDS next to the
+                               state (FP64, 1024 points: up to 4 terms) and there are no
+                               BW vertices, each swf_step call runs all its time steps in
+                               one kernel per launch group (at most 1024 steps per
+                               launch), one workgroup per solve, with the state held on
+                               chip; otherwise, and with 0, one launch per pass and RK4
+                               stage                                                    */
     int bw_partial;         /* 1: also integrate every BW vertex by the partial-integration
                                route of the paper's BW section (eq. (MScatScat2) and its
                                (back,scat), (scat,back) partners), read back with

@@ -39,7 +39,6 @@ thread_local std::string g_init_error;
 constexpr int RED_BLOCKS = 512;          // blocks of every reduction launch (fixed: deterministic sums)
 constexpr int BW_BLOCKS = 1024;          // most blocks per vertex of the BW stage reduction
 constexpr int BW2_BLOCKS = 256;          // blocks per vertex of the partial-integration route's reductions
-constexpr size_t LINE_STATIC_LDS = 1024;  // bound on the line kernel's static LDS
 constexpr int NKIND = 6;                 // kernel-stats kinds (swf_kernel_stats)
 constexpr int PROF_POOL = 2048;          // event pairs kept in flight when profiling
 
@@ -438,6 +437,22 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         twoff.push_back({n, o});
         return o;
     };
+    // the same in the order a stepping pass reads them: per step after the first, output k and r
+    std::map<std::pair<int, int>, size_t> twpoff;   // (length, row plan or column plan)
+    auto twp_for = [&](int n, int col) -> size_t {
+        auto it = twpoff.find({n, col});
+        if (it != twpoff.end()) return it->second;
+        const swf::SizeKernels* k = swf::size_kernels(P.fp64, n);
+        const swf::StepRadices& pl = col ? k->col_plan : k->row_plan;
+        const size_t nat = tw_for(n);
+        std::vector<cd> tw;
+        int ns = pl.r[0];
+        for (int j = 1; j < pl.n; ns *= pl.r[j++])
+            for (int q = 1; q < pl.r[j]; ++q)
+                for (int r = 0; r < ns; ++r) tw.push_back(P.ctab[nat + (size_t)r * q * (n / (ns * pl.r[j]))]);
+        tw.resize(n);
+        return twpoff[{n, col}] = add_c(tw);
+    };
     // derivative factors k / n of an axis, transform order (the Nyquist mode negative)
     std::map<std::pair<int, double>, size_t> ktoff;
     auto kt_for = [&](int n, double dk) -> size_t {
@@ -522,6 +537,7 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         }
         for (int j = 0; j < 3; ++j) {
             d.tw[j] = (long long)tw_for(G.n[j] > 1 ? G.n[j] : G.n[0]);
+            d.twp[j] = j < G.dim ? (long long)twp_for(G.n[j], j > 0) : 0;
             d.kt[j] = j < G.dim ? (long long)kt_for(G.n[j], d.dk[j]) : 0;
         }
         P.hs.push_back(d);
@@ -1263,10 +1279,10 @@ static int enqueue_step(swf_ctx* ctx) {
     return SWF_OK;
 }
 
-// One-dimensional whole-loop path: every group is a 1D grid with a line
-// kernel and no vertex couples two solves.
-static size_t line_lds(const swf_ctx* ctx, const Group& g, int nterm_max, int wide) {
-    return g.k[0]->line_lds[wide] + (size_t)nterm_max * ctx->P.grids[g.grid].n[0] * ctx->P.rsize;
+// Dynamic LDS of the line kernel of a group: its buffers, and the profiles of
+// the field terms it does not keep in registers.
+static size_t line_lds(const Group& g, const Plan& P, int nterm_max) {
+    return g.k[0]->line_lds + (size_t)std::max(0, nterm_max - swf::LINE_TERMS) * P.grids[g.grid].n[0] * P.rsize;
 }
 
 static int max_terms(const swf_ctx* ctx, const Group& g) {
@@ -1275,23 +1291,12 @@ static int max_terms(const swf_ctx* ctx, const Group& g) {
     return m;
 }
 
-// The line kernel build a group runs: 1 wide exchange rounds, 0 narrow, -1
-// none fits the LDS of one workgroup.
-static int line_build(const swf_ctx* ctx, const Group& g) {
-    if (ctx->P.grids[g.grid].dim != 1 || !g.k[0]->line[0]) return -1;
-    const int nt = max_terms(ctx, g);
-    for (int w = 1; w >= 0; --w)
-        if (line_lds(ctx, g, nt, w) + LINE_STATIC_LDS <= ctx->lds_max) return w;
-    return -1;
-}
-
-// One-dimensional whole-loop path: every group is a 1D grid with a line
-// kernel whose LDS (with the group's field terms) fits, and no vertex couples
-// two solves.
+// One-dimensional whole-loop path: every group is a 1D grid whose line kernel
+// fits the LDS with the group's field terms, and no vertex couples two solves.
 static bool line_path(swf_ctx* ctx) {
     if (!ctx->opt.persistent || !ctx->P.hv.empty() || ctx->P.dp5 || ctx->P.ip) return false;
     for (const auto& g : groups(ctx))
-        if (line_build(ctx, g) < 0) return false;
+        if (ctx->P.grids[g.grid].dim != 1 || line_lds(g, ctx->P, max_terms(ctx, g)) > ctx->lds_max) return false;
     return true;
 }
 
@@ -1305,9 +1310,8 @@ static int line_steps(swf_ctx* ctx, int n) {
             swf::PassArgs a = pass_args(ctx);
             a.nsteps = c;
             const double bytes = 2.0 * 4.0 * ctx->P.csize * group_sites(ctx, g);
-            const int w = line_build(ctx, g);
-            int r = launch(ctx, g.k[0]->line[w], g.n_line, g.it_line, g.k[0]->line_threads,
-                           line_lds(ctx, g, max_terms(ctx, g), w), a, 5, bytes);
+            int r = launch(ctx, g.k[0]->line, g.n_line, g.it_line, g.k[0]->line_threads,
+                           line_lds(g, ctx->P, max_terms(ctx, g)), a, 5, bytes);
             if (r) return r;
         }
         HIPCHK(swf::launch_advance(ctx->d_step(), c, ctx->st));
@@ -1940,11 +1944,9 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
                 for (int a = 0; a < 2; ++a)
                     for (int m = 0; m < 3; ++m)
                         INITCHK(hipFuncSetAttribute(k->col.fn[a][m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->col.lds));
-                if (k->line[0] && ax == 0)
-                    for (int w = 0; w < 2; ++w)
-                        INITCHK(hipFuncSetAttribute(k->line[w], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)std::min(ctx->lds_max - LINE_STATIC_LDS,
-                                                                  line_lds(ctx, g, swf::MAX_TERMS, w))));
+                if (ax == 0)
+                    INITCHK(hipFuncSetAttribute(k->line, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)std::min(ctx->lds_max, line_lds(g, P, swf::MAX_TERMS))));
                 for (int st = 0; st < 4; ++st)
                     INITCHK(hipFuncSetAttribute(k->row.stage[st], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row.lds));
                 for (int st = 0; st < 6; ++st)

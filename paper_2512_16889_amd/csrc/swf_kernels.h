@@ -536,7 +536,7 @@ __attribute__((amdgpu_waves_per_eu(CdVar<R, N, V>::template waves<ACCUM>(), 8)))
     gptr<const nv2<R>> ctab = cview<R>(a.ctab);
     gptr<const R> rtab = glob(reinterpret_cast<const R*>(a.rtab));
     for (int i = tid; i < N; i += VC::THREADS) {
-        tw[i] = gload<C>(ctab, S->tw[AXIS] + i);
+        tw[i] = gload<C>(ctab, S->twp[AXIS] + i);
         if constexpr (sizeof(R) == 4) kt[i] = rtab[S->kt[AXIS] + i];
     }
     C v[E], g[E];
@@ -659,7 +659,7 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
     constexpr bool FIRST = STAGE == 0 || STAGE == 4, LAST = STAGE == 3 || STAGE == 9;
     gptr<const nv2<R>> pin = cview<R>(S->buf[FIRST ? BUF_Y : BUF_YS]) + tile0;
     for (int i = tid; i < N; i += VC::THREADS) {
-        tw[i] = gload<C>(ctab, S->tw[0] + i);
+        tw[i] = gload<C>(ctab, S->twp[0] + i);
         if constexpr (sizeof(R) == 4) kt[i] = rtab[S->kt[0] + i];
     }
     // the component alpha^1 takes (read again, as whole sites, by the epilogue)
@@ -830,215 +830,290 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
 // ------------------------------------------------------------------ 1D whole-loop kernel
 // A (1+1)D solve is one line of at most 1024 points: its whole state fits on
 // one compute unit.  line_kernel runs a.nsteps complete RK4 steps of one solve
-// per workgroup without leaving the chip: the state y and the stage input stay
-// in registers, the running RK4 sum in thread-private LDS slots, and each stage
-// transforms the line forward, multiplies by -i H0(k)/N and transforms back
-// through LDS.  Only the final state is written to the Y array.  The update is
-// the classical y_{n+1} = y + h/6 (k1 + 2 k2 + 2 k3 + k4) with h = -dt,
-// accumulated stage by stage.  Field profiles, background phases, the absorber
-// mask and the twiddles are staged in LDS once per launch; the per-stage time
-// factors are evaluated in double by a few lanes and broadcast through LDS.
-// WIDE: the exchange rounds move CGW components at once (fewer barriers, more
-// LDS); otherwise half as many.  The host takes the wide build where its LDS,
-// with the field's profile tables, fits.
-template <class R, int N, bool WIDE> struct LineVar {
-    using PL = Plan4<N>;
+// per workgroup without leaving the chip.  4T threads, as in the row pass: a
+// group of T transforms one component (E = N/T points each, within one wave, so
+// without a barrier), and every thread finishes whole sites t + T (q + 4 j),
+// whose state, stage input and RK4 sum it keeps in registers, with the
+// background phase, the absorber mask and the profiles of the first
+// LINE_TERMS field terms (further terms' profiles are staged in LDS).  A stage
+// costs two workgroup barriers: the stage inputs go through LDS to the component
+// groups, the derivatives back to the sites.  The update is the classical
+// y_{n+1} = y + h/6 (k1 + 2 k2 + 2 k3 + k4) with h = -dt, accumulated stage by
+// stage.  The time factors of LINE_BLOCK steps are evaluated at once, in double,
+// one per thread, and kept in LDS.  Only the final state is written to the Y array.
+//
+// What bounds it: one workgroup's latency, LDS first (1024 points in double:
+// about 270 16-byte accesses a thread and stage, 8 cycles each for every one of
+// four waves, against 1500 vector instructions of 4 cycles).  In double, 1024
+// points take 33 us a step and 512 points 16.6 us (47 and 34 us with all four
+// components in each thread, radix 4 and a barrier per exchange and component
+// pair); 1024 points over eight waves, whose exchanges then need barriers, 37 us.
+constexpr int LINE_TERMS = 4;    // field terms whose profiles a thread keeps in registers
+constexpr int LINE_BLOCK = 16;   // steps whose time factors are formed together
+template <class R, int N> struct LineVar {
+    using PL = StepPlan<N>;
     static constexpr int T = PL::T;
     static constexpr int E = N / T;
-    using Lay = RowLay<N, 1>;
-    static constexpr int CGW = sizeof(R) == 8 ? 2 : 4;
-    static constexpr int CG = WIDE ? CGW : CGW / 2;
-    static constexpr size_t XCH = CG * (size_t)Lay::STRIDE * sizeof(cpx<R>);
-    // dynamic LDS without the field profiles: exchange, twiddles, phases,
-    // RK4 sum, mask (the host adds nterm * N reals)
-    static constexpr size_t BASE_BYTES = XCH + 2 * N * sizeof(cpx<R>) + 4 * N * sizeof(cpx<R>) + N * sizeof(R);
-    static_assert(PL::NR >= 2, "the stage broadcast relies on the barriers of the exchanges");
-    static_assert(plan_ok<N, T, PL>(), "line plan violates the FFT plan constraints");
+    static constexpr int THREADS = 4 * T;
+    static constexpr int SITES = E / 4;
+    static constexpr bool WLINE = THREADS <= 64;
+    static constexpr int STRIDE = xch_stride<N, PL, sizeof(cpx<R>)>();   // points of a component line
+    static constexpr size_t XCH = (size_t)4 * STRIDE * sizeof(cpx<R>);
+    static constexpr size_t IN = (size_t)4 * N * sizeof(cpx<R>);
+    // dynamic LDS without profiles: exchange, stage input, twiddles, derivative
+    // factors (single precision), time factors (the host adds N reals per term
+    // beyond LINE_TERMS)
+    static constexpr size_t BASE_BYTES = XCH + IN + N * sizeof(cpx<R>) + (sizeof(R) == 4 ? N * sizeof(R) : 0) +
+                                         LINE_BLOCK * 3 * sizeof(StageConst<R>);
+    static_assert(plan_ok<N, T, PL>() && E % 4 == 0, "whole sites per thread");
 };
 
-// A zero the compiler cannot see through.  Offsetting the lane index with it
-// once per transform keeps the (loop-invariant) exchange addresses from being
-// hoisted out of the time loop into registers.
+// A zero the compiler cannot see through.
 __device__ __forceinline__ int opaque_zero() {
     int z = 0;
     asm volatile("" : "+s"(z));
     return z;
 }
 
-template <class R, int N, bool WIDE>
-__global__ void __launch_bounds__((LineVar<R, N, WIDE>::T)) line_kernel(PassArgs a) {
+template <class R, int N>
+__global__ void __launch_bounds__((LineVar<R, N>::THREADS)) line_kernel(PassArgs a) {
     using C = cpx<R>;
-    using VC = LineVar<R, N, WIDE>;
+    using VC = LineVar<R, N>;
     constexpr int T = VC::T;
     constexpr int E = VC::E;
-    constexpr int CG = VC::CG;
-    using Lay = typename VC::Lay;
+    constexpr int SITES = VC::SITES;
+    constexpr int STRIDE = VC::STRIDE;
     using PL = typename VC::PL;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* xch = reinterpret_cast<C*>(smem_raw);
-    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH);
-    C* phx = tw + N;                               // exp(i K.x) on the line (trivial axes folded in)
-    C* accl = phx + N;                             // RK4 sum, [q][m][lane]
-    R* msk = reinterpret_cast<R*>(accl + 4 * N);   // absorber mask (1 if off)
-    R* fx = msk + N;                               // spatial profile of each field term
-    __shared__ R sh_coef[2][MAX_TERMS];            // amp * f_t(t) per term, double-buffered by stage
-    __shared__ C sh_wc[2][4];                      // background spinor * exp(-i E t)
-    __shared__ int sh_mu[MAX_TERMS];
+    C* yin = reinterpret_cast<C*>(smem_raw + VC::XCH);
+    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH + VC::IN);
+    StageConst<R>* tc = reinterpret_cast<StageConst<R>*>(tw + N);   // [step of the block][node 0, 1/2, 1]
+    R* kt = reinterpret_cast<R*>(tc + LINE_BLOCK * 3);
+    R* fxl = kt + (sizeof(R) == 4 ? N : 0);                         // profiles of the terms beyond LINE_TERMS
 
-    const int t = threadIdx.x;
-    const SolveDev* __restrict__ S = a.solves + a.items[blockIdx.x].x;
+    const int tid = threadIdx.x;
+    const int t = tid % T;
+    const int q = T == 64 ? __builtin_amdgcn_readfirstlane(tid / T) : tid / T;
+    const int solve = (int)*(sptr<unsigned>)(a.items + blockIdx.x);
+    const sptr<SolveDev> S = uni(a.solves + solve);
     gptr<const nv2<R>> ctab = cview<R>(a.ctab);
     gptr<const R> rtab = glob(reinterpret_cast<const R*>(a.rtab));
-    const int nterm = S->nterm;
+    const int nterm = S->nterm, mus = S->mus;
+    const long long mk = S->mask;
+    for (int i = tid; i < N; i += VC::THREADS) {
+        tw[i] = gload<C>(ctab, S->twp[0] + i);
+        if constexpr (sizeof(R) == 4) kt[i] = rtab[S->kt[0] + i];
+    }
+    const int site0 = t + T * q;
+    // trivial axes (index 0 of each): constant factors of the tables
+    C ph[SITES];
+    R msk[SITES], fx0[SITES], fx1[SITES], fx2[SITES], fx3[SITES];
+    int mu0, mu1, mu2, mu3;
+    static_assert(LINE_TERMS == 4, "fx0 .. fx3");
     {
-        // trivial axes (index 0 of each): constant factors of the tables
         const C phyz = cmul(gload<C>(ctab, S->ph + N), gload<C>(ctab, S->ph + N + 1));
-        const long long mk = S->mask;
         const R myz = mk >= 0 ? rtab[mk + N] * rtab[mk + N + 1] : (R)1;
-        for (int i = t; i < N; i += T) {
-            tw[i] = gload<C>(ctab, S->tw[0] + i);
-            phx[i] = cmul(gload<C>(ctab, S->ph + i), phyz);
-            msk[i] = mk >= 0 ? rtab[mk + i] * myz : (R)1;
-        }
-        for (int j = 0; j < nterm; ++j) {
-            const long long tb = a.terms[S->term0 + j].tab;
-            const R fyz = rtab[tb + N] * rtab[tb + N + 1];
-            for (int i = t; i < N; i += T) fx[j * N + i] = rtab[tb + i] * fyz;
-        }
-        if (t < nterm) sh_mu[t] = a.terms[S->term0 + t].mu;
-    }
-    C y[4][E];
-    {
-        gptr<const nv2<R>> p = cview<R>(S->buf[BUF_Y]) + t;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int j = 0; j < SITES; ++j) {
+            const int i = site0 + 4 * T * j;
+            ph[j] = cmul(gload<C>(ctab, S->ph + i), phyz);
+            msk[j] = mk >= 0 ? rtab[mk + i] * myz : (R)1;
+        }
+        auto term = [&](int k, int& m, R (&f)[SITES]) {
+            m = -1;
 #pragma unroll
-            for (int m = 0; m < E; ++m) y[q][m] = gload<C>(p, q * (long long)N + T * m);
+            for (int j = 0; j < SITES; ++j) f[j] = (R)0;
+            if (k < nterm) {
+                const sptr<TermDev> tm = uni(a.terms + S->term0 + k);
+                gptr<const R> tab = rtab + tm->tab;
+                const R fyz = tab[N] * tab[N + 1];
+                m = tm->mu;
+#pragma unroll
+                for (int j = 0; j < SITES; ++j) f[j] = tab[site0 + 4 * T * j] * fyz;
+            }
+        };
+        // (written out: a loop over them is unrolled too late for registers)
+        term(0, mu0, fx0);
+        term(1, mu1, fx1);
+        term(2, mu2, fx2);
+        term(3, mu3, fx3);
+        for (int k = LINE_TERMS; k < nterm; ++k) {
+            gptr<const R> tab = rtab + uni(a.terms + S->term0 + k)->tab;
+            const R fyz = tab[N] * tab[N + 1];
+            for (int i = tid; i < N; i += VC::THREADS) fxl[(k - LINE_TERMS) * N + i] = tab[i] * fyz;
+        }
     }
-    __syncthreads();
+    gptr<nv2<R>> py = wview<R>(S->buf[BUF_Y]) + site0;
+    C y[SITES][4];
+#pragma unroll
+    for (int j = 0; j < SITES; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[j][c] = gload<C>((gptr<const nv2<R>>)py, c * (long long)N + 4 * T * j);
 
-    const R Ky = (R)S->kap[1], Kz = (R)S->kap[2], inv_n = (R)S->inv_n;
-    const double dk = S->dk[0];
+    const R Ky = (R)S->kap[1], Kz = (R)S->kap[2];
+    const double kscale = S->dk[0] / (double)N;
     const double dt = a.dt;
     const R h = (R)(-dt), h2 = (R)(-0.5 * dt), h3 = (R)(-dt / 3.0), h6 = (R)(-dt / 6.0);
-    const int n_first = *a.step;
+    const int n_first = *a.step + a.step_add;
+    C* xq = xch + q * STRIDE;
 
-    // v = IFFT[-i H0 FFT(yi)]/N - i V(ts) (yi + psi_b(ts)); par selects the
-    // broadcast buffer of this stage
-    auto rhs = [&](const C (&yi)[4][E], C (&v)[4][E], double ts, int par) {
-        for (int j = t; j < nterm; j += T) {
-            const TermDev tm = a.terms[S->term0 + j];
-            sh_coef[par][j] = (R)(tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts));
-        }
-        if (t >= T - 4) {
-            const int q = t - (T - 4);
-            double sn, cs;
-            sincos(-S->E * ts, &sn, &cs);
-            const double wr = S->w[2 * q], wi = S->w[2 * q + 1];
-            sh_wc[par][q] = cmake<C>((R)(wr * cs - wi * sn), (R)(wr * sn + wi * cs));
-        }
+    // k = -i [alpha^1 D_x y + beta y + kappa terms + (A_0 + alpha^j A_j)(y + psi_b)] at the thread's
+    // sites; tcs: the stage's time factors
+    auto rhs = [&](const C (&yst)[SITES][4], C (&k)[SITES][4], const StageConst<R>* tcs) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int j = 0; j < SITES; ++j)
 #pragma unroll
-            for (int m = 0; m < E; ++m) v[q][m] = yi[q][m];
-        // the exchanges' barriers also publish sh_coef / sh_wc
-        const int tf = t + opaque_zero();
-        fft_line<C, N, T, -1, 4, CG, Lay, PL>(v, xch, tf, 0, tw);
+            for (int c = 0; c < 4; ++c) yin[c * N + site0 + 4 * T * j] = yst[j][c];
+        xch_order<VC::WLINE>();
+        C v[E];
 #pragma unroll
-        for (int m = 0; m < E; ++m)
-            apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], (R)(dk * kindex(tf + T * m, N)), Ky, Kz, inv_n);
-        const int ti = t + opaque_zero();
-        fft_line<C, N, T, +1, 4, CG, Lay, PL>(v, xch, ti, 0, tw);
-        const C wc[4] = {sh_wc[par][0], sh_wc[par][1], sh_wc[par][2], sh_wc[par][3]};
+        for (int m = 0; m < E; ++m) v[m] = yin[(3 - q) * N + t + T * m];
+        fft_row<C, N, -1, false, PL>(v, xq, t, tw);
+        // (an opaque zero: the factors are formed here, not kept in registers over the time loop)
+        const double td = (double)(t + opaque_zero());
 #pragma unroll
         for (int m = 0; m < E; ++m) {
-            const int i = ti + T * m;
-            R A[4] = {(R)0, (R)0, (R)0, (R)0};
-            for (int j = 0; j < nterm; ++j) {
-                const R f = sh_coef[par][j] * fx[j * N + i];
-                const int mu = sh_mu[j];
-                A[0] += mu == 0 ? f : (R)0;
-                A[1] += mu == 1 ? f : (R)0;
-                A[2] += mu == 2 ? f : (R)0;
-                A[3] += mu == 3 ? f : (R)0;
-            }
-            const C ph = phx[i];
-            C sv[4], vs[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sv[q] = cadd(yi[q][m], cmul(wc[q], ph));
-            apply_pot(sv, vs, A[0], A[1], A[2], A[3]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q][m] = cadd(v[q][m], cmul_mi(vs[q]));
+            if constexpr (sizeof(R) == 4) v[m] = cscale(v[m], kt[t + T * m]);
+            else v[m] = cscale(v[m], (R)(kscale * (td + (double)(T * m - (m < E / 2 ? 0 : N)))));
         }
+        fft_row<C, N, +1, false, PL>(v, xq, t, tw);
+        wave_lds_order();
+#pragma unroll
+        for (int m = 0; m < E; ++m) xq[t + T * m] = v[m];
+        // field and source at the sites: independent of the derivative, ahead of the barrier
+        R A[4][SITES];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < SITES; ++j) A[u][j] = (R)0;
+        auto add = [&](int m, R coef, const R (&f)[SITES]) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (m == u) {
+#pragma unroll
+                    for (int j = 0; j < SITES; ++j) A[u][j] += coef * f[j];
+                }
+        };
+        if (nterm > 0) add(mu0, tcs->coef[0], fx0);
+        if (nterm > 1) add(mu1, tcs->coef[1], fx1);
+        if (nterm > 2) add(mu2, tcs->coef[2], fx2);
+        if (nterm > 3) add(mu3, tcs->coef[3], fx3);
+        for (int i = LINE_TERMS; i < nterm; ++i) {
+            R f[SITES];
+#pragma unroll
+            for (int j = 0; j < SITES; ++j) f[j] = fxl[(i - LINE_TERMS) * N + site0 + 4 * T * j];
+            add(uni(a.terms + S->term0 + i)->mu, tcs->coef[i], f);
+        }
+        C wc[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) wc[c] = cmake<C>(tcs->w[2 * c], tcs->w[2 * c + 1]);
+        C u[SITES][4];
+#pragma unroll
+        for (int j = 0; j < SITES; ++j) {
+            // (the stage input again from LDS: not held in registers over the transforms)
+            C yi[4], s[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) yi[c] = yin[c * N + site0 + 4 * T * j];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                s[c] = cadd(yi[c], cmul(wc[c], ph[j]));
+                u[j][c] = cadd(cscale(yi[c], c < 2 ? (R)1 : (R)-1),
+                               cadd(cscale(alpha2_phase(c, yi[3 - c]), Ky), cscale(alpha3_phase(c, yi[c ^ 2]), Kz)));
+            }
+            // only the components some term has
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (mus & (1 << m)) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const C b = m == 0 ? s[c] : m == 1 ? s[3 - c] : m == 2 ? alpha2_phase(c, s[3 - c]) : alpha3_phase(c, s[c ^ 2]);
+                        u[j][c] = cadd(u[j][c], cscale(b, A[m][j]));
+                    }
+                }
+        }
+        xch_order<VC::WLINE>();
+#pragma unroll
+        for (int j = 0; j < SITES; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) k[j][c] = cmul_mi(cadd(xch[c * STRIDE + site0 + 4 * T * j], u[j][c]));
     };
-    // this lane's RK4 sum slot of component q, point m
-    auto acc = [&](int q, int m) -> C& { return accl[(q * E + m) * T + t]; };
 
 #pragma unroll 1
-    for (int n = 0; n < a.nsteps; ++n) {
-        const double tn = a.t_out - (double)(n_first + n) * dt;
-        C yi[4][E], k[4][E];
-        // stage 1 at t_n
-        rhs(y, k, tn, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int m = 0; m < E; ++m) {
-                acc(q, m) = cadd(y[q][m], cscale(k[q][m], h6));
-                yi[q][m] = cadd(y[q][m], cscale(k[q][m], h2));
+    for (int n0 = 0; n0 < a.nsteps; n0 += LINE_BLOCK) {
+        // the time factors of the next LINE_BLOCK steps (the last stage of the
+        // block before has been left by every thread once they are all here)
+        __syncthreads();
+        constexpr int SLOTS = 4 + MAX_TERMS;
+        for (int i = tid; i < LINE_BLOCK * 3 * SLOTS; i += VC::THREADS) {
+            const int slot = i % SLOTS, node = i / SLOTS % 3, n = n0 + i / SLOTS / 3;
+            const double tn = a.t_out - (double)(n_first + n) * dt;
+            const double ts = node == 0 ? tn : node == 1 ? tn - 0.5 * dt : tn - dt;
+            StageConst<R>* K = tc + i / SLOTS;
+            if (slot < 4) {
+                double sn, cs;
+                sincos(-S->E * ts, &sn, &cs);
+                const double wr = S->w[2 * slot], wi = S->w[2 * slot + 1];
+                K->w[2 * slot] = (R)(wr * cs - wi * sn);
+                K->w[2 * slot + 1] = (R)(wr * sn + wi * cs);
+            } else if (slot - 4 < nterm) {
+                const TermDev tm = a.terms[S->term0 + slot - 4];
+                K->coef[slot - 4] = (R)(tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts));
             }
-        // stage 2 at t_n + h/2
-        rhs(yi, k, tn - 0.5 * dt, 1);
+        }
+        __syncthreads();
+        const int nb = a.nsteps - n0 < LINE_BLOCK ? a.nsteps - n0 : LINE_BLOCK;
+#pragma unroll 1
+        for (int n = 0; n < nb; ++n) {
+            // stage 1 at t_n, stages 2 and 3 at t_n + h/2, stage 4 at t_n + h, then the
+            // absorber: one copy of the stage's code, which otherwise does not fit the
+            // instruction cache
+            C yi[SITES][4], acc[SITES][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+            for (int j = 0; j < SITES; ++j)
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                acc(q, m) = cadd(acc(q, m), cscale(k[q][m], h3));
-                yi[q][m] = cadd(y[q][m], cscale(k[q][m], h2));
+                for (int c = 0; c < 4; ++c) yi[j][c] = acc[j][c] = y[j][c];
+#pragma unroll 1
+            for (int st = 0; st < 4; ++st) {
+                const R ha = st == 0 || st == 3 ? h6 : h3, hn = st < 2 ? h2 : h;
+                C k[SITES][4];
+                rhs(yi, k, tc + 3 * n + (st + 1) / 2);
+#pragma unroll
+                for (int j = 0; j < SITES; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        acc[j][c] = cadd(acc[j][c], cscale(k[j][c], ha));
+                        yi[j][c] = cadd(y[j][c], cscale(k[j][c], hn));
+                    }
             }
-        // stage 3 at t_n + h/2
-        rhs(yi, k, tn - 0.5 * dt, 0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+            for (int j = 0; j < SITES; ++j)
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                acc(q, m) = cadd(acc(q, m), cscale(k[q][m], h3));
-                yi[q][m] = cadd(y[q][m], cscale(k[q][m], h));
-            }
-        // stage 4 at t_n + h, then the absorber
-        rhs(yi, k, tn - dt, 1);
-        const int o = opaque_zero();
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const R mk = msk[t + T * m + o];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) y[q][m] = cscale(cadd(acc(q, m), cscale(k[q][m], h6)), mk);
+                for (int c = 0; c < 4; ++c) y[j][c] = cscale(acc[j][c], msk[j]);
         }
     }
-    {
-        gptr<nv2<R>> p = wview<R>(S->buf[BUF_Y]) + t;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+    for (int j = 0; j < SITES; ++j)
 #pragma unroll
-            for (int m = 0; m < E; ++m) gstore<C>(p, q * (long long)N + T * m, y[q][m]);
-    }
+        for (int c = 0; c < 4; ++c) gstore<C>(py, c * (long long)N + 4 * T * j, y[j][c]);
 }
 
 // Kernel table of one (precision, N) instantiation.
 struct RowVariant { const void* stage[4]; const void* dp5[6]; int threads, rows; size_t lds; };   // RK4 / Dormand-Prince stages
 struct CdVariant { const void* fn[2]; int threads, w; size_t lds; };   // [axis - 1]: y writes G, z adds to it
 struct ColVariant { const void* fn[2][3]; int threads, w; size_t lds; };
+struct StepRadices { int n, r[8]; };   // a plan's radices
 struct SizeKernels {
+    StepRadices row_plan, col_plan;   // of the stepping passes (their twiddle tables' order)
     RowVariant row;                // the stage row pass
     CdVariant cd[NVAR];            // the stepping column passes, by variant
     const void* row_other[ROW_NMODES];  // whole-state row modes
     int row0_threads, row0_rows;
     size_t row0_lds;
     ColVariant col;                // whole-state column transforms
-    const void* line[2];           // 1D whole-loop kernel, narrow / wide exchange rounds
-                                   // (NULL where there is no 4-point plan)
+    const void* line;              // 1D whole-loop kernel
     int line_threads;
-    size_t line_lds[2];            // their dynamic LDS without the field-term profiles
+    size_t line_lds;               // its dynamic LDS without the profiles of terms beyond LINE_TERMS
 };
 
 template <class R, int N>
@@ -1078,9 +1153,17 @@ ColVariant make_col_variant() {
     return c;
 }
 
+template <class P> StepRadices radices() {
+    StepRadices s;
+    s.n = P::NR;
+    for (int j = 0; j < P::NR; ++j) s.r[j] = P::R[j];
+    return s;
+}
 template <class R, int N>
 SizeKernels make_size_kernels() {
     SizeKernels k;
+    k.row_plan = radices<StepPlan<N>>();
+    k.col_plan = radices<ColPlan<N>>();
     k.row = make_row_variant<R, N>();
     k.cd[0] = make_cd_variant<R, N, 0>();
     k.cd[1] = make_cd_variant<R, N, 1>();
@@ -1096,17 +1179,9 @@ SizeKernels make_size_kernels() {
     k.row0_threads = RowVar<R, N, 0>::THREADS;
     k.row0_rows = RowVar<R, N, 0>::ROWS;
     k.row0_lds = RowVar<R, N, 0>::BYTES;
-    if constexpr (has_plan4<N>()) {
-        k.line[0] = (const void*)line_kernel<R, N, false>;
-        k.line[1] = (const void*)line_kernel<R, N, true>;
-        k.line_threads = LineVar<R, N, false>::T;
-        k.line_lds[0] = LineVar<R, N, false>::BASE_BYTES;
-        k.line_lds[1] = LineVar<R, N, true>::BASE_BYTES;
-    } else {
-        k.line[0] = k.line[1] = nullptr;
-        k.line_threads = 0;
-        k.line_lds[0] = k.line_lds[1] = 0;
-    }
+    k.line = (const void*)line_kernel<R, N>;
+    k.line_threads = LineVar<R, N>::THREADS;
+    k.line_lds = LineVar<R, N>::BASE_BYTES;
     return k;
 }
 
