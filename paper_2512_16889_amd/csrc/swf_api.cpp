@@ -36,7 +36,7 @@ namespace {
 
 thread_local std::string g_init_error;
 
-constexpr int RED_BLOCKS = 512;          // blocks of every reduction launch (fixed: deterministic sums)
+constexpr int RED_BLOCKS = 512;          // most blocks of a reduction launch (a lattice's number is fixed: deterministic sums)
 constexpr int BW_BLOCKS = 1024;          // most blocks per vertex of the BW stage reduction
 constexpr int BW2_BLOCKS = 256;          // blocks per vertex of the partial-integration route's reductions
 constexpr int NKIND = 6;                 // kernel-stats kinds (swf_kernel_stats)
@@ -206,7 +206,6 @@ struct Plan {
     std::vector<cd> ctab;               // complex tables
     std::vector<Group> batched, single; // groups per grid / per solve
     std::vector<int2> items;
-    size_t state_bytes = 0;             // all state arrays
     // arena layout (byte offsets)
     size_t off_state = 0, off_solves = 0, off_terms = 0, off_verts = 0, off_vgroups = 0, off_modes = 0, off_packets = 0,
            off_rtab = 0, off_ctab = 0,
@@ -692,7 +691,6 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
         P.solve_off.push_back(off);
         off += (size_t)nbufs(P, i) * align256(4 * (size_t)P.hs[i].nsites * P.csize);
     }
-    P.state_bytes = off;
     P.off_solves = off = align256(off);
     off += sizeof(SolveDev) * n_solves;
     P.off_terms = off = align256(off);
@@ -799,7 +797,8 @@ struct swf_ctx {
 namespace {
 
 // Order the context's own stream after the caller's stream (on entry) and the
-// caller's stream after the context's work (on exit).
+// caller's stream after the context's work (on exit; not needed by the calls
+// that return results to the host: they have waited for their work).
 static int enter(swf_ctx* ctx) {
     HIPCHK(hipEventRecord(ctx->ev_in, ctx->user));
     HIPCHK(hipStreamWaitEvent(ctx->st, ctx->ev_in, 0));
@@ -1442,8 +1441,7 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
     }
     ctx->opt.profile = prof;
     ctx->tune_report = rep.str();
-    // the tuning launches stepped the state: start from psi_s(t_out) = 0 again
-    HIPCHK(hipMemsetAsync(ctx->arena + ctx->P.off_state, 0, ctx->P.state_bytes, ctx->st));
+    // (the stages timed write the other state arrays, not psi_s)
     HIPCHK(hipStreamSynchronize(ctx->st));
     return SWF_OK;
 }
@@ -1452,12 +1450,13 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
 static int reduce(swf_ctx* ctx, int kind, swf::RedArgs a, int nv, std::vector<cd>& out) {
     a.solves = ctx->d_solves();
     a.out = ctx->d_red();
-    HIPCHK(swf::launch_reduction(ctx->P.fp64, kind, a, RED_BLOCKS, ctx->st));
-    std::vector<double2> h((size_t)RED_BLOCKS * nv);
+    const int nb = swf::bw_blocks(ctx->P.hs[a.sa].nsites, RED_BLOCKS);   // (one site per thread until the limit)
+    HIPCHK(swf::launch_reduction(ctx->P.fp64, kind, a, nb, ctx->st));
+    std::vector<double2> h((size_t)nb * nv);
     HIPCHK(hipMemcpyAsync(h.data(), ctx->d_red(), h.size() * sizeof(double2), hipMemcpyDeviceToHost, ctx->st));
     HIPCHK(hipStreamSynchronize(ctx->st));
     out.assign(nv, cd(0));
-    for (int b = 0; b < RED_BLOCKS; ++b)
+    for (int b = 0; b < nb; ++b)
         for (int v = 0; v < nv; ++v) out[v] += cd(h[(size_t)b * nv + v].x, h[(size_t)b * nv + v].y);
     return SWF_OK;
 }
@@ -1887,8 +1886,8 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
     // fill buffer pointers and upload descriptors / tables
     for (size_t i = 0; i < P.hs.size(); ++i)
         for (int role = 0; role < swf::NBUF; ++role) P.hs[i].buf[role] = role < nbufs(P, i) ? ctx->buf((int)i, role) : nullptr;
-    INITCHK(hipMemsetAsync(ctx->arena + P.off_state, 0, P.state_bytes, ctx->st));
     INITCHK(hipMemcpyAsync(ctx->d_solves(), P.hs.data(), sizeof(SolveDev) * P.hs.size(), hipMemcpyHostToDevice, ctx->st));
+    INITCHK(swf::launch_zero_psi(ctx->d_solves(), (int)P.hs.size(), (int)P.csize, ctx->st));
     if (!P.ht.empty())
         INITCHK(hipMemcpyAsync(ctx->d_terms(), P.ht.data(), sizeof(TermDev) * P.ht.size(), hipMemcpyHostToDevice, ctx->st));
     if (!P.hv.empty())
@@ -2063,7 +2062,7 @@ swf_status swf_reset(swf_ctx* ctx) {
     if (!ctx) return SWF_E_ARG;
     int r = enter(ctx);
     if (r) return (swf_status)r;
-    HIPCHK(hipMemsetAsync(ctx->arena + ctx->P.off_state, 0, ctx->P.state_bytes, ctx->st));
+    HIPCHK(swf::launch_zero_psi(ctx->d_solves(), (int)ctx->P.solves.size(), (int)ctx->P.csize, ctx->st));
     HIPCHK(hipMemsetAsync(ctx->d_step(), 0, 256, ctx->st));
     HIPCHK(hipMemsetAsync(ctx->d_M(), 0, sizeof(double2) * 3 * std::max<size_t>(1, ctx->P.hv.size()), ctx->st));
     if (ctx->P.bw2) HIPCHK(hipMemsetAsync(ctx->d_M2(), 0, sizeof(double2) * 3 * ctx->P.hv.size(), ctx->st));
@@ -2127,8 +2126,6 @@ swf_status swf_amplitude(swf_ctx* ctx, int which, int i, int j, double out[2]) {
         return SWF_E_ARG;
     }
     if (r) return (swf_status)r;
-    r = leave(ctx);
-    if (r) return (swf_status)r;
     out[0] = val.real();
     out[1] = val.imag();
     return std::isfinite(out[0]) && std::isfinite(out[1]) ? SWF_OK : SWF_E_NONFINITE;
@@ -2150,8 +2147,6 @@ static swf_status pair_matrix_abi(swf_ctx* ctx, int form, const int* u_solves, i
     std::vector<int> us(u_solves, u_solves + nu), vs(v_solves, v_solves + nv);
     std::vector<cd> res;
     r = pair_matrix(ctx, form, us, vs, res, ext, ext_bytes);
-    if (r) return (swf_status)r;
-    r = leave(ctx);
     if (r) return (swf_status)r;
     bool finite = true;
     for (size_t k = 0; k < res.size(); ++k) {
@@ -2212,8 +2207,6 @@ swf_status swf_probability(swf_ctx* ctx, int which, int i, int j, double* out) {
         cd v;
         r = projected(ctx, i, i, want == 0 ? -1 : +1, v);
         if (r) return (swf_status)r;
-        r = leave(ctx);
-        if (r) return (swf_status)r;
         *out = v.real();
     } else if (which == SWF_P_PAIR || which == SWF_P_BW) {
         double a[2];
@@ -2246,13 +2239,14 @@ swf_status swf_diagnostics(swf_ctx* ctx, int i, double out[4]) {
     lattice_x(ctx, i, a);
     a.solves = ctx->d_solves();
     a.out = ctx->d_red();
-    HIPCHK(swf::launch_reduction(ctx->P.fp64, swf::RED_XDIAG, a, RED_BLOCKS, ctx->st));
-    std::vector<double2> h((size_t)RED_BLOCKS * 3);
+    const int nb = swf::bw_blocks(ctx->P.hs[i].nsites, RED_BLOCKS);
+    HIPCHK(swf::launch_reduction(ctx->P.fp64, swf::RED_XDIAG, a, nb, ctx->st));
+    std::vector<double2> h((size_t)nb * 3);
     HIPCHK(hipMemcpyAsync(h.data(), ctx->d_red(), h.size() * sizeof(double2), hipMemcpyDeviceToHost, ctx->st));
     HIPCHK(hipStreamSynchronize(ctx->st));
     double ss = 0, mx = 0, bad = 0;
     cd bs = 0;
-    for (int b = 0; b < RED_BLOCKS; ++b) {
+    for (int b = 0; b < nb; ++b) {
         ss += h[3 * b].x;
         bs += cd(h[3 * b + 1].x, h[3 * b + 1].y);
         mx = std::max(mx, h[3 * b + 2].x);
@@ -2263,8 +2257,6 @@ swf_status swf_diagnostics(swf_ctx* ctx, int i, double out[4]) {
     out[1] = 2.0 * (bs * dV).real();
     out[2] = mx;
     out[3] = bad == 0 ? 1.0 : 0.0;
-    r = leave(ctx);
-    if (r) return (swf_status)r;
     if (bad != 0) {
         ctx->err = "non-finite values in the state";
         return SWF_E_NONFINITE;

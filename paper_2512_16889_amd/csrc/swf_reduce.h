@@ -153,6 +153,8 @@ hipError_t launch_bw2_accum(const BwArgs& a, int nblk, hipStream_t st);
 struct StageNodes { double c[6]; };
 hipError_t launch_stage_consts(int fp64, const PassArgs& a, const StageNodes& cst, int nsolves, hipStream_t st);
 hipError_t launch_advance(int* step, int n, hipStream_t st);
+// psi_s = 0 for every solve (csize: bytes of a state number)
+hipError_t launch_zero_psi(const SolveDev* solves, int nsolves, int csize, hipStream_t st);
 hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, int step, unsigned long long* flag,
                                hipStream_t st);
 

@@ -848,6 +848,27 @@ hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, in
     return hipGetLastError();
 }
 
+// Clears the Y array of every solve.  (Every other state array is written before
+// it is read, so a reset moves a quarter of the bytes of clearing them all: 8
+// x 320^3 in single precision 1.4 ms instead of 5.6.)
+__global__ void __launch_bounds__(RED_THREADS) zero_psi_kernel(const SolveDev* solves, int csize) {
+    using v4 = unsigned __attribute__((ext_vector_type(4)));
+    const SolveDev* S = solves + blockIdx.y;
+    v4* y = reinterpret_cast<v4*>(S->buf[BUF_Y]);
+    const long long n = 4 * S->nsites * csize / 16;   // (a lattice has a multiple of 8 sites)
+    for (long long i = (long long)blockIdx.x * RED_THREADS + threadIdx.x; i < n; i += (long long)gridDim.x * RED_THREADS)
+        __builtin_nontemporal_store(v4{0, 0, 0, 0}, y + i);
+}
+
+hipError_t launch_zero_psi(const SolveDev* solves, int nsolves, int csize, hipStream_t st) {
+    const int per = nsolves < 64 ? 2048 / nsolves : 32;   // workgroups a solve: 2048 or more in all
+    for (int s0 = 0; s0 < nsolves; s0 += 65535) {
+        const int m = nsolves - s0 < 65535 ? nsolves - s0 : 65535;
+        hipLaunchKernelGGL(zero_psi_kernel, dim3(per, m), dim3(RED_THREADS), 0, st, solves + s0, csize);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_advance(int* step, int n, hipStream_t st) {
     hipLaunchKernelGGL(tick_kernel, dim3(1), dim3(64), 0, st, step, n);
     return hipGetLastError();
