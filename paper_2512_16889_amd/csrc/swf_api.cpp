@@ -279,7 +279,7 @@ static void add_items(Plan& P, Group& g, int fp64) {
 
 // State arrays of solve i: Y, ACC, YS, T; A0, A1 for the partial-integration
 // BW route; all eight (the Dormand-Prince slopes) with that stepper.
-static int nbufs(const Plan& P, size_t i) { return P.dp5 ? swf::NBUF : (P.aux[i] || P.ip ? 6 : 4); }
+static int nbufs(const Plan& P, size_t i) { return P.dp5 ? swf::NBUF : (P.aux[i] ? 6 : 4); }
 
 static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_grids, const swf_term* terms,
                       const int* ffirst, int n_fields, const swf_solve* solves, int n_solves,
@@ -1152,24 +1152,28 @@ static int free_evolve(swf_ctx* ctx, const Group& g, int role, double tau) {
     return r;
 }
 
-// out_j = sum_i c[j][i] in_i over a group's states (roles; -1 unused).
-static int combo(swf_ctx* ctx, const Group& g, const int (&in)[3], const int (&out)[2], const double (&c)[2][3],
-                 int mask = 0) {
-    swf::ComboArgs a;
+// The per-step constants of every stage (StageConst), at the step about to be enqueued.
+static int stage_consts(swf_ctx* ctx) {
+    swf::StageNodes n;
+    for (int st = 0; st < 6; ++st) n.c[st] = ctx->P.cst[st];
+    HIPCHK(swf::launch_stage_consts(ctx->P.fp64, pass_args(ctx), n, (int)ctx->P.solves.size(), ctx->st));
+    return SWF_OK;
+}
+
+// One pointwise part of an interaction-picture step of a group.
+static int ip_point(swf_ctx* ctx, const Group& g, int mode) {
+    swf::IpArgs a;
     memset(&a, 0, sizeof(a));
     a.solves = ctx->d_solves();
+    a.terms = ctx->d_terms();
     a.items = ctx->d_items() + g.it_orow;
     a.rows = g.k[0]->row0_rows;
     a.rtab = ctx->d_rtab();
-    for (int i = 0; i < 3; ++i) {
-        a.in[i] = in[i];
-        a.c[0][i] = c[0][i];
-        a.c[1][i] = c[1][i];
-    }
-    a.out[0] = out[0];
-    a.out[1] = out[1];
-    a.mask = mask;
-    HIPCHK(swf::launch_combo(ctx->P.fp64, a, g.n_orow, ctx->st));
+    a.ctab = ctx->d_ctab();
+    a.consts = ctx->d_consts();
+    a.nst = ctx->P.nst;
+    a.h = -ctx->P.sdt;
+    HIPCHK(swf::launch_ip_point(ctx->P.fp64, mode, a, g.n_orow, ctx->st));
     return SWF_OK;
 }
 
@@ -1178,13 +1182,15 @@ static int combo(swf_ctx* ctx, const Group& g, const int (&in)[3], const int (&o
 //   k2 = N(t + h/2, a),          b = E y + h/2 k2,
 //   k3 = N(t + h/2, b),          c = E (E y + h k3),
 //   k4 = N(t + h, c),            y' = E (E (y + h/6 k1) + h/3 (k2 + k3)) + h/6 k4
-// (= E^2 y + h/6 (E^2 k1 + 2 E k2 + 2 E k3 + k4)).  The stage inputs y, a, b, c
-// pass through YS (y itself at stage 0) so that the BW reductions read them as
-// for the classical stepper; ACC carries the update, A0 the sum k2 + k3, A1 the
-// latest slope, T is the transforms' work buffer.
+// (= E^2 y + h/6 (E^2 k1 + 2 E k2 + 2 E k3 + k4)).  E is linear, so
+// E (y + h/6 k1) = (2 E y + a) / 3 needs no transform of its own: four free
+// evolutions, of YS = y + h/2 k1 and Y, then of YS = E y + h k3 and ACC.  The
+// stage inputs y, a, b, c pass through YS (y itself at stage 0), where the BW
+// reductions read them as for the classical stepper; T is the transforms' work
+// buffer.
 static int ip_step(swf_ctx* ctx) {
     using namespace swf;
-    const double h = -ctx->P.sdt;
+    const double tau = -0.5 * ctx->P.sdt;
     auto each = [&](auto&& f) {
         for (const auto& g : groups(ctx)) {
             int r = f(g);
@@ -1192,46 +1198,32 @@ static int ip_step(swf_ctx* ctx) {
         }
         return (int)SWF_OK;
     };
-    int r = bw_stage(ctx, 0);
+    const bool vertices = !ctx->P.hv.empty();
+    int r = stage_consts(ctx);
+    if (!r) r = bw_stage(ctx, 0);
     if (!r) r = each([&](const Group& g) {
-        int rr = row_pass(ctx, g, ROW_SRC, 0, BUF_Y, BUF_A1, 0, 0);
-        if (!rr) rr = combo(ctx, g, {BUF_Y, BUF_A1, -1}, {BUF_YS, BUF_ACC}, {{1.0, 0.5 * h, 0.0}, {1.0, h / 6.0, 0.0}});
-        if (!rr) rr = free_evolve(ctx, g, BUF_YS, 0.5 * h);   // a
-        if (!rr) rr = free_evolve(ctx, g, BUF_Y, 0.5 * h);    // E y
+        int rr = ip_point(ctx, g, IP_FIRST);
+        if (!rr) rr = free_evolve(ctx, g, BUF_YS, tau);   // a
+        if (!rr) rr = free_evolve(ctx, g, BUF_Y, tau);    // E y
+        if (!rr && !vertices) rr = ip_point(ctx, g, IP_MIDDLE);
         return rr;
     });
-    if (!r) r = bw_stage(ctx, 1);
+    if (!r && vertices) {
+        r = bw_stage(ctx, 1);
+        if (!r) r = each([&](const Group& g) { return ip_point(ctx, g, IP_SECOND); });   // b
+        if (!r) r = bw_stage(ctx, 2);
+        if (!r) r = each([&](const Group& g) { return ip_point(ctx, g, IP_THIRD); });
+    }
     if (!r) r = each([&](const Group& g) {
-        int rr = row_pass(ctx, g, ROW_SRC, 1, BUF_YS, BUF_A1, 0, 0);
-        if (!rr) rr = combo(ctx, g, {BUF_Y, BUF_A1, -1}, {BUF_YS, BUF_A0}, {{1.0, 0.5 * h, 0.0}, {0.0, 1.0, 0.0}});   // b, k2
-        return rr;
-    });
-    if (!r) r = bw_stage(ctx, 2);
-    if (!r) r = each([&](const Group& g) {
-        int rr = row_pass(ctx, g, ROW_SRC, 2, BUF_YS, BUF_A1, 0, 0);
-        if (!rr) rr = combo(ctx, g, {BUF_Y, BUF_A1, BUF_A0}, {BUF_YS, BUF_A0}, {{1.0, h, 0.0}, {0.0, 1.0, 1.0}});
-        if (!rr) rr = free_evolve(ctx, g, BUF_YS, 0.5 * h);   // c
-        if (!rr) rr = free_evolve(ctx, g, BUF_ACC, 0.5 * h);
-        if (!rr) rr = combo(ctx, g, {BUF_ACC, BUF_A0, -1}, {BUF_ACC, -1}, {{1.0, h / 3.0, 0.0}, {0.0, 0.0, 0.0}});
-        if (!rr) rr = free_evolve(ctx, g, BUF_ACC, 0.5 * h);
+        int rr = free_evolve(ctx, g, BUF_YS, tau);        // c
+        if (!rr) rr = free_evolve(ctx, g, BUF_ACC, tau);
         return rr;
     });
     if (!r) r = bw_stage(ctx, 3);
-    if (!r) r = each([&](const Group& g) {
-        int rr = row_pass(ctx, g, ROW_SRC, 3, BUF_YS, BUF_A1, 0, 0);
-        if (!rr) rr = combo(ctx, g, {BUF_ACC, BUF_A1, -1}, {BUF_Y, -1}, {{1.0, h / 6.0, 0.0}, {0.0, 0.0, 0.0}}, 1);
-        return rr;
-    });
+    if (!r) r = each([&](const Group& g) { return ip_point(ctx, g, IP_LAST); });
     if (!r) r = bw_accum(ctx);
     if (r) return r;
     ++ctx->step_add;
-    return SWF_OK;
-}
-
-static int stage_consts(swf_ctx* ctx) {
-    swf::StageNodes n;
-    for (int st = 0; st < 6; ++st) n.c[st] = ctx->P.cst[st];
-    HIPCHK(swf::launch_stage_consts(ctx->P.fp64, pass_args(ctx), n, (int)ctx->P.solves.size(), ctx->st));
     return SWF_OK;
 }
 

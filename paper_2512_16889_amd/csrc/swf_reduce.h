@@ -124,20 +124,21 @@ struct PairArgs {
     double2* part;       // [mp][np][splits] partial tiles, then [mp][np] the sum
 };
 
-// Pointwise combination of state arrays of a group's solves (the interaction
-// picture's stage inputs and update): out_j = sum_i c[j][i] in_i over every
-// site and component, optionally times the absorber mask.
-struct ComboArgs {
+// Pointwise parts of an interaction-picture step (see ip_point_kernel), for a
+// group's solves.
+enum { IP_FIRST = 0, IP_MIDDLE = 1, IP_SECOND = 2, IP_THIRD = 3, IP_LAST = 4 };
+struct IpArgs {
     const SolveDev* solves;
+    const TermDev* terms;
     const int2* items;   // (solve, block of `rows` x-lines) per workgroup
     int rows;
-    const void* rtab;    // real tables (the masks)
-    int in[3];           // input roles (-1: unused)
-    int out[2];          // output roles (-1: unused)
-    double c[2][3];
-    int mask;            // 1: output 0 is multiplied by the solve's absorber mask (if it has one)
+    const void* rtab;    // real tables (field profiles, masks)
+    const void* ctab;    // complex tables (background phases)
+    const void* consts;  // StageConst per solve and stage
+    int nst;
+    double h;            // the signed step
 };
-hipError_t launch_combo(int fp64, const ComboArgs& a, int nitems, hipStream_t st);
+hipError_t launch_ip_point(int fp64, int mode, const IpArgs& a, int nitems, hipStream_t st);
 
 hipError_t launch_reduction(int fp64, int kind, const RedArgs& a, int blocks, hipStream_t st);
 hipError_t launch_pair_gemm(int fp64, const PairArgs& a, hipStream_t st);

@@ -796,47 +796,133 @@ hipError_t launch_bw2_accum(const BwArgs& a, int nblk, hipStream_t st) {
     return hipGetLastError();
 }
 
+// The field terms N(t_stage, y) = -i (A_0 + alpha^j A_j)(y + psi_b) at one site.
 template <class R>
-__global__ void __launch_bounds__(RED_THREADS) combo_kernel(ComboArgs a) {
+struct IpSite {
     using C = cpx<R>;
-    const int2 it = a.items[blockIdx.x];
-    const SolveDev* __restrict__ S = a.solves + it.x;
-    const int n0 = S->n[0], n1 = S->n[1], nrows = S->nrows;
-    const long long ns = S->nsites;
-    gptr<const nv2<R>> in[3];
-    R c[2][3];
+    sptr<SolveDev> S;
+    const TermDev* terms;
+    gptr<const R> rtab;
+    sptr<StageConst<R>> K;   // of stage 0
+    int x, yy, zz, n0, n1;
+    C ph;
+    __device__ __forceinline__ void slope(int stage, const C (&y)[4], C (&k)[4]) const {
+        const sptr<StageConst<R>> Ks = K + stage;
+        R A[4] = {(R)0, (R)0, (R)0, (R)0};
+        for (int j = 0; j < S->nterm; ++j) {
+            const sptr<TermDev> tm = uni(terms + S->term0 + j);
+            gptr<const R> tab = rtab + tm->tab;
+            const R f = Ks->coef[j] * tab[n0 + yy] * tab[n0 + n1 + zz] * tab[x];
+            const int mu = tm->mu;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        in[i] = a.in[i] >= 0 ? cview<R>(S->buf[a.in[i]]) : cview<R>(S->buf[0]);
-        c[0][i] = (R)a.c[0][i];
-        c[1][i] = (R)a.c[1][i];
+            for (int u = 0; u < 4; ++u)
+                if (mu == u) A[u] += f;
+        }
+        C s[4], vs[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] = cadd(y[q], cmul(cmake<C>(Ks->w[2 * q], Ks->w[2 * q + 1]), ph));
+        apply_pot(s, vs, A[0], A[1], A[2], A[3]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) k[q] = cmul_mi(vs[q]);
     }
-    gptr<nv2<R>> o0 = wview<R>(S->buf[a.out[0] >= 0 ? a.out[0] : 0]);
-    gptr<nv2<R>> o1 = wview<R>(S->buf[a.out[1] >= 0 ? a.out[1] : 0]);
+};
+
+// The pointwise parts of an interaction-picture step, between its free
+// evolutions E = exp(-i H0 h/2) (the scheme stands at ip_step).  The slopes act
+// on single sites, so everything between two free evolutions is one pass:
+//   IP_FIRST   reads y:        YS = y + h/2 k1
+//   IP_MIDDLE  reads a, E y:   k2, b = E y + h/2 k2, k3;  YS = E y + h k3,  ACC = (2 E y + a + h (k2 + k3)) / 3
+//   IP_LAST    reads c, E ACC: Y = E ACC + h/6 k4, times the absorber mask
+// IP_SECOND and IP_THIRD are the halves of IP_MIDDLE, with b left in YS for the
+// Breit-Wheeler sums.  HBM-bound: 2 + 4 + 3 array traversals a step, where a
+// source pass and a combination pass per slope took 27 (16 solves of 256 x 192
+// in double: 270 us a step).
+template <class R, int MODE>
+__global__ void __launch_bounds__(RED_THREADS) ip_point_kernel(IpArgs a) {
+    using C = cpx<R>;
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const int solve = (int)(unsigned)item, ty = (int)(item >> 32);
+    const sptr<SolveDev> S = uni(a.solves + solve);
+    const int n0 = S->n[0], n1 = S->n[1];
+    const long long ns = S->nsites;
     gptr<const R> rtab = glob(reinterpret_cast<const R*>(a.rtab));
-    const bool mask = a.mask && S->mask >= 0;
-    const int per = a.rows * n0;
-    for (int e = threadIdx.x; e < 4 * per; e += RED_THREADS) {
-        const int q = e / per, r = e % per;
-        const int row = it.y * a.rows + r / n0, x = r % n0;
-        if (row >= nrows) continue;
-        const long long idx = (long long)q * ns + (long long)row * n0 + x;
-        C v[3];
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
+    const int row0 = ty * a.rows, rows = S->nrows - row0 < a.rows ? S->nrows - row0 : a.rows;
+    const long long tile = (long long)row0 * n0;
+    gptr<const nv2<R>> pY = cview<R>(S->buf[BUF_Y]) + tile, pYS = cview<R>(S->buf[BUF_YS]) + tile, pA = cview<R>(S->buf[BUF_ACC]) + tile;
+    gptr<nv2<R>> wY = wview<R>(S->buf[BUF_Y]) + tile, wYS = wview<R>(S->buf[BUF_YS]) + tile, wA = wview<R>(S->buf[BUF_ACC]) + tile;
+    const R h = (R)a.h, h2 = (R)(0.5 * a.h), h6 = (R)(a.h / 6.0), h3 = (R)(a.h / 3.0), third = (R)(1.0 / 3.0);
+    IpSite<R> site;
+    site.S = S;
+    site.terms = a.terms;
+    site.rtab = rtab;
+    site.K = uni(reinterpret_cast<const StageConst<R>*>(a.consts) + (long long)solve * a.nst);
+    site.n0 = n0;
+    site.n1 = n1;
+    const long long mask = S->mask;
+    for (int e = threadIdx.x; e < rows * n0; e += RED_THREADS) {
+        const int r = e / n0, row = row0 + r;
+        site.x = e - r * n0;
+        site.yy = row % n1;
+        site.zz = row / n1;
+        C u[4], v[4], w[4], k[4];   // the arrays the mode reads
 #pragma unroll
-        for (int i = 0; i < 3; ++i) v[i] = a.in[i] >= 0 ? gload_nt<C>(in[i], idx) : cmake<C>((R)0, (R)0);
-        C w0 = cadd(cadd(cscale(v[0], c[0][0]), cscale(v[1], c[0][1])), cscale(v[2], c[0][2]));
-        if (mask) w0 = cscale(w0, rtab[S->mask + x] * rtab[S->mask + n0 + row % n1] * rtab[S->mask + n0 + n1 + row / n1]);
-        if (a.out[0] >= 0) gstore_nt<C>(o0, idx, w0);
-        if (a.out[1] >= 0)
-            gstore_nt<C>(o1, idx, cadd(cadd(cscale(v[0], c[1][0]), cscale(v[1], c[1][1])), cscale(v[2], c[1][2])));
+        for (int q = 0; q < 4; ++q) {
+            u[q] = gload_nt<C>(MODE == IP_FIRST ? pY : pYS, q * ns + e);
+            if constexpr (MODE == IP_MIDDLE || MODE == IP_SECOND || MODE == IP_THIRD) v[q] = gload_nt<C>(pY, q * ns + e);
+            if constexpr (MODE == IP_THIRD || MODE == IP_LAST) w[q] = gload_nt<C>(pA, q * ns + e);
+        }
+        site.ph = cmul(gload<C>(ctab, S->ph + site.x), cmul(gload<C>(ctab, S->ph + n0 + site.yy), gload<C>(ctab, S->ph + n0 + n1 + site.zz)));
+        site.slope(MODE == IP_FIRST ? 0 : MODE == IP_LAST ? 3 : MODE == IP_THIRD ? 2 : 1, u, k);
+        if constexpr (MODE == IP_FIRST) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) gstore_nt<C>(wYS, q * ns + e, cadd(u[q], cscale(k[q], h2)));
+        } else if constexpr (MODE == IP_LAST) {
+            const R mk = mask >= 0 ? rtab[mask + site.x] * rtab[mask + n0 + site.yy] * rtab[mask + n0 + n1 + site.zz] : (R)1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const C o = cadd(w[q], cscale(k[q], h6));
+                gstore_nt<C>(wY, q * ns + e, mask >= 0 ? cscale(o, mk) : o);
+            }
+        } else {
+            C b[4], acc[4];
+            if constexpr (MODE == IP_THIRD) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = w[q];
+            } else {
+                // a in u, E y in v, k2 in k
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    b[q] = cadd(v[q], cscale(k[q], h2));
+                    acc[q] = cadd(cscale(cadd(cscale(v[q], (R)2), u[q]), third), cscale(k[q], h3));
+                }
+                if constexpr (MODE == IP_MIDDLE) site.slope(2, b, k);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                gstore_nt<C>(wYS, q * ns + e, MODE == IP_SECOND ? b[q] : cadd(v[q], cscale(k[q], h)));
+                gstore_nt<C>(wA, q * ns + e, MODE == IP_SECOND ? acc[q] : cadd(acc[q], cscale(k[q], h3)));
+            }
+        }
     }
 }
 
-hipError_t launch_combo(int fp64, const ComboArgs& a, int nitems, hipStream_t st) {
-    if (nitems <= 0) return hipSuccess;
-    if (fp64) hipLaunchKernelGGL(combo_kernel<double>, dim3(nitems), dim3(RED_THREADS), 0, st, a);
-    else hipLaunchKernelGGL(combo_kernel<float>, dim3(nitems), dim3(RED_THREADS), 0, st, a);
+template <class R>
+static hipError_t launch_ip_point_t(int mode, const IpArgs& a, int n, hipStream_t st) {
+    const dim3 g(n), b(RED_THREADS);
+    switch (mode) {
+        case IP_FIRST: hipLaunchKernelGGL((ip_point_kernel<R, IP_FIRST>), g, b, 0, st, a); break;
+        case IP_MIDDLE: hipLaunchKernelGGL((ip_point_kernel<R, IP_MIDDLE>), g, b, 0, st, a); break;
+        case IP_SECOND: hipLaunchKernelGGL((ip_point_kernel<R, IP_SECOND>), g, b, 0, st, a); break;
+        case IP_THIRD: hipLaunchKernelGGL((ip_point_kernel<R, IP_THIRD>), g, b, 0, st, a); break;
+        case IP_LAST: hipLaunchKernelGGL((ip_point_kernel<R, IP_LAST>), g, b, 0, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
+}
+hipError_t launch_ip_point(int fp64, int mode, const IpArgs& a, int nitems, hipStream_t st) {
+    if (nitems <= 0) return hipSuccess;
+    return fp64 ? launch_ip_point_t<double>(mode, a, nitems, st) : launch_ip_point_t<float>(mode, a, nitems, st);
 }
 
 hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, int step, unsigned long long* flag,
