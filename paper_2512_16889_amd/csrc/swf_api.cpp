@@ -915,6 +915,12 @@ static int row_pass(swf_ctx* ctx, const Group& g, int mode, int stage, int src, 
         return launch(ctx, ctx->P.dp5 ? v.dp5[stage] : v.stage[stage], g.n_row, g.it_row, v.threads,
                       v.lds, a, kind, bytes);
     }
+    // transforms that mix no components (an inverse along the only axis multiplies by H0 first)
+    const int t = mode == swf::ROW_FWD ? 0 : mode == swf::ROW_FWDPH ? 1 : mode == swf::ROW_INV && !a.h0row ? 2 : -1;
+    if (t >= 0) {
+        if (t == 2) a.src = swf::BUF_T;
+        return launch(ctx, k->row_t[t], g.n_row, g.it_row, k->row.threads, k->row.lds, a, kind, bytes);
+    }
     return launch(ctx, k->row_other[mode], g.n_orow, g.it_orow, k->row0_threads, k->row0_lds, a, kind, bytes);
 }
 
@@ -927,10 +933,16 @@ static int col_pass(swf_ctx* ctx, const Group& g, int axis, int mode, int role, 
     a.src = role;
     a.expo = expo;
     a.tau = tau;
+    const double bytes = 2.0 * 4.0 * ctx->P.csize * group_sites(ctx, g);
+    if (mode != swf::COL_H0) {
+        const int v = g.k[axis]->col_tv[axis - 1];
+        const auto& tv = g.k[axis]->cd[v];
+        return launch(ctx, g.k[axis]->col_t[axis - 1][mode == swf::COL_FWD ? 0 : 1], axis == 1 ? g.n_coly[v] : g.n_colz[v],
+                      axis == 1 ? g.it_coly[v] : g.it_colz[v], tv.threads, tv.lds, a, kind, bytes, 4);
+    }
     const int n = axis == 1 ? g.n_ocy : g.n_ocz;
     const size_t it = axis == 1 ? g.it_ocy : g.it_ocz;
-    return launch(ctx, cv.fn[axis - 1][mode], n, it, cv.threads, cv.lds, a, kind,
-                  2.0 * 4.0 * ctx->P.csize * group_sites(ctx, g));
+    return launch(ctx, cv.fn[axis - 1], n, it, cv.threads, cv.lds, a, kind, bytes);
 }
 
 // Stepping column pass along `axis` of the stage input `src`: alpha^j D_j of
@@ -1932,9 +1944,13 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
                 for (int m = 0; m < swf::ROW_NMODES; ++m)
                     if (k->row_other[m])
                         INITCHK(hipFuncSetAttribute(k->row_other[m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row0_lds));
-                for (int a = 0; a < 2; ++a)
-                    for (int m = 0; m < 3; ++m)
-                        INITCHK(hipFuncSetAttribute(k->col.fn[a][m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->col.lds));
+                for (int m = 0; m < 3; ++m)
+                    INITCHK(hipFuncSetAttribute(k->row_t[m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->row.lds));
+                for (int a = 0; a < 2; ++a) {
+                    INITCHK(hipFuncSetAttribute(k->col.fn[a], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->col.lds));
+                    for (int m = 0; m < 2; ++m)
+                        INITCHK(hipFuncSetAttribute(k->col_t[a][m], hipFuncAttributeMaxDynamicSharedMemorySize, (int)k->cd[k->col_tv[a]].lds));
+                }
                 if (ax == 0)
                     INITCHK(hipFuncSetAttribute(k->line, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)std::min(ctx->lds_max, line_lds(g, P, swf::MAX_TERMS))));

@@ -225,126 +225,111 @@ __global__ void __launch_bounds__((RowVar<R, N, V>::THREADS)) row_kernel(PassArg
     };
 
     C v[4][E];
-    if constexpr (MODE == ROW_FWD || MODE == ROW_FWDPH) {
-        load(a.src, v);
-        if constexpr (MODE == ROW_FWDPH) {
-            const long long ph = a.ph2;
-            const C pyz = cmul(gload<C>(ctab, ph + n0 + yy), gload<C>(ctab, ph + n0 + n1 + zz));
+    if constexpr (MODE == ROW_SRC) {
+        // no kinetic term: the epilogue below adds the source to zero
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const C p = cmul(gload<C>(ctab, ph + t + T * m), pyz);
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q][m] = cmul(v[q][m], p);
+            for (int m = 0; m < E; ++m) v[q][m] = cmake<C>((R)0, (R)0);
+    } else {
+        // ---- inverse transform of the k-space buffer (optionally after -i H0 / N)
+        load(BUF_T, v);
+        if (a.h0row) {
+            const R Ky = (R)S->kap[1], Kz = (R)S->kap[2], s = (R)S->inv_n;
+            const double dk = S->dk[0];
+            if (a.expo) {
+#pragma unroll
+                for (int m = 0; m < E; ++m)
+                    apply_expo(v[0][m], v[1][m], v[2][m], v[3][m], dk * kindex(t + T * m, N), S->kap[1], S->kap[2],
+                               a.tau, S->inv_n);
+            } else {
+#pragma unroll
+                for (int m = 0; m < E; ++m) {
+                    const R Kx = (R)(dk * kindex(t + T * m, N));
+                    apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], Kx, Ky, Kz, s);
+                }
             }
         }
-        fft4<C, N, T, -1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, line, tw);
+        fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, line, tw);
+    }
+    if constexpr (MODE == ROW_INV) {
         store(a.dst, v);
         return;
     } else {
-        if constexpr (MODE == ROW_SRC) {
-            // no kinetic term: the epilogue below adds the source to zero
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int m = 0; m < E; ++m) v[q][m] = cmake<C>((R)0, (R)0);
+        // ---- stage epilogue: k = K - i V(t_i) (y_i + psi_b(t_i))
+        double ts;
+        if constexpr (MODE == ROW_RHS) {
+            ts = a.t_explicit;
         } else {
-            // ---- inverse transform of the k-space buffer (optionally after -i H0 / N)
-            load(BUF_T, v);
-            if (a.h0row) {
-                const R Ky = (R)S->kap[1], Kz = (R)S->kap[2], s = (R)S->inv_n;
-                const double dk = S->dk[0];
-                if (a.expo) {
+            const double cst = a.stage == 0 ? 0.0 : (a.stage == 3 ? 1.0 : 0.5);
+            ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - cst * a.dt;
+        }
+        const int nterm = S->nterm;
+        for (int j = t; j < nterm; j += T) {
+            const TermDev tm = a.terms[S->term0 + j];
+            const double coef = tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts);
+            sh_fyz[line][j] = (R)coef * rtab[tm.tab + n0 + yy] * rtab[tm.tab + n0 + n1 + zz];
+            if (line == 0) {
+                sh_mu[j] = tm.mu;
+                sh_tab[j] = tm.tab;
+            }
+        }
+        for (int q = tid; q < 4; q += VC::THREADS) {
+            double sn, cs;
+            sincos(-S->E * ts, &sn, &cs);
+            const double wr = S->w[2 * q], wi = S->w[2 * q + 1];
+            sh_wc[q] = cmake<C>((R)(wr * cs - wi * sn), (R)(wr * sn + wi * cs));
+        }
+        if (t == 0) sh_phyz[line] = cmul(gload<C>(ctab, S->ph + n0 + yy), gload<C>(ctab, S->ph + n0 + n1 + zz));
+        {
+            // state loads are independent of the barrier below: issue them first
+            C yi[4][E];
+            load(a.src, yi);
+            __syncthreads();
+            // field A_mu on this line's points
+            R A[4][E];
 #pragma unroll
-                    for (int m = 0; m < E; ++m)
-                        apply_expo(v[0][m], v[1][m], v[2][m], v[3][m], dk * kindex(t + T * m, N), S->kap[1], S->kap[2],
-                                   a.tau, S->inv_n);
-                } else {
+            for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+                for (int m = 0; m < E; ++m) A[mu][m] = (R)0;
+#pragma unroll
+            for (int j = 0; j < MAX_TERMS; ++j) {
+                if (j < nterm) {
+                    const R fyz = sh_fyz[line][j];
+                    gptr<const R> tab = rtab + sh_tab[j] + t;
+                    const int mu = sh_mu[j];
 #pragma unroll
                     for (int m = 0; m < E; ++m) {
-                        const R Kx = (R)(dk * kindex(t + T * m, N));
-                        apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], Kx, Ky, Kz, s);
+                        const R f = fyz * tab[T * m];
+                        A[0][m] += mu == 0 ? f : (R)0;
+                        A[1][m] += mu == 1 ? f : (R)0;
+                        A[2][m] += mu == 2 ? f : (R)0;
+                        A[3][m] += mu == 3 ? f : (R)0;
                     }
                 }
             }
-            fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, line, tw);
-        }
-        if constexpr (MODE == ROW_INV) {
+            const long long phx = S->ph + t;
+            const C wc[4] = {sh_wc[0], sh_wc[1], sh_wc[2], sh_wc[3]};
+            const C phyz = sh_phyz[line];
+#pragma unroll
+            for (int m = 0; m < E; ++m) {
+                const C ph = cmul(gload<C>(ctab, phx + T * m), phyz);
+                C sv[4], vs[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sv[q] = cadd(yi[q][m], cmul(wc[q], ph));
+                apply_pot(sv, vs, A[0][m], A[1][m], A[2][m], A[3][m]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q][m] = cadd(v[q][m], cmul_mi(vs[q]));   // v = k
+            }
             store(a.dst, v);
-            return;
-        } else {
-            // ---- stage epilogue: k = K - i V(t_i) (y_i + psi_b(t_i))
-            double ts;
-            if constexpr (MODE == ROW_RHS) {
-                ts = a.t_explicit;
-            } else {
-                const double cst = a.stage == 0 ? 0.0 : (a.stage == 3 ? 1.0 : 0.5);
-                ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - cst * a.dt;
-            }
-            const int nterm = S->nterm;
-            for (int j = t; j < nterm; j += T) {
-                const TermDev tm = a.terms[S->term0 + j];
-                const double coef = tm.amp * profile_t(tm.ft_type, tm.c, tm.w, tm.k, tm.phi, ts);
-                sh_fyz[line][j] = (R)coef * rtab[tm.tab + n0 + yy] * rtab[tm.tab + n0 + n1 + zz];
-                if (line == 0) {
-                    sh_mu[j] = tm.mu;
-                    sh_tab[j] = tm.tab;
-                }
-            }
-            for (int q = tid; q < 4; q += VC::THREADS) {
-                double sn, cs;
-                sincos(-S->E * ts, &sn, &cs);
-                const double wr = S->w[2 * q], wi = S->w[2 * q + 1];
-                sh_wc[q] = cmake<C>((R)(wr * cs - wi * sn), (R)(wr * sn + wi * cs));
-            }
-            if (t == 0) sh_phyz[line] = cmul(gload<C>(ctab, S->ph + n0 + yy), gload<C>(ctab, S->ph + n0 + n1 + zz));
-            {
-                // state loads are independent of the barrier below: issue them first
-                C yi[4][E];
-                load(a.src, yi);
-                __syncthreads();
-                // field A_mu on this line's points
-                R A[4][E];
-#pragma unroll
-                for (int mu = 0; mu < 4; ++mu)
-#pragma unroll
-                    for (int m = 0; m < E; ++m) A[mu][m] = (R)0;
-#pragma unroll
-                for (int j = 0; j < MAX_TERMS; ++j) {
-                    if (j < nterm) {
-                        const R fyz = sh_fyz[line][j];
-                        gptr<const R> tab = rtab + sh_tab[j] + t;
-                        const int mu = sh_mu[j];
-#pragma unroll
-                        for (int m = 0; m < E; ++m) {
-                            const R f = fyz * tab[T * m];
-                            A[0][m] += mu == 0 ? f : (R)0;
-                            A[1][m] += mu == 1 ? f : (R)0;
-                            A[2][m] += mu == 2 ? f : (R)0;
-                            A[3][m] += mu == 3 ? f : (R)0;
-                        }
-                    }
-                }
-                const long long phx = S->ph + t;
-                const C wc[4] = {sh_wc[0], sh_wc[1], sh_wc[2], sh_wc[3]};
-                const C phyz = sh_phyz[line];
-#pragma unroll
-                for (int m = 0; m < E; ++m) {
-                    const C ph = cmul(gload<C>(ctab, phx + T * m), phyz);
-                    C sv[4], vs[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) sv[q] = cadd(yi[q][m], cmul(wc[q], ph));
-                    apply_pot(sv, vs, A[0][m], A[1][m], A[2][m], A[3][m]);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q][m] = cadd(v[q][m], cmul_mi(vs[q]));   // v = k
-                }
-                store(a.dst, v);
-            }
         }
     }
 }
 
 // ------------------------------------------------------------------ column pass
-template <class R, int N, int V, int MODE, int AXIS>
+// Forward transform along the last axis, -i H0 / N or the free evolution, and back
+// (the whole state of a column in a thread group: the multiply mixes components).
+template <class R, int N, int V, int AXIS>
 __global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArgs a) {
     using C = cpx<R>;
     using VC = ColVar<R, N, V>;
@@ -385,25 +370,23 @@ __global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArg
 #pragma unroll
             for (int m = 0; m < E; ++m) v[q][m] = gload<C>(p, q * ns + (long long)(T * m) * stride);
     }
-    if constexpr (MODE == COL_FWD || MODE == COL_H0) fft4<C, N, T, -1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
-    if constexpr (MODE == COL_H0) {
-        const double kx = S->dk[0] * kindex(act ? x : 0, n0);
+    fft4<C, N, T, -1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
+    const double kx = S->dk[0] * kindex(act ? x : 0, n0);
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int idx = t + T * m;
-            double ky, kz;
-            if constexpr (AXIS == 1) {
-                ky = S->dk[1] * kindex(idx, N);
-                kz = S->kap[2];
-            } else {
-                ky = S->dk[1] * kindex(other, n1);
-                kz = S->dk[2] * kindex(idx, N);
-            }
-            if (a.expo) apply_expo(v[0][m], v[1][m], v[2][m], v[3][m], kx, ky, kz, a.tau, S->inv_n);
-            else apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], (R)kx, (R)ky, (R)kz, (R)S->inv_n);
+    for (int m = 0; m < E; ++m) {
+        const int idx = t + T * m;
+        double ky, kz;
+        if constexpr (AXIS == 1) {
+            ky = S->dk[1] * kindex(idx, N);
+            kz = S->kap[2];
+        } else {
+            ky = S->dk[1] * kindex(other, n1);
+            kz = S->dk[2] * kindex(idx, N);
         }
+        if (a.expo) apply_expo(v[0][m], v[1][m], v[2][m], v[3][m], kx, ky, kz, a.tau, S->inv_n);
+        else apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], (R)kx, (R)ky, (R)kz, (R)S->inv_n);
     }
-    if constexpr (MODE == COL_INV || MODE == COL_H0) fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
+    fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
     if (act) {
         gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + base;
 #pragma unroll
@@ -827,6 +810,97 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
     }
 }
 
+// ------------------------------------------------------------------ whole-state transforms
+// Transforms of a state along one axis that mix no components: one component
+// per group of threads, with the row pass's lines and exchanges or the column
+// pass's tiles (one component per blockIdx.y).  They read a state once and write
+// it once, which is what bounds them where the state is large; a single small
+// state is bound by the launch, so more threads a line help there too.
+// PH: times exp(i k.x) before the transform (tables at a.ph2).
+//
+// Measured, one 320^3 state in single precision: x 0.36 ms (5.8 TB/s; 0.46 with
+// all four components in each thread and barriers), y 0.37, z 0.42 ms (5.0 TB/s;
+// 0.42 on average); 16 x 256 x 192 in double, x inverse 17 us (25), forward 20 (19).
+template <class R, int N, int DIR, bool PH>
+__global__ void __launch_bounds__((RdVar<R, N>::THREADS)) row_t_kernel(PassArgs a) {
+    using C = cpx<R>;
+    using VC = RdVar<R, N>;
+    constexpr int T = VC::T;
+    constexpr int E = VC::E;
+    using PL = typename VC::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH);
+    const int tid = threadIdx.x;
+    const int t = tid % T, q = tid / T % 4, line = tid / VC::LT;
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const sptr<SolveDev> S = uni(a.solves + (int)(unsigned)item);
+    const int row0 = (int)(item >> 32) * VC::ROWS;
+    const bool act = row0 + line < S->nrows;
+    const int row = row0 + (act ? line : 0);
+    const long long at = q * S->nsites + (long long)row * N + t;
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
+    for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S->twp[0] + i);
+    C v[E];
+    {
+        gptr<const nv2<R>> p = cview<R>(S->buf[a.src]) + at;
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = gload_nt<C>(p, T * m);
+    }
+    if constexpr (PH) {
+        const int n1 = S->n[1];
+        const C pyz = cmul(gload<C>(ctab, a.ph2 + N + row % n1), gload<C>(ctab, a.ph2 + N + n1 + row / n1));
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = cmul(v[m], cmul(gload<C>(ctab, a.ph2 + t + T * m), pyz));
+    }
+    __syncthreads();   // the twiddles
+    fft_row<C, N, DIR, true, PL>(v, reinterpret_cast<R*>(smem_raw) + (4 * line + q) * VC::STRIDE, t, tw);
+    if (act) {
+        gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + at;
+#pragma unroll
+        for (int m = 0; m < E; ++m) gstore_nt<C>(p, T * m, v[m]);
+    }
+}
+
+// Along z tiles of two lines up to 512 points (320^3 in
+// single precision 0.42 ms, one line 0.45); along y one, since a single (2+1)D
+// state has few tiles (256 x 192 in double 5.1 us, two lines 5.7; 320^3 0.37 either way).
+constexpr int col_t_tile(int axis, int n) { return axis == 2 && n <= 512 ? 1 : 0; }
+template <class R, int N, int AXIS, int DIR>
+__global__ void __launch_bounds__((CdVar<R, N, col_t_tile(AXIS, N)>::THREADS)) col_t_kernel(PassArgs a) {
+    using C = cpx<R>;
+    using VC = CdVar<R, N, col_t_tile(AXIS, N)>;
+    constexpr int T = VC::T;
+    constexpr int W = VC::W;
+    constexpr int E = VC::E;
+    using PL = typename VC::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C* tw = reinterpret_cast<C*>(smem_raw + VC::XCH);
+    const int tid = threadIdx.x, xl = tid % W, t = tid / W;
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const int ty = (int)(item >> 32);
+    const sptr<SolveDev> S = uni(a.solves + (int)(unsigned)item);
+    const int n0 = S->n[0], n1 = S->n[1];
+    const int ntx = (n0 + W - 1) / W;
+    const unsigned stride = AXIS == 1 ? (unsigned)n0 : (unsigned)n0 * (unsigned)n1;
+    const int other = __builtin_amdgcn_readfirstlane(ty / ntx), x0 = (ty - other * ntx) * W;
+    const bool act = x0 + xl < n0;
+    const long long base = x0 + (AXIS == 1 ? (long long)other * n0 * n1 : (long long)other * n0);
+    const unsigned off = (unsigned)(t * stride + (act ? xl : 0)) * (unsigned)sizeof(C);
+    gptr<const char> pd = (gptr<const char>)(cview<R>(S->buf[a.dst]) + (base + (int)blockIdx.y * S->nsites));
+    const long long step = (long long)T * stride * (long long)sizeof(C);
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
+    for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S->twp[AXIS] + i);
+    C v[E];
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = gload_at<C>(scalar_base(pd + m * step), off);
+    if constexpr (T * W <= 64) __syncthreads();   // the twiddles
+    fft_col<C, N, DIR, W, VC::SPLIT, PL>(v, smem_raw + xl * VC::XB, t, tw);
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) gstore_at((gptr<char>)scalar_base(pd + m * step), off, v[m]);
+    }
+}
+
 // ------------------------------------------------------------------ 1D whole-loop kernel
 // A (1+1)D solve is one line of at most 1024 points: its whole state fits on
 // one compute unit.  line_kernel runs a.nsteps complete RK4 steps of one solve
@@ -1101,16 +1175,19 @@ __global__ void __launch_bounds__((LineVar<R, N>::THREADS)) line_kernel(PassArgs
 // Kernel table of one (precision, N) instantiation.
 struct RowVariant { const void* stage[4]; const void* dp5[6]; int threads, rows; size_t lds; };   // RK4 / Dormand-Prince stages
 struct CdVariant { const void* fn[2]; int threads, w; size_t lds; };   // [axis - 1]: y writes G, z adds to it
-struct ColVariant { const void* fn[2][3]; int threads, w; size_t lds; };
+struct ColVariant { const void* fn[2]; int threads, w; size_t lds; };   // [axis - 1]
 struct StepRadices { int n, r[8]; };   // a plan's radices
 struct SizeKernels {
     StepRadices row_plan, col_plan;   // of the stepping passes (their twiddle tables' order)
     RowVariant row;                // the stage row pass
     CdVariant cd[NVAR];            // the stepping column passes, by variant
-    const void* row_other[ROW_NMODES];  // whole-state row modes
+    const void* row_t[3];          // whole-state transforms along x: forward, forward with a phase, inverse
+    const void* col_t[2][2];       // along y, z: forward, inverse
+    int col_tv[2];                 // and the stepping variant whose tiles these have
+    const void* row_other[ROW_NMODES];  // whole-state row modes that mix components
     int row0_threads, row0_rows;
     size_t row0_lds;
-    ColVariant col;                // whole-state column transforms
+    ColVariant col;                // last axis with -i H0 or the free evolution
     const void* line;              // 1D whole-loop kernel
     int line_threads;
     size_t line_lds;               // its dynamic LDS without the profiles of terms beyond LINE_TERMS
@@ -1141,12 +1218,8 @@ template <class R, int N, int V>
 ColVariant make_col_variant() {
     using VC = ColVar<R, N, V>;
     ColVariant c;
-    c.fn[0][COL_FWD] = (const void*)col_kernel<R, N, V, COL_FWD, 1>;
-    c.fn[0][COL_INV] = (const void*)col_kernel<R, N, V, COL_INV, 1>;
-    c.fn[0][COL_H0] = (const void*)col_kernel<R, N, V, COL_H0, 1>;
-    c.fn[1][COL_FWD] = (const void*)col_kernel<R, N, V, COL_FWD, 2>;
-    c.fn[1][COL_INV] = (const void*)col_kernel<R, N, V, COL_INV, 2>;
-    c.fn[1][COL_H0] = (const void*)col_kernel<R, N, V, COL_H0, 2>;
+    c.fn[0] = (const void*)col_kernel<R, N, V, 1>;
+    c.fn[1] = (const void*)col_kernel<R, N, V, 2>;
     c.threads = VC::THREADS;
     c.w = VC::W;
     c.lds = VC::BYTES;
@@ -1170,11 +1243,19 @@ SizeKernels make_size_kernels() {
     k.cd[2] = make_cd_variant<R, N, 2>();
     // whole-state column transforms: the few-points plan where there is one
     k.col = make_col_variant<R, N, (N >= 256 && has_small_plan<N>()) ? 2 : 0>();
-    k.row_other[ROW_FWD] = (const void*)row_kernel<R, N, 0, ROW_FWD, 0>;
+    k.row_t[0] = (const void*)row_t_kernel<R, N, -1, false>;
+    k.row_t[1] = (const void*)row_t_kernel<R, N, -1, true>;
+    k.row_t[2] = (const void*)row_t_kernel<R, N, +1, false>;
+    k.col_t[0][0] = (const void*)col_t_kernel<R, N, 1, -1>;
+    k.col_t[0][1] = (const void*)col_t_kernel<R, N, 1, +1>;
+    k.col_t[1][0] = (const void*)col_t_kernel<R, N, 2, -1>;
+    k.col_t[1][1] = (const void*)col_t_kernel<R, N, 2, +1>;
+    k.col_tv[0] = col_t_tile(1, N);
+    k.col_tv[1] = col_t_tile(2, N);
+    k.row_other[ROW_FWD] = k.row_other[ROW_FWDPH] = nullptr;
     k.row_other[ROW_STAGE] = nullptr;
     k.row_other[ROW_INV] = (const void*)row_kernel<R, N, 0, ROW_INV, 0>;
     k.row_other[ROW_RHS] = (const void*)row_kernel<R, N, 0, ROW_RHS, 0>;
-    k.row_other[ROW_FWDPH] = (const void*)row_kernel<R, N, 0, ROW_FWDPH, 0>;
     k.row_other[ROW_SRC] = (const void*)row_kernel<R, N, 0, ROW_SRC, 0>;
     k.row0_threads = RowVar<R, N, 0>::THREADS;
     k.row0_rows = RowVar<R, N, 0>::ROWS;
