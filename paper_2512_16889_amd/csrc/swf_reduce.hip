@@ -210,6 +210,14 @@ __global__ void __launch_bounds__(RED_THREADS) xspace_diag_kernel(RedArgs a) {
 // the group is summed; the vertices take theirs.  Sites are visited in a fixed
 // grid-stride order with 32-bit coordinates advanced by carries (a lattice has
 // at most 1024^3 = 2^30 sites).
+//
+// What bounds it: reading the states, on a large lattice.  The next site's states
+// are in flight while this one's products are formed (two waves per SIMD): 8 x
+// 320^3 in single precision 1.61 ms (5.2 TB/s; 1.76 without), 4 x 192 x 192 x 256
+// in double 0.40 ms (6.0 TB/s; 0.58).  On a line of 512 points the chain from
+// descriptors to states to block sums: uniform descriptors as scalar loads, time
+// factors formed while the states arrive and sums that halve the lanes' values
+// take 5.8 us; vector loads, factors at the end and a butterfly per value took 9.4.
 // s += conj(a) b and s += a b, four fused multiply-adds each
 __device__ __forceinline__ void cmac_conj(double2& s, double2 a, double2 b) {
     s.x = fma(a.x, b.x, s.x);
@@ -236,117 +244,164 @@ __device__ __forceinline__ void gam_eps_fma(const double2 (&p)[4], double2 (&o)[
     }
 }
 
+// Sums of V doubles per lane over a wave: while the count is even, each half of
+// the lanes keeps one half of the values (V / 2 exchanges instead of V), the
+// rest are added in a butterfly.  Lane `l` ends with value kept(l) + i in v[i],
+// i < LEFT.
+template <int V, int OFF = 32> struct WaveSums {
+    static constexpr bool HALVE = V % 2 == 0 && OFF > 0;
+    using Next = WaveSums<HALVE ? V / 2 : V, OFF / 2>;
+    static constexpr int LEFT = Next::LEFT;
+    // lanes that differ in these bits hold the same sums
+    static constexpr int SAME = Next::SAME | (HALVE ? 0 : OFF);
+    static __device__ __forceinline__ int kept(int lane) {
+        return (HALVE && (lane & OFF) ? V / 2 : 0) + Next::kept(lane);
+    }
+    static __device__ __forceinline__ void run(double* v, int lane) {
+        if constexpr (HALVE) {
+#pragma unroll
+            for (int i = 0; i < V / 2; ++i) {
+                const bool up = lane & OFF;
+                const double keep = up ? v[i + V / 2] : v[i], give = up ? v[i] : v[i + V / 2];
+                v[i] = keep + __shfl_xor(give, OFF, 64);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < V; ++i) v[i] += __shfl_xor(v[i], OFF, 64);
+        }
+        Next::run(v, lane);
+    }
+};
+template <int V> struct WaveSums<V, 0> {
+    static constexpr int LEFT = V, SAME = 0;
+    static __device__ __forceinline__ int kept(int) { return 0; }
+    static __device__ __forceinline__ void run(double*, int) {}
+};
+
 template <class R, int NU, int NV>
 __global__ void __launch_bounds__(RED_THREADS) bw_stage_kernel(BwArgs a) {
     using C = cpx<R>;
     constexpr int NP = NU * NV;
-    const VertexGroupDev* G = a.groups + blockIdx.y;
+    const sptr<VertexGroupDev> G = uni(a.groups + blockIdx.y);
     const int role = a.stage == 0 ? BUF_Y : BUF_YS;
-    const C* ctab = reinterpret_cast<const C*>(a.ctab);
-    const SolveDev* S0 = a.solves + G->su[0];
+    const sptr<SolveDev> S0 = uni(a.solves + G->su[0]);
     const unsigned n0 = (unsigned)S0->n[0], n1 = (unsigned)S0->n[1];
     const unsigned ns = (unsigned)S0->nsites;
-    gptr<const nv2<R>> Up[NU], Vp[NV];
-    const C* T1[NU];
-    const C* T2[NV];
+    // (a launch has as many workgroups as its largest lattice takes)
+    const unsigned nblk = (unsigned)bw_blocks(ns, a.nblk);
+    if (blockIdx.x >= nblk) return;
+    // the states, U solves first
+    gptr<const nv2<R>> st[NU + NV];
+    gptr<const nv2<R>> T1[NU], T2[NV];
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        Up[u] = cview<R>(a.solves[G->su[u]].buf[role]);
+        st[u] = cview<R>(uni(a.solves + G->su[u])->buf[role]);
         T1[u] = ctab + G->t1[u];
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        Vp[v] = cview<R>(a.solves[G->sv[v]].buf[role]);
+        st[NU + v] = cview<R>(uni(a.solves + G->sv[v])->buf[role]);
         T2[v] = ctab + G->t2[v];
     }
-    const C* TK = ctab + G->tk;
+    gptr<const nv2<R>> TK = ctab + G->tk;
     const double e0 = G->eps[0], e1 = G->eps[1], e2 = G->eps[2];
-    double acc[NP][3][2];
+    double acc[NP * 6];   // [pair][term][re, im]
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[p][c][0] = acc[p][c][1] = 0.0;
-    // (a launch has as many workgroups as its largest lattice takes)
-    const unsigned nblk = (unsigned)bw_blocks(ns, a.nblk);
-    if (blockIdx.x >= nblk) return;
+    for (int p = 0; p < NP * 6; ++p) acc[p] = 0.0;
+    const int tid = threadIdx.x;
     const unsigned stride = nblk * RED_THREADS;
-    unsigned i = blockIdx.x * RED_THREADS + threadIdx.x;
+    unsigned i = blockIdx.x * RED_THREADS + tid;
     unsigned x = i % n0, y = (i / n0) % n1, z = (i / n0) / n1;
     const unsigned sx = stride % n0, sy = (stride / n0) % n1, sz = (stride / n0) / n1;
-    for (; i < ns; i += stride) {
-        const unsigned iy = n0 + y, iz = n0 + n1 + z;
-        // V side: (alpha.eps) V_scat of each V solve, and its (s,b) factor
-        double2 gy[NV][4], f2[NV];
+    C w[NU + NV][4];
+    auto load = [&](unsigned at) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            double2 yv[4];
+        for (int s = 0; s < NU + NV; ++s)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) yv[q] = todbl(gload_nt<C>(Vp[v], (long long)q * ns + i));
-            gam_eps_fma(yv, gy[v], e0, e1, e2);
-            f2[v] = todbl(cmul(cmul(T2[v][x], T2[v][iy]), T2[v][iz]));
-        }
-        const double2 f0 = todbl(cmul(cmul(TK[x], TK[iy]), TK[iz]));
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            double2 yu[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) yu[q] = todbl(gload_nt<C>(Up[u], (long long)q * ns + i));
-            const double2 f1 = todbl(cmul(cmul(T1[u][x], T1[u][iy]), T1[u][iz]));
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                double2 ss = d2(0, 0), bs = d2(0, 0), sb = d2(0, 0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    cmac_conj(ss, yu[q], gy[v][q]);
-                    cmac_conj(bs, d2(G->cu[u][2 * q], G->cu[u][2 * q + 1]), gy[v][q]);
-                    cmac_conj(sb, yu[q], d2(G->cv[v][2 * q], G->cv[v][2 * q + 1]));
-                }
-                double (&A)[3][2] = acc[u * NV + v];
-                cmac(A[0][0], A[0][1], f0, ss);
-                cmac(A[1][0], A[1][1], f1, bs);
-                cmac(A[2][0], A[2][1], f2[v], sb);
-            }
-        }
-        x += sx;
-        y += sy;
-        z += sz;
-        if (x >= n0) { x -= n0; ++y; }
-        if (y >= n1) { y -= n1; ++z; }
-    }
-    // block sums of the 3 terms of every pair: a fixed butterfly within each
-    // wave, then the waves in order; times the terms' time factors; partials
-    // layout [vertex][stage][block][3]
-    constexpr int NT = 3 * NP;
-    constexpr int NW = RED_THREADS / 64;
-    __shared__ double2 shw[NW][NT];
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double2 s = d2(acc[p][c][0], acc[p][c][1]);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                s.x += __shfl_down(s.x, off, 64);
-                s.y += __shfl_down(s.y, off, 64);
-            }
-            if (lane == 0) shw[wave][3 * p + c] = s;
-        }
-    __syncthreads();
+            for (int q = 0; q < 4; ++q) w[s][q] = gload_nt<C>(st[s], (long long)q * ns + at);
+    };
+    if (i < ns) load(i);
+    // the time factor this thread applies at the end, while the first sites arrive
+    double2 tf = d2(0, 0);
     if (tid < 3 * G->nvx) {
         const int j = tid / 3, c = tid % 3;
-        const int p = G->ui[j] * NV + G->vi[j];
-        double2 s = shw[0][3 * p + c];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) s = dadd(s, shw[w][3 * p + c]);
-        const double ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - a.cst * a.dt;
+        const double ts = a.t_out - (double)(*uni(a.step) + a.step_add) * a.dt - a.cst * a.dt;
         // phase of the term: -(k0 + [E_V]) t for (s,s) / (s,b), (E_U - k0) t for (b,s)
         double w = -a.verts[G->vtx[0]].k0;
         if (c == 1) w += a.solves[G->su[G->ui[j]]].E;
         if (c == 2) w -= a.solves[G->sv[G->vi[j]]].E;
         double sn, cs;
         sincos(w * ts, &sn, &cs);
-        a.part[(((long long)G->vtx[j] * a.nst + a.stage) * a.nblk + blockIdx.x) * 3 + c] = dmul(d2(cs, sn), s);
+        tf = d2(cs, sn);
+    }
+    for (; i < ns; i += stride) {
+        const unsigned iy = n0 + y, iz = n0 + n1 + z;
+        auto factor = [&](gptr<const nv2<R>> T) {
+            return todbl(cmul(cmul(gload<C>(T, x), gload<C>(T, iy)), gload<C>(T, iz)));
+        };
+        const double2 f0 = factor(TK);
+        double2 f1[NU], f2[NV];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) f1[u] = factor(T1[u]);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) f2[v] = factor(T2[v]);
+        // V side: (alpha.eps) V_scat of each V solve
+        double2 yu[NU][4], gy[NV][4];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            double2 yv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) yv[q] = todbl(w[NU + v][q]);
+            gam_eps_fma(yv, gy[v], e0, e1, e2);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) yu[u][q] = todbl(w[u][q]);
+        if (i + stride < ns) load(i + stride);   // the next site's states
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                double2 ss = d2(0, 0), bs = d2(0, 0), sb = d2(0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    cmac_conj(ss, yu[u][q], gy[v][q]);
+                    cmac_conj(bs, d2(G->cu[u][2 * q], G->cu[u][2 * q + 1]), gy[v][q]);
+                    cmac_conj(sb, yu[u][q], d2(G->cv[v][2 * q], G->cv[v][2 * q + 1]));
+                }
+                double* A = acc + 6 * (u * NV + v);
+                cmac(A[0], A[1], f0, ss);
+                cmac(A[2], A[3], f1[u], bs);
+                cmac(A[4], A[5], f2[v], sb);
+            }
+        x += sx;
+        y += sy;
+        z += sz;
+        if (x >= n0) { x -= n0; ++y; }
+        if (y >= n1) { y -= n1; ++z; }
+    }
+    // block sums of the 3 terms of every pair: within each wave, then the waves
+    // in order; times the terms' time factors; partials layout
+    // [vertex][stage][block][3]
+    constexpr int NW = RED_THREADS / 64;
+    using Sums = WaveSums<6 * NP>;
+    __shared__ double shw[NW][6 * NP];
+    const int lane = tid % 64, wave = tid / 64;
+    Sums::run(acc, lane);
+    if ((lane & Sums::SAME) == 0) {
+#pragma unroll
+        for (int k = 0; k < Sums::LEFT; ++k) shw[wave][Sums::kept(lane) + k] = acc[k];
+    }
+    __syncthreads();
+    if (tid < 3 * G->nvx) {
+        const int j = tid / 3, c = tid % 3;
+        const int p = 2 * (3 * (G->ui[j] * NV + G->vi[j]) + c);
+        double2 s = d2(shw[0][p], shw[0][p + 1]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s = dadd(s, d2(shw[w][p], shw[w][p + 1]));
+        a.part[(((long long)G->vtx[j] * a.nst + a.stage) * a.nblk + blockIdx.x) * 3 + c] = dmul(tf, s);
     }
 }
 
