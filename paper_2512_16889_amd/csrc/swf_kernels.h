@@ -901,6 +901,105 @@ __global__ void __launch_bounds__((CdVar<R, N, col_t_tile(AXIS, N)>::THREADS)) c
     }
 }
 
+// Forward transform along the last axis, -i H0 / N or the free evolution, and
+// back: one component per group of threads for the transforms, whole sites (a
+// quarter of them a thread) for the multiply, which mixes components; real and
+// imaginary parts cross the LDS one after the other.
+//
+// With all four components in each thread (col_kernel) a batch of 50 MB in
+// double leaves one wave per SIMD, which waits for its own loads, sincos and
+// barriers.  Microseconds here and there, 256 columns x N, 3072 / N solves, in
+// double / single precision:  32: 15 / 12 (29 / 14), 64: 24 / 15 (34 / 18),
+// 80: 26 / 18 (126 / 32), 160: 37 / 34 (70 / 37), 192: 31 / 22 (40 / 27),
+// 320: 56 / 36 (73 / 38), 384 in double: 37 (47).  No better, and left to
+// col_kernel: powers of two from 128 (double 31 (29) at 128 and 46 (45) at 256
+// points, single precision 28 (21) at 128: the other plan is already at 8 points
+// a thread), 384 in single precision (42 (32): 1024 threads of 24 points), and
+// what does not fit a workgroup with whole 128-byte lines.
+template <class R, int N> struct HdVar {
+    using CV = CdVar<R, N, 0>;
+    static constexpr int T = CV::T, W = CV::W, E = CV::E;
+    static constexpr int THREADS = 4 * T * W;
+    static constexpr size_t COMP = (size_t)N * W * sizeof(R);
+    static constexpr size_t BYTES = 4 * COMP + N * sizeof(cpx<R>);
+    static constexpr bool FITS = THREADS <= 1024 && BYTES <= 163840 && E % 4 == 0 &&
+                                 ((N & (N - 1)) == 0 ? N <= 64 : THREADS <= 512 || E <= 20);
+};
+
+template <class R, int N, int AXIS>
+__global__ void __launch_bounds__((HdVar<R, N>::THREADS)) col_h0_kernel(PassArgs a) {
+    using C = cpx<R>;
+    using VC = HdVar<R, N>;
+    constexpr int T = VC::T;
+    constexpr int W = VC::W;
+    constexpr int E = VC::E;
+    constexpr int SITES = E / 4;
+    using PL = typename VC::CV::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C* tw = reinterpret_cast<C*>(smem_raw + 4 * VC::COMP);
+    const int tid = threadIdx.x, xl = tid % W, t = tid / W % T, q = tid / (W * T);
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const int ty = (int)(item >> 32);
+    const sptr<SolveDev> S = uni(a.solves + (int)(unsigned)item);
+    const int n0 = S->n[0], n1 = S->n[1];
+    const int ntx = (n0 + W - 1) / W;
+    const unsigned stride = AXIS == 1 ? (unsigned)n0 : (unsigned)n0 * (unsigned)n1;
+    const int other = __builtin_amdgcn_readfirstlane(ty / ntx), x0 = (ty - other * ntx) * W;
+    const bool act = x0 + xl < n0;
+    const int x = act ? x0 + xl : x0;
+    gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + (x + (AXIS == 1 ? (long long)other * n0 * n1 : (long long)other * n0) +
+                                              q * S->nsites + (long long)t * stride);
+    const long long step = (long long)T * stride;
+    gptr<const nv2<R>> ctab = cview<R>(a.ctab);
+    for (int i = tid; i < N; i += VC::THREADS) tw[i] = gload<C>(ctab, S->twp[AXIS] + i);
+    C v[E];
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = gload<C>(p, m * step);
+    if constexpr (T * W <= 64) __syncthreads();   // the twiddles
+    unsigned char* col = smem_raw + q * VC::COMP + xl * sizeof(R);
+    fft_col<C, N, -1, W, true, PL>(v, col, t, tw);
+    // ---- to whole sites t + T (q + 4 j), the multiply, and back to components
+    R* xs = reinterpret_cast<R*>(smem_raw) + t * W + xl;
+    constexpr int COMP = N * W, LINE = T * W;
+    C d[SITES][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < E; ++m) xs[q * COMP + m * LINE] = h ? v[m].y : v[m].x;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SITES; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) (h ? d[j][c].y : d[j][c].x) = xs[c * COMP + (q + 4 * j) * LINE];
+    }
+    const double kx = S->dk[0] * kindex(x, n0);
+#pragma unroll
+    for (int j = 0; j < SITES; ++j) {
+        const int idx = t + T * (q + 4 * j);
+        const double ky = S->dk[1] * (AXIS == 1 ? kindex(idx, N) : kindex(other, n1));
+        const double kz = AXIS == 1 ? S->kap[2] : S->dk[2] * kindex(idx, N);
+        if (a.expo) apply_expo(d[j][0], d[j][1], d[j][2], d[j][3], kx, ky, kz, a.tau, S->inv_n);
+        else apply_h0(d[j][0], d[j][1], d[j][2], d[j][3], (R)kx, (R)ky, (R)kz, (R)S->inv_n);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SITES; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) xs[c * COMP + (q + 4 * j) * LINE] = h ? d[j][c].y : d[j][c].x;
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < E; ++m) (h ? v[m].y : v[m].x) = xs[q * COMP + m * LINE];
+    }
+    fft_col<C, N, +1, W, true, PL>(v, col, t, tw);
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) gstore<C>(p, m * step, v[m]);
+    }
+}
+
 // ------------------------------------------------------------------ 1D whole-loop kernel
 // A (1+1)D solve is one line of at most 1024 points: its whole state fits on
 // one compute unit.  line_kernel runs a.nsteps complete RK4 steps of one solve
@@ -1214,15 +1313,25 @@ CdVariant make_cd_variant() {
     c.lds = VC::BYTES;
     return c;
 }
-template <class R, int N, int V>
+template <class R, int N>
 ColVariant make_col_variant() {
-    using VC = ColVar<R, N, V>;
     ColVariant c;
-    c.fn[0] = (const void*)col_kernel<R, N, V, 1>;
-    c.fn[1] = (const void*)col_kernel<R, N, V, 2>;
-    c.threads = VC::THREADS;
-    c.w = VC::W;
-    c.lds = VC::BYTES;
+    if constexpr (HdVar<R, N>::FITS) {
+        using VC = HdVar<R, N>;
+        c.fn[0] = (const void*)col_h0_kernel<R, N, 1>;
+        c.fn[1] = (const void*)col_h0_kernel<R, N, 2>;
+        c.threads = VC::THREADS;
+        c.w = VC::W;
+        c.lds = VC::BYTES;
+    } else {
+        constexpr int V = N >= 256 && has_small_plan<N>() ? 2 : 0;   // the few-points plan where there is one
+        using VC = ColVar<R, N, V>;
+        c.fn[0] = (const void*)col_kernel<R, N, V, 1>;
+        c.fn[1] = (const void*)col_kernel<R, N, V, 2>;
+        c.threads = VC::THREADS;
+        c.w = VC::W;
+        c.lds = VC::BYTES;
+    }
     return c;
 }
 
@@ -1241,8 +1350,7 @@ SizeKernels make_size_kernels() {
     k.cd[0] = make_cd_variant<R, N, 0>();
     k.cd[1] = make_cd_variant<R, N, 1>();
     k.cd[2] = make_cd_variant<R, N, 2>();
-    // whole-state column transforms: the few-points plan where there is one
-    k.col = make_col_variant<R, N, (N >= 256 && has_small_plan<N>()) ? 2 : 0>();
+    k.col = make_col_variant<R, N>();
     k.row_t[0] = (const void*)row_t_kernel<R, N, -1, false>;
     k.row_t[1] = (const void*)row_t_kernel<R, N, -1, true>;
     k.row_t[2] = (const void*)row_t_kernel<R, N, +1, false>;

@@ -40,3 +40,18 @@ def test_every_length_along_each_axis(S, n, axis):
             for op, ref in ((0, fwd), (1, kin)):
                 err = np.abs(ctx.apply_op(op, 0, psi) - ref).max() / np.abs(ref).max()
                 assert err < tol, (shape, prec, op, err)
+
+
+@pytest.mark.parametrize("n", LENGTHS)
+def test_kinetic_term_in_two_dimensions(S, n):
+    """y is the last axis here: its pass multiplies by H0 between the transforms."""
+    shape = [40, n]
+    grid = W.Grid(2, shape + [1], [m / 4.0 for m in shape] + [1.0])
+    field = [[W.Term(0, 0.3, W.gauss(1.0), [W.sech2(3.0), W.const(), W.const()])]]
+    prob = W.Problem("transforms", [grid], field, [W.Solve(W.U_OUT, 1, [0.3, -0.2, 0.4])], W.Window(-1.0, 1.0, 0.05))
+    psi = W.random_state([4] + shape, seed=4)
+    ref = SWFSolve(prob, 0).kinetic(psi)
+    for prec, tol in TOL.items():
+        with S.Context(prob, precision=prec) as ctx:
+            err = np.abs(ctx.apply_op(1, 0, psi) - ref).max() / np.abs(ref).max()
+            assert err < tol, (shape, prec, err)
