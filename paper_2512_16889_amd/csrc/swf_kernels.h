@@ -816,12 +816,12 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
 // pass's tiles (one component per blockIdx.y).  They read a state once and write
 // it once, which is what bounds them where the state is large; a single small
 // state is bound by the launch, so more threads a line help there too.
-// PH: times exp(i k.x) before the transform (tables at a.ph2).
+// PH: times exp(i k.x) before the transform (tables at a.ph2).  NT: past the caches.
 //
 // Measured, one 320^3 state in single precision: x 0.36 ms (5.8 TB/s; 0.46 with
 // all four components in each thread and barriers), y 0.37, z 0.42 ms (5.0 TB/s;
 // 0.42 on average); 16 x 256 x 192 in double, x inverse 17 us (25), forward 20 (19).
-template <class R, int N, int DIR, bool PH>
+template <class R, int N, int DIR, bool PH, bool NT>
 __global__ void __launch_bounds__((RdVar<R, N>::THREADS)) row_t_kernel(PassArgs a) {
     using C = cpx<R>;
     using VC = RdVar<R, N>;
@@ -844,7 +844,7 @@ __global__ void __launch_bounds__((RdVar<R, N>::THREADS)) row_t_kernel(PassArgs 
     {
         gptr<const nv2<R>> p = cview<R>(S->buf[a.src]) + at;
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[m] = gload_nt<C>(p, T * m);
+        for (int m = 0; m < E; ++m) v[m] = NT ? gload_nt<C>(p, T * m) : gload<C>(p, T * m);
     }
     if constexpr (PH) {
         const int n1 = S->n[1];
@@ -857,7 +857,7 @@ __global__ void __launch_bounds__((RdVar<R, N>::THREADS)) row_t_kernel(PassArgs 
     if (act) {
         gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + at;
 #pragma unroll
-        for (int m = 0; m < E; ++m) gstore_nt<C>(p, T * m, v[m]);
+        for (int m = 0; m < E; ++m) NT ? gstore_nt<C>(p, T * m, v[m]) : gstore<C>(p, T * m, v[m]);
     }
 }
 
@@ -1280,7 +1280,7 @@ struct SizeKernels {
     StepRadices row_plan, col_plan;   // of the stepping passes (their twiddle tables' order)
     RowVariant row;                // the stage row pass
     CdVariant cd[NVAR];            // the stepping column passes, by variant
-    const void* row_t[3];          // whole-state transforms along x: forward, forward with a phase, inverse
+    const void* row_t[3][2];       // whole-state transforms along x: forward, forward with a phase, inverse; cached or streaming
     const void* col_t[2][2];       // along y, z: forward, inverse
     int col_tv[2];                 // and the stepping variant whose tiles these have
     const void* row_other[ROW_NMODES];  // whole-state row modes that mix components
@@ -1351,9 +1351,12 @@ SizeKernels make_size_kernels() {
     k.cd[1] = make_cd_variant<R, N, 1>();
     k.cd[2] = make_cd_variant<R, N, 2>();
     k.col = make_col_variant<R, N>();
-    k.row_t[0] = (const void*)row_t_kernel<R, N, -1, false>;
-    k.row_t[1] = (const void*)row_t_kernel<R, N, -1, true>;
-    k.row_t[2] = (const void*)row_t_kernel<R, N, +1, false>;
+    k.row_t[0][0] = (const void*)row_t_kernel<R, N, -1, false, false>;
+    k.row_t[0][1] = (const void*)row_t_kernel<R, N, -1, false, true>;
+    k.row_t[1][0] = (const void*)row_t_kernel<R, N, -1, true, false>;
+    k.row_t[1][1] = (const void*)row_t_kernel<R, N, -1, true, true>;
+    k.row_t[2][0] = (const void*)row_t_kernel<R, N, +1, false, false>;
+    k.row_t[2][1] = (const void*)row_t_kernel<R, N, +1, false, true>;
     k.col_t[0][0] = (const void*)col_t_kernel<R, N, 1, -1>;
     k.col_t[0][1] = (const void*)col_t_kernel<R, N, 1, +1>;
     k.col_t[1][0] = (const void*)col_t_kernel<R, N, 2, -1>;

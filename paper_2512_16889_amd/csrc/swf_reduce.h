@@ -137,6 +137,7 @@ struct IpArgs {
     const void* consts;  // StageConst per solve and stage
     int nst;
     double h;            // the signed step
+    int stream;          // non-temporal loads and stores
 };
 hipError_t launch_ip_point(int fp64, int mode, const IpArgs& a, int nitems, hipStream_t st);
 

@@ -892,7 +892,7 @@ struct IpSite {
 // Breit-Wheeler sums.  HBM-bound: 2 + 4 + 3 array traversals a step, where a
 // source pass and a combination pass per slope took 27 (16 solves of 256 x 192
 // in double: 270 us a step).
-template <class R, int MODE>
+template <class R, int MODE, bool NT>
 __global__ void __launch_bounds__(RED_THREADS) ip_point_kernel(IpArgs a) {
     using C = cpx<R>;
     const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
@@ -906,6 +906,8 @@ __global__ void __launch_bounds__(RED_THREADS) ip_point_kernel(IpArgs a) {
     const long long tile = (long long)row0 * n0;
     gptr<const nv2<R>> pY = cview<R>(S->buf[BUF_Y]) + tile, pYS = cview<R>(S->buf[BUF_YS]) + tile, pA = cview<R>(S->buf[BUF_ACC]) + tile;
     gptr<nv2<R>> wY = wview<R>(S->buf[BUF_Y]) + tile, wYS = wview<R>(S->buf[BUF_YS]) + tile, wA = wview<R>(S->buf[BUF_ACC]) + tile;
+    auto ld = [&](gptr<const nv2<R>> p, long long i) { return NT ? gload_nt<C>(p, i) : gload<C>(p, i); };
+    auto st = [&](gptr<nv2<R>> p, long long i, C c) { NT ? gstore_nt<C>(p, i, c) : gstore<C>(p, i, c); };
     const R h = (R)a.h, h2 = (R)(0.5 * a.h), h6 = (R)(a.h / 6.0), h3 = (R)(a.h / 3.0), third = (R)(1.0 / 3.0);
     IpSite<R> site;
     site.S = S;
@@ -923,21 +925,21 @@ __global__ void __launch_bounds__(RED_THREADS) ip_point_kernel(IpArgs a) {
         C u[4], v[4], w[4], k[4];   // the arrays the mode reads
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            u[q] = gload_nt<C>(MODE == IP_FIRST ? pY : pYS, q * ns + e);
-            if constexpr (MODE == IP_MIDDLE || MODE == IP_SECOND || MODE == IP_THIRD) v[q] = gload_nt<C>(pY, q * ns + e);
-            if constexpr (MODE == IP_THIRD || MODE == IP_LAST) w[q] = gload_nt<C>(pA, q * ns + e);
+            u[q] = ld(MODE == IP_FIRST ? pY : pYS, q * ns + e);
+            if constexpr (MODE == IP_MIDDLE || MODE == IP_SECOND || MODE == IP_THIRD) v[q] = ld(pY, q * ns + e);
+            if constexpr (MODE == IP_THIRD || MODE == IP_LAST) w[q] = ld(pA, q * ns + e);
         }
         site.ph = cmul(gload<C>(ctab, S->ph + site.x), cmul(gload<C>(ctab, S->ph + n0 + site.yy), gload<C>(ctab, S->ph + n0 + n1 + site.zz)));
         site.slope(MODE == IP_FIRST ? 0 : MODE == IP_LAST ? 3 : MODE == IP_THIRD ? 2 : 1, u, k);
         if constexpr (MODE == IP_FIRST) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) gstore_nt<C>(wYS, q * ns + e, cadd(u[q], cscale(k[q], h2)));
+            for (int q = 0; q < 4; ++q) st(wYS, q * ns + e, cadd(u[q], cscale(k[q], h2)));
         } else if constexpr (MODE == IP_LAST) {
             const R mk = mask >= 0 ? rtab[mask + site.x] * rtab[mask + n0 + site.yy] * rtab[mask + n0 + n1 + site.zz] : (R)1;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const C o = cadd(w[q], cscale(k[q], h6));
-                gstore_nt<C>(wY, q * ns + e, mask >= 0 ? cscale(o, mk) : o);
+                st(wY, q * ns + e, mask >= 0 ? cscale(o, mk) : o);
             }
         } else {
             C b[4], acc[4];
@@ -955,29 +957,30 @@ __global__ void __launch_bounds__(RED_THREADS) ip_point_kernel(IpArgs a) {
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                gstore_nt<C>(wYS, q * ns + e, MODE == IP_SECOND ? b[q] : cadd(v[q], cscale(k[q], h)));
-                gstore_nt<C>(wA, q * ns + e, MODE == IP_SECOND ? acc[q] : cadd(acc[q], cscale(k[q], h3)));
+                st(wYS, q * ns + e, MODE == IP_SECOND ? b[q] : cadd(v[q], cscale(k[q], h)));
+                st(wA, q * ns + e, MODE == IP_SECOND ? acc[q] : cadd(acc[q], cscale(k[q], h3)));
             }
         }
     }
 }
 
-template <class R>
+template <class R, bool NT>
 static hipError_t launch_ip_point_t(int mode, const IpArgs& a, int n, hipStream_t st) {
     const dim3 g(n), b(RED_THREADS);
     switch (mode) {
-        case IP_FIRST: hipLaunchKernelGGL((ip_point_kernel<R, IP_FIRST>), g, b, 0, st, a); break;
-        case IP_MIDDLE: hipLaunchKernelGGL((ip_point_kernel<R, IP_MIDDLE>), g, b, 0, st, a); break;
-        case IP_SECOND: hipLaunchKernelGGL((ip_point_kernel<R, IP_SECOND>), g, b, 0, st, a); break;
-        case IP_THIRD: hipLaunchKernelGGL((ip_point_kernel<R, IP_THIRD>), g, b, 0, st, a); break;
-        case IP_LAST: hipLaunchKernelGGL((ip_point_kernel<R, IP_LAST>), g, b, 0, st, a); break;
+        case IP_FIRST: hipLaunchKernelGGL((ip_point_kernel<R, IP_FIRST, NT>), g, b, 0, st, a); break;
+        case IP_MIDDLE: hipLaunchKernelGGL((ip_point_kernel<R, IP_MIDDLE, NT>), g, b, 0, st, a); break;
+        case IP_SECOND: hipLaunchKernelGGL((ip_point_kernel<R, IP_SECOND, NT>), g, b, 0, st, a); break;
+        case IP_THIRD: hipLaunchKernelGGL((ip_point_kernel<R, IP_THIRD, NT>), g, b, 0, st, a); break;
+        case IP_LAST: hipLaunchKernelGGL((ip_point_kernel<R, IP_LAST, NT>), g, b, 0, st, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 hipError_t launch_ip_point(int fp64, int mode, const IpArgs& a, int nitems, hipStream_t st) {
-    if (nitems <= 0) return hipSuccess;
-    return fp64 ? launch_ip_point_t<double>(mode, a, nitems, st) : launch_ip_point_t<float>(mode, a, nitems, st);
+    if (a.stream)
+        return fp64 ? launch_ip_point_t<double, true>(mode, a, nitems, st) : launch_ip_point_t<float, true>(mode, a, nitems, st);
+    return fp64 ? launch_ip_point_t<double, false>(mode, a, nitems, st) : launch_ip_point_t<float, false>(mode, a, nitems, st);
 }
 
 hipError_t launch_finite_check(int fp64, const SolveDev* solves, int nsolves, int step, unsigned long long* flag,

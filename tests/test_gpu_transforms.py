@@ -55,3 +55,26 @@ def test_kinetic_term_in_two_dimensions(S, n):
         with S.Context(prob, precision=prec) as ctx:
             err = np.abs(ctx.apply_op(1, 0, psi) - ref).max() / np.abs(ref).max()
             assert err < tol, (shape, prec, err)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_batches_beyond_the_cache(S, prec):
+    """Whole-state passes over more than 128 MB stream past the caches: the
+    interaction-picture steps of four 1024^2 solves (268 MB, 134 MB in single
+    precision) are those of one, bit for bit (the same operations)."""
+    shape = [1024, 1024]
+    grid = W.Grid(2, shape + [1], [m / 4.0 for m in shape] + [1.0], absorb_cells=8, absorb_strength=0.2)
+    field = [[W.Term(0, 0.3, W.gauss(1.0), [W.sech2(3.0), W.const(), W.const()])]]
+    psi = W.random_state([4] + shape, seed=6)
+    out = []
+    for count in (1, 4):
+        solves = [W.Solve(W.U_OUT, 1, [0.3, -0.2, 0.4]) for _ in range(count)]
+        prob = W.Problem("stream", [grid], field, solves, W.Window(-1.0, 1.0, 0.05, "iprk4"))
+        with S.Context(prob, precision=prec) as ctx:
+            for i in range(count):
+                ctx.set_psi(i, psi, 0)
+            ctx.step(2)
+            out += [ctx.get_psi(i) for i in (0, count - 1)]
+    assert np.abs(out[0]).max() > 0
+    for other in out[1:]:
+        assert np.array_equal(out[0], other)
