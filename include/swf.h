@@ -165,8 +165,8 @@ typedef struct {
                                Anal. 4 (1967) 372): the free evolution exp(-i H0(k) h/2)
                                exact in Fourier space, the field terms -i V (psi_s +
                                psi_b) by the classical tableau; four free-evolution
-                               transforms of a whole state per step, four state arrays
-                               per solve, BW integrals with the RK4 weights over its
+                               transforms of a whole state per step, six state arrays
+                               per solve reserved, BW integrals with the RK4 weights over its
                                stage inputs; not with bw_partial or the persistent 1D
                                kernel                                                   */
     int graph_steps;        /* with use_graph: > 1 also captures that many consecutive
