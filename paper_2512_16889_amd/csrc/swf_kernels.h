@@ -51,6 +51,7 @@ struct PassArgs {
     double t_explicit;     // time of ROW_RHS
     long long ph2;         // ROW_FWDPH: complex offset of exp(i k_j x_j) tables
     int nitems;            // work items of this launch
+    int rev;               // stepping passes: the items in reverse order
     int step_add;          // steps enqueued since the device counter was last advanced
     const void* consts;    // StageConst per solve and stage of the current step (nst each)
     int nst;               // stages of the stepper
@@ -432,15 +433,19 @@ template <bool NT = true, class C> __device__ __forceinline__ void gstore_at(gpt
     else *(gptr<V2>)(base + off) = v;
 }
 
-// Column derivative pass: the blocks of blockIdx.y = q transform the
-// component alpha^j takes for output component q along axis j = AXIS (y or
-// z), multiply by k_j / n_j, transform back, and write (ACCUM = 0) or add
+// Column derivative pass: a block transforms the component alpha^j takes for
+// output component q of one tile along axis j = AXIS (y or z), multiply by k_j / n_j, transform back, and write (ACCUM = 0) or add
 // (ACCUM = 1) the result, with alpha^j's phase, into component q of the G
 // buffer (a.dst).  a.src: the stage input.  One component per thread: E
 // points of the transform in registers, exchanged through LDS: as real and
 // imaginary parts in turn where whole numbers would leave a compute unit room
 // for one workgroup (SPLIT), so that one's loads cover another's transform.
 //   v0, v1, v2: 1, 2, 4 lines of 128 bytes along x per tile.
+// The four components of a tile are neighbouring blocks along y; along z a
+// sweep over the tiles takes one component (blockIdx.y) after the other: y / z
+// 2.87 / 5.19 ms with neighbouring components, 3.02 / 5.04 component after
+// component (8 x 320^3 in single precision), 1.47 / 2.48 and 1.58 / 2.44 ms
+// (4 x 256^3 in double).
 // What bounds it: the access pattern, rows of a tile's width at the stride of
 // the axis.  More lines per row help while several tiles fit a compute unit:
 // 31 x 128^3 in single precision, y / z: 4.9 / 5.0 TB/s with one line, 6.1 / 5.8
@@ -496,9 +501,10 @@ __attribute__((amdgpu_waves_per_eu(CdVar<R, N, V>::template waves<ACCUM>(), 8)))
     const int tid = threadIdx.x;
     const int xl = tid % W;
     const int t = tid / W;
-    const int q = blockIdx.y;                       // output component
+    const int block = a.rev ? a.nitems - 1 - (int)blockIdx.x : (int)blockIdx.x;
+    const int q = AXIS == 1 ? block & 3 : (int)blockIdx.y;   // output component
     const int src = AXIS == 1 ? 3 - q : (q ^ 2);    // the component alpha^j takes
-    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const unsigned long long item = *(sptr<unsigned long long>)(a.items + (AXIS == 1 ? block >> 2 : block));
     const int solve = (int)(unsigned)item, ty = (int)(item >> 32);
     const sptr<SolveDev> S = uni(a.solves + solve);
     const int n0 = S->n[0], n1 = S->n[1];
@@ -625,7 +631,8 @@ __attribute__((amdgpu_waves_per_eu(RdVar<R, N>::WAVES, 8))) row_d_kernel(PassArg
     // (uniform over the wave where a line, or a component line, takes whole waves)
     const int q = T == 64 ? __builtin_amdgcn_readfirstlane(tid / T % 4) : tid / T % 4;
     const int line = LT >= 64 ? __builtin_amdgcn_readfirstlane(tid / LT) : tid / LT;
-    const unsigned long long item = *(sptr<unsigned long long>)(a.items + blockIdx.x);
+    const unsigned long long item =
+        *(sptr<unsigned long long>)(a.items + (a.rev ? a.nitems - 1 - (int)blockIdx.x : (int)blockIdx.x));
     const int solve = (int)(unsigned)item, ty = (int)(item >> 32);
     const sptr<SolveDev> S = uni(a.solves + solve);
     const int row0 = ty * ROWS;
