@@ -744,7 +744,7 @@ struct swf_ctx {
     char* arena = nullptr;
     bool own_arena = false;
     int step = 0;
-    int step_add = 0;             // steps enqueued since the device step counter was last advanced
+    int step_add = 0;             // steps enqueued since the device step counter was last advanced (0 between calls)
     size_t lds_max = 65536;       // dynamic LDS one workgroup may use on this device
     int ncu = 256;                // compute units of this device
     void* pm_buf = nullptr;       // pair-matrix scratch (grown on demand, freed by swf_free)
@@ -2037,6 +2037,15 @@ swf_status swf_step(swf_ctx* ctx, int n_steps, int* steps_left) {
         checked = true;
         return SWF_OK;
     };
+    // on a failure the counter still moves past the steps that were enqueued: the
+    // states are those of its time, and the next call starts from a counter
+    // without a remainder
+    auto failed = [&](int code) {
+        const std::string why = ctx->err;
+        (void)advance(ctx);
+        ctx->err = why;
+        return (swf_status)code;
+    };
     if (line_path(ctx)) {
         for (int done = 0; done < n_steps;) {
             int c = n_steps - done;
@@ -2058,12 +2067,9 @@ swf_status swf_step(swf_ctx* ctx, int n_steps, int* steps_left) {
                 HIPCHK(hipGraphLaunch(ctx->gexec, ctx->st));
             } else {
                 r = enqueue_step(ctx);
-                if (r) {
-                    ctx->step_add = 0;
-                    return (swf_status)r;
-                }
+                if (r) return failed(r);
             }
-            if (K > 0 && (ctx->step + i) % K == 0 && (r = check(ctx->step + i))) return (swf_status)r;
+            if (K > 0 && (ctx->step + i) % K == 0 && (r = check(ctx->step + i))) return failed(r);
         }
     }
     r = advance(ctx);
