@@ -37,7 +37,8 @@ namespace {
 thread_local std::string g_init_error;
 
 constexpr int RED_BLOCKS = 512;          // most blocks of a reduction launch (a lattice's number is fixed: deterministic sums)
-constexpr int BW_BLOCKS = 1024;          // most blocks per vertex of the BW stage reduction
+constexpr int BW_BLOCKS = 1024;          // blocks that fill a launch of the BW stage reduction
+constexpr int BW_MIN_BLOCKS = 256;       // most blocks per vertex where several groups fill it together
 constexpr int BW2_BLOCKS = 256;          // blocks per vertex of the partial-integration route's reductions
 constexpr int NKIND = 6;                 // kernel-stats kinds (swf_kernel_stats)
 constexpr int PROF_POOL = 2048;          // event pairs kept in flight when profiling
@@ -206,6 +207,7 @@ struct Plan {
     std::vector<cd> ctab;               // complex tables
     std::vector<Group> batched, single; // groups per grid / per solve
     std::vector<int2> items;
+    size_t npart = 0;                   // partials of the vertices' stage sums
     // arena layout (byte offsets)
     size_t off_state = 0, off_solves = 0, off_terms = 0, off_verts = 0, off_vgroups = 0, off_modes = 0, off_packets = 0,
            off_rtab = 0, off_ctab = 0,
@@ -656,6 +658,24 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
             }
         }
     }
+    // workgroups and partials of the stage sums: one site per thread up to 1024
+    // workgroups a launch (one launch per group shape and one of the packets),
+    // which its groups share as long as each may take 256
+    auto set_blocks = [&](int v, size_t sharing) {
+        VertexDev& d = P.hv[v];
+        d.nblk = swf::bw_blocks(P.hs[d.su].nsites, std::max<int>(BW_MIN_BLOCKS, BW_BLOCKS / (int)sharing));
+        d.part = (long long)P.npart;
+        P.npart += (size_t)3 * P.nst * d.nblk;
+    };
+    for (auto& g : P.hg) {
+        const size_t alike = std::count_if(P.hg.begin(), P.hg.end(), [&](const auto& o) { return o.nu == g.nu && o.nv == g.nv; });
+        for (int j = 0; j < g.nvx; ++j) {
+            set_blocks(g.vtx[j], alike);
+            g.part[j] = P.hv[g.vtx[j]].part;
+        }
+        g.nblk = P.hv[g.vtx[0]].nblk;
+    }
+    for (int v : P.packets) set_blocks(v, P.packets.size());
     // ---- groups and work items
     if (opt->chunk < 0) FAIL(SWF_E_ARG, "chunk must be >= 0");
     if (opt->check_every < 0) FAIL(SWF_E_ARG, "check_every must be >= 0");
@@ -718,7 +738,7 @@ static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_gr
     P.off_M = off = align256(off);
     off += sizeof(double2) * 3 * std::max(1, n_verts);
     P.off_part = off = align256(off);
-    off += sizeof(double2) * 3 * P.nst * (size_t)BW_BLOCKS * std::max(1, n_verts);
+    off += sizeof(double2) * P.npart;
     P.off_red = off = align256(off);
     off += sizeof(double2) * 4 * (size_t)RED_BLOCKS;
     if (P.bw2) {
@@ -1038,7 +1058,6 @@ static int bw_stage(swf_ctx* ctx, int stage) {
     b.nst = ctx->P.nst;
     b.nvert = (int)ctx->P.hv.size();
     b.part = ctx->d_part();
-    b.nblk = BW_BLOCKS;
     b.M = ctx->d_M();
     b.groups = ctx->d_vgroups();
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1059,13 +1078,13 @@ static int bw_stage(swf_ctx* ctx, int stage) {
         swf::BwArgs bg = b;
         bg.groups = ctx->d_vgroups() + g0;
         int nb = 1;
-        for (size_t g = g0; g < g1; ++g) nb = std::max(nb, swf::bw_blocks(ctx->P.hs[hg[g].su[0]].nsites, BW_BLOCKS));
+        for (size_t g = g0; g < g1; ++g) nb = std::max(nb, hg[g].nblk);
         HIPCHK(swf::launch_bw_stage(ctx->P.fp64, bg, nb, hg[g0].nu, hg[g0].nv, (int)(g1 - g0), ctx->st));
         g0 = g1;
     }
     if (!ctx->P.packets.empty()) {
         int nb = 1;
-        for (int v : ctx->P.packets) nb = std::max(nb, swf::bw_blocks(ctx->P.hs[ctx->P.hv[v].su].nsites, BW_BLOCKS));
+        for (int v : ctx->P.packets) nb = std::max(nb, ctx->P.hv[v].nblk);
         HIPCHK(swf::launch_bw_packet_stage(ctx->P.fp64, b, nb, (int)ctx->P.packets.size(), ctx->st));
     }
     if (prof) {
@@ -1090,7 +1109,6 @@ static int bw_accum(swf_ctx* ctx) {
     for (int st = 0; st < ctx->P.nst; ++st) b.wst[st] = ctx->P.wst[st];
     b.nvert = (int)ctx->P.hv.size();
     b.part = ctx->d_part();
-    b.nblk = BW_BLOCKS;
     b.M = ctx->d_M();
     HIPCHK(swf::launch_bw_accum(b, ctx->st));
     return SWF_OK;

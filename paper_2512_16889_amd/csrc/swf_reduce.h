@@ -42,6 +42,8 @@ struct VertexDev {
     double ksb[3];       // k - q: that of the (scat, back) term
     double p0, q0;       // electron and positron energies
     double x0[3], dx[3]; // lattice coordinates x_i = x0 + i dx
+    int nblk;            // workgroups of the vertex' stage sums
+    long long part;      // their partials in BwArgs::part, [stage][workgroup][3]
 };
 
 // Vertices reduced together at each RK4 stage: every state of the group's (at
@@ -50,6 +52,7 @@ constexpr int BWG_SOLVES = 2;
 constexpr int BWG_VERTS = 4;
 struct VertexGroupDev {
     int nu, nv, nvx;
+    int nblk;                             // workgroups (as of its vertices)
     int su[BWG_SOLVES], sv[BWG_SOLVES];   // the solves
     int vtx[BWG_VERTS];                   // the vertices
     int ui[BWG_VERTS], vi[BWG_VERTS];     // each vertex's U and V solve within su / sv
@@ -59,11 +62,12 @@ struct VertexGroupDev {
     long long tk;                         // exp(i k.x) tables (complex offset, n0 + n1 + n2 entries)
     long long t1[BWG_SOLVES];             // conj(U background phase) exp(i k.x), per U solve
     long long t2[BWG_SOLVES];             // V background phase exp(i k.x), per V solve
+    long long part[BWG_VERTS];            // the vertices' partials
 };
 
-// Workgroups of a vertex' stage reduction on a lattice of ns sites: one site
-// per thread until they fill the chip (nblk), so a short line takes a few
-// workgroups and leaves as few partials to add.
+// Workgroups of a reduction over a lattice of ns sites: one site per thread up
+// to nblk of them, so a short line takes a few workgroups and leaves as few
+// partials to add.
 constexpr int RED_THREADS = 256;
 __host__ __device__ inline int bw_blocks(long long ns, int nblk) {
     const long long b = (ns + RED_THREADS - 1) / RED_THREADS;
@@ -86,8 +90,7 @@ struct BwArgs {
     int nst;             // stages per step (4 RK4, 6 Dormand-Prince)
     double wst[6];       // the stages' quadrature weights (sum 1)
     int nvert;
-    int nblk;            // blocks a vertex and stage have room for in `part`
-    double2* part;       // [vertex][stage][block][3]
+    double2* part;       // the stage sums' partials (VertexDev::part)
     double2* M;          // [vertex][3] accumulated integrals (device, double)
     // partial-integration route
     int vtx;             // vertex of a per-vertex launch

@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_stage_kernel(BwArgs a) {
     const unsigned n0 = (unsigned)S0->n[0], n1 = (unsigned)S0->n[1];
     const unsigned ns = (unsigned)S0->nsites;
     // (a launch has as many workgroups as its largest lattice takes)
-    const unsigned nblk = (unsigned)bw_blocks(ns, a.nblk);
+    const unsigned nblk = (unsigned)G->nblk;
     if (blockIdx.x >= nblk) return;
     // the states, U solves first
     gptr<const nv2<R>> st[NU + NV];
@@ -383,8 +383,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_stage_kernel(BwArgs a) {
         if (y >= n1) { y -= n1; ++z; }
     }
     // block sums of the 3 terms of every pair: within each wave, then the waves
-    // in order; times the terms' time factors; partials layout
-    // [vertex][stage][block][3]
+    // in order; times the terms' time factors
     constexpr int NW = RED_THREADS / 64;
     using Sums = WaveSums<6 * NP>;
     __shared__ double shw[NW][6 * NP];
@@ -401,7 +400,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_stage_kernel(BwArgs a) {
         double2 s = d2(shw[0][p], shw[0][p + 1]);
 #pragma unroll
         for (int w = 1; w < NW; ++w) s = dadd(s, d2(shw[w][p], shw[w][p + 1]));
-        a.part[(((long long)G->vtx[j] * a.nst + a.stage) * a.nblk + blockIdx.x) * 3 + c] = dmul(tf, s);
+        a.part[G->part[j] + ((long long)a.stage * nblk + blockIdx.x) * 3 + c] = dmul(tf, s);
     }
 }
 
@@ -429,7 +428,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_packet_stage_kernel(BwArgs a) 
     const double ts = a.t_out - (double)(*a.step + a.step_add) * a.dt - a.cst * a.dt;
     const C* ctab = reinterpret_cast<const C*>(a.ctab);
     const int nm = V->nmodes;
-    const int nblk = bw_blocks(SU->nsites, a.nblk);
+    const int nblk = V->nblk;
     if ((int)blockIdx.x >= nblk) return;
     // c_m e^{-i k0_m t} eps_m of every mode and its phase tables
     __shared__ double2 am[MAX_MODES][3];
@@ -488,8 +487,7 @@ __global__ void __launch_bounds__(RED_THREADS) bw_packet_stage_kernel(BwArgs a) 
             acc[2] = dadd(acc[2], dcmul(yu[q], gbv[q]));
         }
     }
-    // partials layout [vertex][stage][block][3]
-    double2* out = a.part + ((long long)a.packets[blockIdx.y] * a.nst + a.stage) * (long long)a.nblk * 3;
+    double2* out = a.part + V->part + (long long)a.stage * nblk * 3;
     block_sum_store<3>(acc, out);
 }
 
@@ -497,17 +495,17 @@ __global__ void __launch_bounds__(RED_THREADS) bw_packet_stage_kernel(BwArgs a) 
 // thread adds every ACC_THREADS-th partial of each stage (always of the same
 // term: the stride is a multiple of 3), then one thread per term adds the
 // threads' sums in order.  The sum is bound by memory latency alone (at most
-// 200 KB in cache), so what counts is how many loads are in flight: one thread
+// 300 KB in cache: six stages of 1024 workgroups), so what counts is how many loads are in flight: one thread
 // per (vertex, term) took 140 us a step for 4 stages of 256 blocks, this 5 us.
 constexpr int ACC_THREADS = 192;
 __global__ void __launch_bounds__(ACC_THREADS) bw_accum_kernel(BwArgs a) {
     __shared__ double2 sh[ACC_THREADS];
     const int v = blockIdx.x, tid = threadIdx.x;
     const SolveDev* SU = a.solves + a.verts[v].su;
-    const int n = 3 * bw_blocks(SU->nsites, a.nblk);
+    const int n = 3 * a.verts[v].nblk;
     double2 s = d2(0, 0);
     for (int st = 0; st < a.nst; ++st) {
-        const double2* p = a.part + ((long long)v * a.nst + st) * (long long)a.nblk * 3;
+        const double2* p = a.part + a.verts[v].part + (long long)st * n;
         double2 ss = d2(0, 0);
 #pragma unroll 4
         for (int e = tid; e < n; e += ACC_THREADS) ss = dadd(ss, p[e]);
