@@ -326,8 +326,9 @@ swf_status swf_apply_op(swf_ctx* ctx, int op, int i, double t, const double* in,
 
 /* Pass timing collected when options.profile = 1.  kind: 0 row pass (x axis,
  * with the stage epilogue), 1 column pass (y axis), 2 column pass (z axis),
- * 3 BW vertex reduction, 4 other, 5 one-dimensional whole-loop kernel
- * (options.persistent).  Returns launches, summed device milliseconds and the
+ * 3 BW vertex reduction, 4 other (a step's time factors, the interaction
+ * picture's passes, transforms of whole states), 5 one-dimensional whole-loop
+ * kernel (options.persistent).  Returns launches, summed device milliseconds and the
  * algorithmic HBM bytes those launches move (state reads + writes). */
 swf_status swf_kernel_stats(swf_ctx* ctx, int kind, long long* launches, double* ms, double* bytes);
 swf_status swf_reset_stats(swf_ctx* ctx);

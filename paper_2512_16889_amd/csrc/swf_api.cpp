@@ -899,13 +899,9 @@ static int streams(swf_ctx* ctx, const Group& g) {
     return 4.0 * ctx->P.csize * group_sites(ctx, g) > STREAM_BYTES ? 1 : 0;
 }
 
-// Launch one pass kernel over n items starting at item offset `it`.
-static int launch(swf_ctx* ctx, const void* fn, int nitems, size_t it, int threads, size_t lds, swf::PassArgs a,
-                  int kind, double bytes, int gy = 1) {
-    if (nitems <= 0) return SWF_OK;
-    a.items = ctx->d_items() + it;
-    a.nitems = nitems;
-    void* args[] = {&a};
+// What `enqueue` launches, timed as a pass of `kind` that moves `bytes` when profiling.
+template <class F>
+static int timed(swf_ctx* ctx, int kind, double bytes, F&& enqueue) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool prof = ctx->opt.profile && !ctx->gexec;
     if (prof) {
@@ -914,12 +910,26 @@ static int launch(swf_ctx* ctx, const void* fn, int nitems, size_t it, int threa
         if (r) return r;
         HIPCHK(hipEventRecord(e0, ctx->st));
     }
-    HIPCHK(hipLaunchKernel(fn, dim3(nitems, gy), dim3(threads), args, lds, ctx->st));
+    int r = enqueue();
+    if (r) return r;
     if (prof) {
         HIPCHK(hipEventRecord(e1, ctx->st));
         ctx->pending.push_back({e0, e1, kind, bytes});
     }
     return SWF_OK;
+}
+
+// Launch one pass kernel over n items starting at item offset `it`.
+static int launch(swf_ctx* ctx, const void* fn, int nitems, size_t it, int threads, size_t lds, swf::PassArgs a,
+                  int kind, double bytes, int gy = 1) {
+    if (nitems <= 0) return SWF_OK;
+    a.items = ctx->d_items() + it;
+    a.nitems = nitems;
+    void* args[] = {&a};
+    return timed(ctx, kind, bytes, [&]() -> int {
+        HIPCHK(hipLaunchKernel(fn, dim3(nitems, gy), dim3(threads), args, lds, ctx->st));
+        return SWF_OK;
+    });
 }
 
 // x-axis pass of a group in the given mode (ROW_STAGE: the RK4 stage pass).
@@ -1060,42 +1070,32 @@ static int bw_stage(swf_ctx* ctx, int stage) {
     b.part = ctx->d_part();
     b.M = ctx->d_M();
     b.groups = ctx->d_vgroups();
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    const bool prof = ctx->opt.profile && !ctx->gexec;
-    if (prof) {
-        int r = get_event(ctx, &e0);
-        if (!r) r = get_event(ctx, &e1);
-        if (r) return r;
-        HIPCHK(hipEventRecord(e0, ctx->st));
-    }
     b.modes = ctx->d_modes();
     b.packets = ctx->d_packets();
-    // one launch per group shape (the groups are sorted by shape)
-    const auto& hg = ctx->P.hg;
-    for (size_t g0 = 0; g0 < hg.size();) {
-        size_t g1 = g0;
-        while (g1 < hg.size() && hg[g1].nu == hg[g0].nu && hg[g1].nv == hg[g0].nv) ++g1;
-        swf::BwArgs bg = b;
-        bg.groups = ctx->d_vgroups() + g0;
-        int nb = 1;
-        for (size_t g = g0; g < g1; ++g) nb = std::max(nb, hg[g].nblk);
-        HIPCHK(swf::launch_bw_stage(ctx->P.fp64, bg, nb, hg[g0].nu, hg[g0].nv, (int)(g1 - g0), ctx->st));
-        g0 = g1;
-    }
-    if (!ctx->P.packets.empty()) {
-        int nb = 1;
-        for (int v : ctx->P.packets) nb = std::max(nb, ctx->P.hv[v].nblk);
-        HIPCHK(swf::launch_bw_packet_stage(ctx->P.fp64, b, nb, (int)ctx->P.packets.size(), ctx->st));
-    }
-    if (prof) {
-        // every state of a group's solves is read once; a packet reads its two
-        double bytes = 0;
-        for (auto& g : ctx->P.hg) bytes += (g.nu + g.nv) * 4.0 * ctx->P.csize * (double)ctx->P.hs[g.su[0]].nsites;
-        for (int v : ctx->P.packets) bytes += 2.0 * 4.0 * ctx->P.csize * (double)ctx->P.hs[ctx->P.hv[v].su].nsites;
-        HIPCHK(hipEventRecord(e1, ctx->st));
-        ctx->pending.push_back({e0, e1, 3, bytes});
-    }
-    return SWF_OK;
+    // every state of a group's solves is read once; a packet reads its two
+    double bytes = 0;
+    for (auto& g : ctx->P.hg) bytes += (g.nu + g.nv) * 4.0 * ctx->P.csize * (double)ctx->P.hs[g.su[0]].nsites;
+    for (int v : ctx->P.packets) bytes += 2.0 * 4.0 * ctx->P.csize * (double)ctx->P.hs[ctx->P.hv[v].su].nsites;
+    return timed(ctx, 3, bytes, [&]() -> int {
+        // one launch per group shape (the groups are sorted by shape)
+        const auto& hg = ctx->P.hg;
+        for (size_t g0 = 0; g0 < hg.size();) {
+            size_t g1 = g0;
+            while (g1 < hg.size() && hg[g1].nu == hg[g0].nu && hg[g1].nv == hg[g0].nv) ++g1;
+            swf::BwArgs bg = b;
+            bg.groups = ctx->d_vgroups() + g0;
+            int nb = 1;
+            for (size_t g = g0; g < g1; ++g) nb = std::max(nb, hg[g].nblk);
+            HIPCHK(swf::launch_bw_stage(ctx->P.fp64, bg, nb, hg[g0].nu, hg[g0].nv, (int)(g1 - g0), ctx->st));
+            g0 = g1;
+        }
+        if (!ctx->P.packets.empty()) {
+            int nb = 1;
+            for (int v : ctx->P.packets) nb = std::max(nb, ctx->P.hv[v].nblk);
+            HIPCHK(swf::launch_bw_packet_stage(ctx->P.fp64, b, nb, (int)ctx->P.packets.size(), ctx->st));
+        }
+        return SWF_OK;
+    });
 }
 
 static int bw_accum(swf_ctx* ctx) {
@@ -1208,8 +1208,10 @@ static int free_evolve(swf_ctx* ctx, const Group& g, int role, double tau) {
 static int stage_consts(swf_ctx* ctx) {
     swf::StageNodes n;
     for (int st = 0; st < 6; ++st) n.c[st] = ctx->P.cst[st];
-    HIPCHK(swf::launch_stage_consts(ctx->P.fp64, pass_args(ctx), n, (int)ctx->P.solves.size(), ctx->st));
-    return SWF_OK;
+    return timed(ctx, 4, 0.0, [&]() -> int {
+        HIPCHK(swf::launch_stage_consts(ctx->P.fp64, pass_args(ctx), n, (int)ctx->P.solves.size(), ctx->st));
+        return SWF_OK;
+    });
 }
 
 // One pointwise part of an interaction-picture step of a group.
@@ -1226,8 +1228,11 @@ static int ip_point(swf_ctx* ctx, const Group& g, int mode) {
     a.nst = ctx->P.nst;
     a.h = -ctx->P.sdt;
     a.stream = streams(ctx, g);
-    HIPCHK(swf::launch_ip_point(ctx->P.fp64, mode, a, g.n_orow, ctx->st));
-    return SWF_OK;
+    const double trav[] = {2, 4, 4, 5, 3};   // state arrays read and written, by mode
+    return timed(ctx, 4, trav[mode] * 4.0 * ctx->P.csize * group_sites(ctx, g), [&]() -> int {
+        HIPCHK(swf::launch_ip_point(ctx->P.fp64, mode, a, g.n_orow, ctx->st));
+        return SWF_OK;
+    });
 }
 
 // One step: with h the signed step, E = exp(-i H0 h/2) and N(t, y) = -i V(t) (y + psi_b),

@@ -88,3 +88,32 @@ def test_counter_after_a_failed_launch(S, lib, failing, at, restart):
             start = 5
         assert c.step(1, None) == 0
         assert lib.stub_step_add() == 0 and lib.stub_step() == start + 1
+
+
+@pytest.mark.parametrize("scheme", ["rk4", "dp5", "iprk4"])
+@pytest.mark.parametrize("vertices", [0, 1])
+def test_every_launch_of_a_step_is_timed(S, lib, scheme, vertices):
+    """Of a step's kernels the statistics leave out the accumulation of the vertices alone.  Each interaction-picture
+    pass moves the state arrays it reads and writes: Y -> YS; YS, Y -> YS, ACC; YS, ACC -> Y, the middle one in two
+    halves (4 and 5 arrays) around the vertices' sums; four free evolutions of 6 (2D) or 2 (1D) passes' arrays."""
+    prob = W.config_bw_1d(n=64, L=100.0, steps=4) if vertices else W.config_2d(n=64, L=160.0, n_solves=2, steps=10)
+    w = prob.window
+    prob.window = W.Window(w.t_in, w.t_out, w.dt, scheme)
+    with Context(S, lib, prob, profile=1, stepper={"rk4": S.SWF_RK4, "dp5": S.SWF_DP5, "iprk4": S.SWF_IPRK4}[scheme]) as c:
+        lib.stub_clear()
+        assert c.step(3, None) == 0
+        n, ms, by = C.c_longlong(), C.c_double(), C.c_double()
+        launches, moved = 0, 0.0
+        for kind in range(6):
+            assert c.kernel_stats(kind, C.byref(n), C.byref(ms), C.byref(by)) == 0
+            launches += n.value
+            assert ms.value == n.value             # the stand-in's events are 1 ms apart
+            if kind != 3:
+                moved += by.value
+        enqueued = sum(lib.stub_count(k.encode()) for k in ("pass", "stage_consts", "ip_point", "bw_stage"))
+        assert lib.stub_count(b"stage_consts") == 3
+        assert launches == enqueued
+        if scheme == "iprk4":
+            array = 4 * 16 * (64 if vertices else 64 * 64) * 2          # of both solves, in double
+            points = 2 + (4 + 5 if vertices else 4) + 3
+            assert moved == 3 * array * (points + 4 * (4 if vertices else 6))
