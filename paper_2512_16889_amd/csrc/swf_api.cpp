@@ -1406,8 +1406,9 @@ static int build_graph(swf_ctx* ctx) {
 
 // ------------------------------------------------------------ autotuner
 // Times every tile variant of the stepping column passes of each group on the
-// problem itself (zero state, stage 1), keeps the fastest, and caches the
-// choice by (precision, grid, batch size) in a text file.
+// problem's own arrays (whatever the stage inputs hold), keeps the fastest, and
+// caches the choice by (precision, grid, batch size) in a text file.  psi_s is
+// neither read by a column pass nor written.
 static std::string tune_key(swf_ctx* ctx, const Group& g) {
     const swf_grid& G = ctx->P.grids[g.grid];
     char b[160];
@@ -1494,7 +1495,7 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
     }
     ctx->opt.profile = prof;
     ctx->tune_report = rep.str();
-    // (the stages timed write the other state arrays, not psi_s)
+    // (the row stage timed reads psi_s and writes the other state arrays)
     HIPCHK(hipStreamSynchronize(ctx->st));
     return SWF_OK;
 }
