@@ -132,7 +132,7 @@ typedef struct {
                                default variant       */
     int persistent;         /* 1: when every grid is one-dimensional, the profiles of the
                                field's terms beyond the fourth fit in LDS next to the
-                               state (FP64, 1024 points: up to 4 terms) and there are no
+                               state (FP64, 1024 points: up to 5 terms) and there are no
                                BW vertices, each swf_step call runs all its time steps in
                                one kernel per launch group (at most 1024 steps per
                                launch), one workgroup per solve, with the state held on
