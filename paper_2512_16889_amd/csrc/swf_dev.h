@@ -179,45 +179,23 @@ SWF_PLAN(1024, 32, 32, 32)
 #undef SWF_PLAN
 
 
-// Plans with 4 points per thread (radix 4, a final radix 2 when log2 N is
-// odd): twice the threads per line and half the registers of the default.
-template <int N> struct Plan4;
-#define SWF_PLAN4(N_, ...)                                               \
-    template <> struct Plan4<N_> {                                       \
-        static constexpr int T = N_ / 4;                                 \
-        static constexpr int R[] = {__VA_ARGS__};                        \
-        static constexpr int NR = sizeof(R) / sizeof(int);               \
-    };
-SWF_PLAN4(64, 4, 4, 4)
-SWF_PLAN4(128, 4, 4, 4, 2)
-SWF_PLAN4(256, 4, 4, 4, 4)
-SWF_PLAN4(512, 4, 4, 4, 4, 2)
-SWF_PLAN4(1024, 4, 4, 4, 4, 4)
-#undef SWF_PLAN4
-template <int N> constexpr bool has_plan4() { return N == 64 || N == 128 || N == 256 || N == 512 || N == 1024; }
-
-// Plans with few points per thread for the mixed-radix lengths: a radix-6
-// (3 * 2^a) or radix-10 (5 * 2^a) first step and radix-2 steps after it, so a
-// thread holds 6 or 10 points instead of 12 or 20 (the default plans' radix-4
-// steps need a multiple of 4 and of 3 or 5 per thread).
-template <int N> struct PlanS;
-#define SWF_PLANS(N_, E_, ...)                                           \
-    template <> struct PlanS<N_> {                                       \
+// Plans with few points per thread, for the passes that hold four components in
+// each thread (col_kernel): 4 points by radix 4 (a final radix 2 when log2 N is
+// odd), or 6 by a radix-6 first step and radix-2 steps after it.  The default
+// plan elsewhere.
+template <int N> struct SmallPlan : FftPlan<N> {};
+#define SWF_PLAN(N_, E_, ...)                                            \
+    template <> struct SmallPlan<N_> {                                   \
         static constexpr int T = N_ / E_;                                \
         static constexpr int R[] = {__VA_ARGS__};                        \
         static constexpr int NR = sizeof(R) / sizeof(int);               \
     };
-SWF_PLANS(384, 6, 6, 2, 2, 2, 2, 2, 2)
-SWF_PLANS(768, 6, 6, 2, 2, 2, 2, 2, 2, 2)
-SWF_PLANS(320, 10, 10, 2, 2, 2, 2, 2)
-#undef SWF_PLANS
-template <int N> constexpr bool has_plans() { return N == 384 || N == 768 || N == 320; }
-
-// The few-points-per-thread plan of a length (tile variants that use it).
-template <int N, bool P4 = has_plan4<N>(), bool PS = has_plans<N>()> struct SmallPlan { using type = FftPlan<N>; };
-template <int N, bool PS> struct SmallPlan<N, true, PS> { using type = Plan4<N>; };
-template <int N> struct SmallPlan<N, false, true> { using type = PlanS<N>; };
-template <int N> constexpr bool has_small_plan() { return has_plan4<N>() || has_plans<N>(); }
+SWF_PLAN(256, 4, 4, 4, 4, 4)
+SWF_PLAN(512, 4, 4, 4, 4, 4, 2)
+SWF_PLAN(1024, 4, 4, 4, 4, 4, 4)
+SWF_PLAN(384, 6, 6, 2, 2, 2, 2, 2, 2)
+SWF_PLAN(768, 6, 6, 2, 2, 2, 2, 2, 2, 2)
+#undef SWF_PLAN
 
 template <class P> constexpr int plan_stride(int j) {
     int s = 1;
@@ -323,30 +301,6 @@ template <int DIR, class C> struct Dft<6, DIR, C> {
     }
 };
 
-// radix 10 = 2 x 5, the same even/odd split around the 5-point transform
-template <int DIR, class C> struct Dft<10, DIR, C> {
-    static __device__ __forceinline__ void run(C* a) {
-        using R = decltype(C::x);
-        const R c1 = (R)0.80901699437494742410, s1 = (R)(DIR * 0.58778525229247312917);   // w^1 (36 degrees)
-        const R c2 = (R)0.30901699437494742410, s2 = (R)(DIR * 0.95105651629515357212);   // w^2 (72)
-        C e[5] = {a[0], a[2], a[4], a[6], a[8]};
-        C o[5] = {a[1], a[3], a[5], a[7], a[9]};
-        Dft<5, DIR, C>::run(e);
-        Dft<5, DIR, C>::run(o);
-        C ow[5];
-        ow[0] = o[0];
-        ow[1] = cmul(o[1], cmake<C>(c1, s1));
-        ow[2] = cmul(o[2], cmake<C>(c2, s2));
-        ow[3] = cmul(o[3], cmake<C>(-c2, s2));    // w^3 (108)
-        ow[4] = cmul(o[4], cmake<C>(-c1, s1));    // w^4 (144)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            a[k] = cadd(e[k], ow[k]);
-            a[k + 5] = csub(e[k], ow[k]);
-        }
-    }
-};
-
 // cos(2 pi m / 32)
 constexpr double cos32(int m) {
     constexpr double c[9] = {1.0, 0.98078528040323044913, 0.92387953251128675613, 0.83146961230254523708,
@@ -416,9 +370,6 @@ template <int R1, int R2, int DIR, class C> __device__ __forceinline__ void dft_
 template <int DIR, class C> struct Dft<12, DIR, C> {
     static __device__ __forceinline__ void run(C* a) { dft_coprime<3, 4, DIR, C>(a); }
 };
-template <int DIR, class C> struct Dft<24, DIR, C> {
-    static __device__ __forceinline__ void run(C* a) { dft_coprime<3, 8, DIR, C>(a); }
-};
 template <int DIR, class C> struct Dft<20, DIR, C> {
     static __device__ __forceinline__ void run(C* a) { dft_coprime<5, 4, DIR, C>(a); }
 };
@@ -470,10 +421,10 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Exchange the outputs of step J-1 into the inputs of step J through LDS,
-// CG components at a time.  Lay::addr(q, line, idx) is the LDS slot of point
-// idx of component q (within the group) of this thread's line.
-template <class C, int N, int T, int J, int NC, int CG, class Lay, class P>
+// Exchange the outputs of step J-1 into the inputs of step J through LDS, one
+// component after the other.  Lay::addr(line, idx) is the LDS slot of point idx
+// of this thread's line.
+template <class C, int N, int T, int J, int NC, class Lay, class P>
 __device__ __forceinline__ void fft_exchange(C (&v)[NC][N / T], C* lds, int t, int line) {
     constexpr int Rp = P::R[J - 1];
     constexpr int NSp = plan_stride<P>(J - 1);
@@ -482,38 +433,32 @@ __device__ __forceinline__ void fft_exchange(C (&v)[NC][N / T], C* lds, int t, i
     constexpr int Bp = E / Rp;
     constexpr int B = E / R;
 #pragma unroll
-    for (int g = 0; g < NC; g += CG) {
+    for (int q = 0; q < NC; ++q) {
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < CG; ++q) {
+        for (int c = 0; c < Bp; ++c) {
+            const int b = t + T * c;
+            const int d = (b / NSp) * NSp * Rp + (b % NSp);
 #pragma unroll
-            for (int c = 0; c < Bp; ++c) {
-                const int b = t + T * c;
-                const int d = (b / NSp) * NSp * Rp + (b % NSp);
-#pragma unroll
-                for (int k = 0; k < Rp; ++k) lds[Lay::addr(q, line, d + k * NSp)] = v[g + q][c + Bp * k];
-            }
+            for (int k = 0; k < Rp; ++k) lds[Lay::addr(line, d + k * NSp)] = v[q][c + Bp * k];
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < CG; ++q) {
+        for (int c = 0; c < B; ++c) {
+            const int b = t + T * c;
 #pragma unroll
-            for (int c = 0; c < B; ++c) {
-                const int b = t + T * c;
-#pragma unroll
-                for (int k = 0; k < R; ++k) v[g + q][c + B * k] = lds[Lay::addr(q, line, b + k * (N / R))];
-            }
+            for (int k = 0; k < R; ++k) v[q][c + B * k] = lds[Lay::addr(line, b + k * (N / R))];
         }
     }
 }
 
-template <class C, int N, int T, int J, int DIR, int NC, int CG, class Lay, class P>
+template <class C, int N, int T, int J, int DIR, int NC, class Lay, class P>
 struct FftRun {
     static __device__ __forceinline__ void run(C (&v)[NC][N / T], C* lds, int t, int line, const C* tw) {
         if constexpr (J < P::NR) {
-            if constexpr (J > 0) fft_exchange<C, N, T, J, NC, CG, Lay, P>(v, lds, t, line);
+            if constexpr (J > 0) fft_exchange<C, N, T, J, NC, Lay, P>(v, lds, t, line);
             fft_step<C, N, T, J, DIR, NC, P>(v, t, tw);
-            FftRun<C, N, T, J + 1, DIR, NC, CG, Lay, P>::run(v, lds, t, line, tw);
+            FftRun<C, N, T, J + 1, DIR, NC, Lay, P>::run(v, lds, t, line, tw);
         }
     }
 };
@@ -521,9 +466,9 @@ struct FftRun {
 // Unnormalised transform of NC components along one line, DIR = -1 forward
 // (numpy sign), +1 inverse.  tw[m] = exp(-2 pi i m / N).  P gives the radix
 // list; every radix must divide N/T and T must divide N/radix.
-template <class C, int N, int T, int DIR, int NC, int CG, class Lay, class P = FftPlan<N>>
+template <class C, int N, int T, int DIR, int NC, class Lay, class P>
 __device__ __forceinline__ void fft_line(C (&v)[NC][N / T], C* lds, int t, int line, const C* tw) {
-    FftRun<C, N, T, 0, DIR, NC, CG, Lay, P>::run(v, lds, t, line, tw);
+    FftRun<C, N, T, 0, DIR, NC, Lay, P>::run(v, lds, t, line, tw);
 }
 
 // The transform of the stepping passes: one component per thread.  Output k of
@@ -650,14 +595,12 @@ __device__ __forceinline__ void fft_col(C (&v)[N / P::T], void* col, int t, cons
 // LDS layouts.  Row passes: lanes run along the line (t fastest), one padded
 // LDS row per line.  Column passes: lanes run across the W lines (x fastest),
 // so points of equal index sit next to each other.
-template <int N, int ROWS> struct RowLay {
+template <int N> struct RowLay {
     static constexpr int STRIDE = N + N / 16 + 1;
-    static __device__ __forceinline__ int addr(int q, int line, int idx) {
-        return (q * ROWS + line) * STRIDE + idx + (idx >> 4);
-    }
+    static __device__ __forceinline__ int addr(int line, int idx) { return line * STRIDE + idx + (idx >> 4); }
 };
 template <int N, int W> struct ColLay {
-    static __device__ __forceinline__ int addr(int q, int line, int idx) { return (q * N + idx) * W + line; }
+    static __device__ __forceinline__ int addr(int line, int idx) { return idx * W + line; }
 };
 
 // ---------------------------------------------------------------- physics helpers

@@ -59,79 +59,41 @@ struct PassArgs {
 };
 
 // ------------------------------------------------------------------ tile variants
-// A column pass kernel is instantiated for several tile shapes; the host times
-// them on the actual problem (autotuner) and keeps the fastest: T threads per
-// line, W adjacent x-columns per block.
+// A stepping column pass is instantiated for several tile widths (W adjacent
+// x-columns per block, T threads per line); the host times them on the actual
+// problem (autotuner) and keeps the fastest.
 template <int N, int T, class P = FftPlan<N>> constexpr bool plan_ok() {
     if (T < 1 || N % T) return false;
     for (int j = 0; j < P::NR; ++j)
         if ((N / P::R[j]) % T || (N / T) % P::R[j]) return false;
     return true;
 }
-// the plan of a variant: the default one, or the few-points-per-thread one
-template <int N, bool SMALL> struct PlanSel { using type = FftPlan<N>; };
-template <int N> struct PlanSel<N, true> { using type = typename SmallPlan<N>::type; };
-template <int N> constexpr int half_t() {
-    constexpr int T = FftPlan<N>::T;
-    return (T % 2 == 0 && 2 * N / T <= 16 && plan_ok<N, T / 2>()) ? T / 2 : T;
-}
 constexpr int NVAR = 3;       // tile variants of the stepping column passes
-constexpr size_t LDS_CAP = 72 * 1024;
 constexpr int imax(int a, int b) { return a > b ? a : b; }
 constexpr int imin(int a, int b) { return a < b ? a : b; }
-constexpr int cg_fit(size_t per_comp) { return 4 * per_comp <= LDS_CAP ? 4 : (2 * per_comp <= LDS_CAP ? 2 : 1); }
 
 // Tile of the row kernel (whole-state transforms and right-hand side): the
 // default plan, T threads per x-line, up to 256 threads per block.
-template <class R, int N, int V> struct RowVar {
+template <class R, int N> struct RowVar {
     using PL = FftPlan<N>;
     static constexpr int T = PL::T;
     static constexpr int ROWS = imax(1, 256 / T);
     static constexpr int THREADS = T * ROWS;
-    using Lay = RowLay<N, ROWS>;
-    static constexpr size_t PER_COMP = (size_t)ROWS * Lay::STRIDE * sizeof(cpx<R>);
-    static constexpr int CG = 1;
-    static constexpr size_t BYTES = CG * PER_COMP;
-    static constexpr bool SEQ = false;
-    static_assert(plan_ok<N, T, PL>(), "row variant violates the FFT plan constraints");
+    using Lay = RowLay<N>;
+    static constexpr size_t BYTES = (size_t)ROWS * Lay::STRIDE * sizeof(cpx<R>);
+    static_assert(plan_ok<N, T, PL>(), "row tile violates the FFT plan constraints");
 };
 
-template <class R, int N, int V> struct ColVar {
-    // columns per block:
-    //   v0: a full 128-byte line (WANT columns) of the default plan, capped at
-    //       512 threads;
-    //   v1: narrower tiles (more, smaller blocks per CU; the host then groups
-    //       the tiles of one line on one XCD);
-    //   v2: the few-points-per-thread plan, capped at 512 threads;
-    //   v3: the few-points-per-thread plan with up to 1024 threads, so that a
-    //       tile still covers a full 128-byte line where T is large (N >= 512)
-    static constexpr int WANT = sizeof(R) == 4 ? 16 : 8;
-    static constexpr bool SMALL = (V == 2 || V == 3) && has_small_plan<N>();
-    using PL = typename PlanSel<N, SMALL>::type;
+// Tile of the last-axis pass with four components in each thread: a full
+// 128-byte line of columns, up to 512 threads.
+template <class R, int N> struct ColVar {
+    using PL = SmallPlan<N>;
     static constexpr int T = PL::T;
-    static constexpr int W0 = imax(1, imin(WANT, (V == 3 ? 1024 : 512) / T));
-    static constexpr int W = V == 1 ? imax(1, WANT / 4) : W0;
+    static constexpr int W = imax(1, imin(128 / (int)sizeof(cpx<R>), 512 / T));
     static constexpr int THREADS = T * W;
-    static constexpr size_t PER_COMP = (size_t)N * W * sizeof(cpx<R>);
-    static constexpr int CG = 1;
-    static constexpr size_t BYTES = CG * PER_COMP;
-    static constexpr bool SEQ = false;
-    static_assert(plan_ok<N, T, PL>(), "column variant violates the FFT plan constraints");
+    static constexpr size_t BYTES = (size_t)N * W * sizeof(cpx<R>);
+    static_assert(plan_ok<N, T, PL>(), "column tile violates the FFT plan constraints");
 };
-
-// Transform the four components of a line: together (shared exchange rounds,
-// more registers live) or one component after another (SEQ: fewer registers,
-// more barriers).
-template <class C, int N, int T, int DIR, int CG, bool SEQ, class Lay, class P>
-__device__ __forceinline__ void fft4(C (&v)[4][N / T], C* lds, int t, int line, const C* tw) {
-    if constexpr (SEQ) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            fft_line<C, N, T, DIR, 1, 1, Lay, P>(reinterpret_cast<C(&)[1][N / T]>(v[q]), lds, t, line, tw);
-    } else {
-        fft_line<C, N, T, DIR, 4, CG, Lay, P>(v, lds, t, line, tw);
-    }
-}
 
 // ------------------------------------------------------------------ row pass
 // Global-address-space views of the state arrays (their pointers come from the
@@ -172,15 +134,14 @@ template <class R> __device__ __forceinline__ gptr<nv2<R>> wview(void* p) {
     return (gptr<nv2<R>>)(reinterpret_cast<nv2<R>*>(p));
 }
 
-template <class R, int N, int V, int MODE, int STAGE>
-__global__ void __launch_bounds__((RowVar<R, N, V>::THREADS)) row_kernel(PassArgs a) {
+template <class R, int N, int MODE>
+__global__ void __launch_bounds__((RowVar<R, N>::THREADS)) row_kernel(PassArgs a) {
     using C = cpx<R>;
-    using VC = RowVar<R, N, V>;
+    using VC = RowVar<R, N>;
     constexpr int T = VC::T;
     constexpr int ROWS = VC::ROWS;
     constexpr int E = N / T;
     using Lay = typename VC::Lay;
-    constexpr int CG = VC::CG;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* lds = reinterpret_cast<C*>(smem_raw);
     __shared__ R sh_fyz[ROWS][MAX_TERMS];
@@ -251,7 +212,7 @@ __global__ void __launch_bounds__((RowVar<R, N, V>::THREADS)) row_kernel(PassArg
                 }
             }
         }
-        fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, line, tw);
+        fft_line<C, N, T, +1, 4, Lay, typename VC::PL>(v, lds, t, line, tw);
     }
     if constexpr (MODE == ROW_INV) {
         store(a.dst, v);
@@ -330,13 +291,12 @@ __global__ void __launch_bounds__((RowVar<R, N, V>::THREADS)) row_kernel(PassArg
 // ------------------------------------------------------------------ column pass
 // Forward transform along the last axis, -i H0 / N or the free evolution, and back
 // (the whole state of a column in a thread group: the multiply mixes components).
-template <class R, int N, int V, int AXIS>
-__global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArgs a) {
+template <class R, int N, int AXIS>
+__global__ void __launch_bounds__((ColVar<R, N>::THREADS)) col_kernel(PassArgs a) {
     using C = cpx<R>;
-    using VC = ColVar<R, N, V>;
+    using VC = ColVar<R, N>;
     constexpr int T = VC::T;
     constexpr int W = VC::W;
-    constexpr int CG = VC::CG;
     constexpr int E = N / T;
     using Lay = ColLay<N, W>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -371,7 +331,7 @@ __global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArg
 #pragma unroll
             for (int m = 0; m < E; ++m) v[q][m] = gload<C>(p, q * ns + (long long)(T * m) * stride);
     }
-    fft4<C, N, T, -1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
+    fft_line<C, N, T, -1, 4, Lay, typename VC::PL>(v, lds, t, xl, tw);
     const double kx = S->dk[0] * kindex(act ? x : 0, n0);
 #pragma unroll
     for (int m = 0; m < E; ++m) {
@@ -387,7 +347,7 @@ __global__ void __launch_bounds__((ColVar<R, N, V>::THREADS)) col_kernel(PassArg
         if (a.expo) apply_expo(v[0][m], v[1][m], v[2][m], v[3][m], kx, ky, kz, a.tau, S->inv_n);
         else apply_h0(v[0][m], v[1][m], v[2][m], v[3][m], (R)kx, (R)ky, (R)kz, (R)S->inv_n);
     }
-    fft4<C, N, T, +1, CG, VC::SEQ, Lay, typename VC::PL>(v, lds, t, xl, tw);
+    fft_line<C, N, T, +1, 4, Lay, typename VC::PL>(v, lds, t, xl, tw);
     if (act) {
         gptr<nv2<R>> p = wview<R>(S->buf[a.dst]) + base;
 #pragma unroll
@@ -1331,10 +1291,9 @@ ColVariant make_col_variant() {
         c.w = VC::W;
         c.lds = VC::BYTES;
     } else {
-        constexpr int V = N >= 256 && has_small_plan<N>() ? 2 : 0;   // the few-points plan where there is one
-        using VC = ColVar<R, N, V>;
-        c.fn[0] = (const void*)col_kernel<R, N, V, 1>;
-        c.fn[1] = (const void*)col_kernel<R, N, V, 2>;
+        using VC = ColVar<R, N>;
+        c.fn[0] = (const void*)col_kernel<R, N, 1>;
+        c.fn[1] = (const void*)col_kernel<R, N, 2>;
         c.threads = VC::THREADS;
         c.w = VC::W;
         c.lds = VC::BYTES;
@@ -1372,12 +1331,12 @@ SizeKernels make_size_kernels() {
     k.col_tv[1] = col_t_tile(2, N);
     k.row_other[ROW_FWD] = k.row_other[ROW_FWDPH] = nullptr;
     k.row_other[ROW_STAGE] = nullptr;
-    k.row_other[ROW_INV] = (const void*)row_kernel<R, N, 0, ROW_INV, 0>;
-    k.row_other[ROW_RHS] = (const void*)row_kernel<R, N, 0, ROW_RHS, 0>;
-    k.row_other[ROW_SRC] = (const void*)row_kernel<R, N, 0, ROW_SRC, 0>;
-    k.row0_threads = RowVar<R, N, 0>::THREADS;
-    k.row0_rows = RowVar<R, N, 0>::ROWS;
-    k.row0_lds = RowVar<R, N, 0>::BYTES;
+    k.row_other[ROW_INV] = (const void*)row_kernel<R, N, ROW_INV>;
+    k.row_other[ROW_RHS] = (const void*)row_kernel<R, N, ROW_RHS>;
+    k.row_other[ROW_SRC] = (const void*)row_kernel<R, N, ROW_SRC>;
+    k.row0_threads = RowVar<R, N>::THREADS;
+    k.row0_rows = RowVar<R, N>::ROWS;
+    k.row0_lds = RowVar<R, N>::BYTES;
     k.line = (const void*)line_kernel<R, N>;
     k.line_threads = LineVar<R, N>::THREADS;
     k.line_lds = LineVar<R, N>::BASE_BYTES;
