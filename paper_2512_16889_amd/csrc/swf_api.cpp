@@ -1010,8 +1010,9 @@ static int cd_pass(swf_ctx* ctx, const Group& g, int axis, int src, int kind, in
 
 // Tile variant of a stepping column pass when none was timed or forced: the
 // widest tile of which a compute unit holds several (4 lines of 128 bytes up to
-// 128 points, 2 up to 512, 1 beyond; the measured rates stand at the kernel),
-// narrower while the launch would leave compute units without a workgroup.
+// 128 points, 2 up to 512, 1 beyond, as far as the length has them; the measured
+// rates stand at the kernel), narrower while the launch would have under two
+// workgroups a compute unit.
 static int default_tile(const swf_ctx* ctx, const Group& g, int axis) {
     if (!g.k[axis]) return 0;
     const int n = ctx->P.grids[g.grid].n[axis];
@@ -1478,6 +1479,8 @@ static int autotune(swf_ctx* ctx, std::vector<Group>& gl) {
             float best = 1e30f;
             int bv = 0;
             for (int v = 0; v < swf::NVAR; ++v) {
+                const auto* cd = g.k[axis]->cd;
+                if (v > 0 && cd[v].fn[axis - 1] == cd[v - 1].fn[axis - 1]) continue;   // no wider tile
                 (axis == 1 ? g.vy : g.vz) = v;
                 float ms = 0;
                 int r = time_it(ctx, [&] { return cd_pass(ctx, g, axis, swf::BUF_YS, 4); }, reps, &ms);

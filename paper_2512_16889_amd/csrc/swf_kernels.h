@@ -400,7 +400,9 @@ template <bool NT = true, class C> __device__ __forceinline__ void gstore_at(gpt
 // points of the transform in registers, exchanged through LDS: as real and
 // imaginary parts in turn where whole numbers would leave a compute unit room
 // for one workgroup (SPLIT), so that one's loads cover another's transform.
-//   v0, v1, v2: 1, 2, 4 lines of 128 bytes along x per tile.
+//   v0, v1, v2: 1, 2, 4 lines of 128 bytes along x per tile, at most what 1024
+//   threads and the LDS allow (512 points in single precision: one line; 512 in
+//   double, 256 in single, 768 and 1024 in either: two).
 // The four components of a tile are neighbouring blocks along y; along z a
 // sweep over the tiles takes one component (blockIdx.y) after the other: y / z
 // 2.87 / 5.19 ms with neighbouring components, 3.02 / 5.04 component after
@@ -1313,9 +1315,12 @@ SizeKernels make_size_kernels() {
     k.row_plan = radices<StepPlan<N>>();
     k.col_plan = radices<ColPlan<N>>();
     k.row = make_row_variant<R, N>();
+    // (a width that T or the LDS caps is the narrower variant's kernel again)
     k.cd[0] = make_cd_variant<R, N, 0>();
-    k.cd[1] = make_cd_variant<R, N, 1>();
-    k.cd[2] = make_cd_variant<R, N, 2>();
+    if constexpr (CdVar<R, N, 1>::W == CdVar<R, N, 0>::W) k.cd[1] = k.cd[0];
+    else k.cd[1] = make_cd_variant<R, N, 1>();
+    if constexpr (CdVar<R, N, 2>::W == CdVar<R, N, 1>::W) k.cd[2] = k.cd[1];
+    else k.cd[2] = make_cd_variant<R, N, 2>();
     k.col = make_col_variant<R, N>();
     k.row_t[0][0] = (const void*)row_t_kernel<R, N, -1, false, false>;
     k.row_t[0][1] = (const void*)row_t_kernel<R, N, -1, false, true>;
