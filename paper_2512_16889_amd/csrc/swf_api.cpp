@@ -281,8 +281,9 @@ static void add_items(Plan& P, Group& g, int fp64) {
 
 // State arrays of solve i: Y, ACC, YS, T; A0, A1 for the partial-integration
 // BW route; all eight (the Dormand-Prince slopes) with that stepper.  The
-// interaction-picture stepper uses the first four; the six it reserves keep the
-// workspace size that callers have seen.
+// interaction-picture stepper works in the first four; A0 and A1 are reserved and
+// stay unused, since the interface gives its need as six arrays, between the
+// other two steppers'.
 static int nbufs(const Plan& P, size_t i) { return P.dp5 ? swf::NBUF : (P.aux[i] || P.ip ? 6 : 4); }
 
 static int build_plan(Plan& P, std::string& err, const swf_grid* grids, int n_grids, const swf_term* terms,
