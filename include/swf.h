@@ -166,9 +166,9 @@ typedef struct {
                                exact in Fourier space, the field terms -i V (psi_s +
                                psi_b) by the classical tableau; four free-evolution
                                transforms of a whole state per step, six state arrays
-                               per solve reserved (four in use), BW integrals with the RK4 weights over its
-                               stage inputs; not with bw_partial or the persistent 1D
-                               kernel                                                   */
+                               per solve reserved (four in use), BW integrals with the
+                               RK4 weights over its stage inputs; not with bw_partial or
+                               the persistent 1D kernel                                 */
     int graph_steps;        /* with use_graph: > 1 also captures that many consecutive
                                time steps as one graph, replayed while at least that
                                many steps remain (the one-step graph takes the rest,

@@ -72,8 +72,8 @@ constexpr int NVAR = 3;       // tile variants of the stepping column passes
 constexpr int imax(int a, int b) { return a > b ? a : b; }
 constexpr int imin(int a, int b) { return a < b ? a : b; }
 
-// Tile of the row kernel (whole-state transforms and right-hand side): the
-// default plan, T threads per x-line, up to 256 threads per block.
+// Tile of the row kernel (inverse along the only axis, right-hand side, source):
+// the default plan, T threads per x-line, up to 256 threads per block.
 template <class R, int N> struct RowVar {
     using PL = FftPlan<N>;
     static constexpr int T = PL::T;
@@ -84,8 +84,8 @@ template <class R, int N> struct RowVar {
     static_assert(plan_ok<N, T, PL>(), "row tile violates the FFT plan constraints");
 };
 
-// Tile of the last-axis pass with four components in each thread: a full
-// 128-byte line of columns, up to 512 threads.
+// Tile of the last-axis pass with four components in each thread: as much of a
+// 128-byte line of columns as 512 threads hold.
 template <class R, int N> struct ColVar {
     using PL = SmallPlan<N>;
     static constexpr int T = PL::T;
@@ -113,10 +113,9 @@ template <class C> __device__ __forceinline__ void gstore(gptr<nv2<decltype(C::x
     v.y = c.y;
     p[i] = v;
 }
-// streaming (non-temporal) load and store for the stepping passes: they read
-// and write each line once per launch, and nothing touches the line again
-// before the whole batch has been swept, so caching it only evicts other data
-// (the column tiles cover whole 128-byte lines).
+// streaming (non-temporal) load and store: the stepping passes read and write
+// each line once per launch, so caching it mostly evicts other data (the column
+// tiles cover whole 128-byte lines).
 template <class C> __device__ __forceinline__ C gload_nt(gptr<const nv2<decltype(C::x)>> p, long long i) {
     const nv2<decltype(C::x)> v = __builtin_nontemporal_load(&p[i]);
     return cmake<C>(v.x, v.y);
@@ -394,9 +393,9 @@ template <bool NT = true, class C> __device__ __forceinline__ void gstore_at(gpt
 }
 
 // Column derivative pass: a block transforms the component alpha^j takes for
-// output component q of one tile along axis j = AXIS (y or z), multiply by k_j / n_j, transform back, and write (ACCUM = 0) or add
-// (ACCUM = 1) the result, with alpha^j's phase, into component q of the G
-// buffer (a.dst).  a.src: the stage input.  One component per thread: E
+// output component q of one tile along axis j = AXIS (y or z), multiplies by
+// k_j / n_j, transforms back, and writes (ACCUM = 0) or adds (ACCUM = 1) the
+// result, with alpha^j's phase, into component q of the G buffer (a.dst).  a.src: the stage input.  One component per thread: E
 // points of the transform in registers, exchanged through LDS: as real and
 // imaginary parts in turn where whole numbers would leave a compute unit room
 // for one workgroup (SPLIT), so that one's loads cover another's transform.
