@@ -1919,6 +1919,15 @@ swf_status swf_init(const swf_grid* grids, int n_grids, const swf_term* terms, c
     INITCHK(hipStreamCreateWithFlags(&ctx->st, hipStreamNonBlocking));
     INITCHK(hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming));
     INITCHK(hipEventCreateWithFlags(&ctx->ev_out, hipEventDisableTiming));
+    {
+        // the caller's queued work on the workspace comes first (a stream under
+        // capture has none, and must not take this call into its graph; the null
+        // stream refuses the question while others capture)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        const bool known = hipStreamIsCapturing(ctx->user, &cap) == hipSuccess;
+        if (!known) (void)hipGetLastError();
+        if (known && cap == hipStreamCaptureStatusNone && enter(ctx)) return fail(SWF_E_HIP);
+    }
     Plan& P = ctx->P;
     if (opt->workspace) {
         if (opt->workspace_bytes < P.total) {

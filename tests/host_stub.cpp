@@ -16,6 +16,12 @@ namespace {
 std::map<std::string, int> g_fail, g_count;
 int g_step_add = -1;         // of the last stage constants
 const int* g_step = nullptr; // the device step counter
+std::string g_log;           // ordering calls and writes to memory, with the streams' names
+bool g_capturing = false;    // the caller's stream is
+
+char own_stream[1];
+const char* stream_name(hipStream_t s) { return s == (hipStream_t)own_stream ? "own" : "caller"; }
+void log(const char* what, hipStream_t s) { g_log += std::string(what) + " " + stream_name(s) + "\n"; }
 
 hipError_t call(const char* name) {
     ++g_count[name];
@@ -32,6 +38,9 @@ int stub_count(const char* name) { return g_count[name]; }
 void stub_clear(void) { g_count.clear(); }
 int stub_step_add(void) { return g_step_add; }
 int stub_step(void) { return g_step ? *g_step : -1; }
+const char* stub_log(void) { return g_log.c_str(); }
+void stub_clear_log(void) { g_log.clear(); }
+void stub_capturing(int on) { g_capturing = on != 0; }
 
 // ---- HIP runtime
 hipError_t hipMalloc(void** p, size_t n) {
@@ -42,11 +51,13 @@ hipError_t hipFree(void* p) {
     free(p);
     return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    log("write", st);
     memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
+    log("write", st);
     memset(d, v, n);
     return hipSuccess;
 }
@@ -59,12 +70,19 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
-    *s = nullptr;
+    *s = (hipStream_t)own_stream;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+    *status = g_capturing && s != (hipStream_t)own_stream ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+    log("wait", s);
+    return hipSuccess;
+}
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSupported; }
 hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t) { return hipErrorNotSupported; }
@@ -80,12 +98,16 @@ hipError_t hipEventDestroy(hipEvent_t e) {
     free((void*)e);
     return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t s) {
+    log("record", s);
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
     *ms = 1.0f;
     return hipSuccess;
 }
+hipError_t hipGetLastError(void) { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "stub error"; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* s) {

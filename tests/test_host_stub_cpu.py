@@ -1,5 +1,6 @@
 """The solver's host code on stand-ins for the HIP runtime and the launchers
-(host_stub.cpp): failures of launches, which no test may provoke on a GPU."""
+(host_stub.cpp): failures of launches, which no test may provoke on a GPU, what
+the kernel statistics count, and the order of streams."""
 import ctypes as C
 import os
 import shutil
@@ -40,6 +41,7 @@ def lib(S, tmp_path_factory):
     lib.swf_last_error.argtypes = [C.c_void_p]
     lib.stub_fail.argtypes = [C.c_char_p, C.c_int]
     lib.stub_count.argtypes = [C.c_char_p]
+    lib.stub_log.restype = C.c_char_p
     return lib
 
 
@@ -117,3 +119,18 @@ def test_every_launch_of_a_step_is_timed(S, lib, scheme, vertices):
             array = 4 * 16 * (64 if vertices else 64 * 64) * 2          # of both solves, in double
             points = 2 + (4 + 5 if vertices else 4) + 3
             assert moved == 3 * array * (points + 4 * (4 if vertices else 6))
+
+
+def test_init_waits_for_the_callers_stream(S, lib):
+    """The workspace is the caller's memory: what the caller has queued on it comes before the first upload.  A
+    stream that is being captured has nothing to wait for, and is left alone."""
+    prob = W.config_2d(n=64, L=160.0, n_solves=1, steps=10)
+    for capturing in (0, 1):
+        lib.stub_clear_log()
+        lib.stub_capturing(capturing)
+        with Context(S, lib, prob):
+            calls = lib.stub_log().decode().splitlines()
+        lib.stub_capturing(0)
+        before = calls[:calls.index("write own")]
+        assert before == ([] if capturing else ["record caller", "wait own"])
+        assert "record caller" not in calls[len(before):] and "write caller" not in calls
