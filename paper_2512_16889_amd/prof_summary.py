@@ -11,12 +11,16 @@ JSON, the HBM bytes per dispatch of every kernel in the first two arguments
 (FETCH_SIZE and WRITE_SIZE, KiB per dispatch; each may be a comma-separated
 list of files, e.g. runs with different tile variants forced), each scaled by
 what the same counter reads for a plain device copy of ``copy_bytes`` bytes
-each way, and the sha256 of the kernel sources they were taken from.
+each way, and the sha256 of the kernel sources they were taken from.  The tile
+variants 0 to 3 that a run can be forced to name the row pass' one form, and 3
+the widest column tile: those numbers get the entry of the kernel they run
+(``same_as``).
 """
 from __future__ import annotations
 
 import csv
 import json
+import re
 import statistics
 import sys
 
@@ -83,6 +87,11 @@ def traffic(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, copy_bytes):
             continue
         kern[name] = {"dispatches": len(f[name]), "fetch_bytes": statistics.mean(f[name]) * fs,
                       "write_bytes": statistics.mean(w[name]) * ws}
+    for name in list(kern):
+        m = re.match(r"(void swf::(row|col)_d_kernel<\w+, \d+, )(\d)(, .*)", name)
+        same = {("row", "0"): "123", ("col", "2"): "3"}.get((m[2], m[3]), "") if m else ""
+        for v in same:
+            kern.setdefault(m[1] + v + m[4], dict(kern[name], same_as=name))
     return {"kernel_source_sha256": source_hash(), "fetch_scale": fs, "write_scale": ws, "kernels": kern}
 
 
